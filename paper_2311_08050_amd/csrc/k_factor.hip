@@ -47,25 +47,37 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 // LDS-resident FP64 pass of 34 KB: L_jj overwrites the lower triangle and
 // X = L_jj^{-1} (lower triangular) is built in the strict upper triangle,
 // transposed, with its diagonal 1 / L_cc kept apart.
-// Cholesky by sub-panels of width 16: an unblocked 16 x 16 Cholesky held in
-// registers of wave 0 (lane r owns row r, pivots and columns broadcast with
-// readlane), a forward-substitution TRSM of the rows below (one thread per
-// row, reciprocal pivots), and the rank-16 update of the rest (row in
-// registers, column values broadcast from LDS).  Inverse by 16 x 16 blocks:
-// X_ii = L_ii^{-1} (one wave per block, one lane per column), then
-// X_ij = -X_ii (L_ij X_jj + ... + L_i,i-1 X_i-1,j) by distance i - j.
+//
+// Bound by a serial chain (64 pivots), so everything that is not the chain is
+// taken off it.  By 16-wide sub-panels J:
+//  1. Wave 0 eliminates in registers.  Lane p stands for row p of the block; its
+//     column b[] of 16 values is what the row operations on the sub-panel's
+//     diagonal block turn into a result: for rows below the block their L, for
+//     rows above it the inverse's entries of the sub-panel, for the block's own
+//     rows (identity columns) its inverse.  Every group of 16 lanes also holds
+//     the diagonal block itself (column q in lane q), so that a multiplier is one
+//     broadcast inside the group.  Per pivot one reciprocal; the column scalings
+//     1 / sqrt(d_c) follow after the last pivot.
+//  2. The rank-16 update of everything below, of the matrix and of the inverse's
+//     rows alike: the lower 16 x 16 blocks (I, C), I > J, as FP64 MFMA products
+//     of the sub-panel's rows; block (I, C) with C <= J is the inverse's.  The
+//     four blocks that the next sub-panel reads come first, one per wave; waves
+//     1 .. 3 do the others while wave 0 eliminates the next sub-panel.
+// One block of potf2_inv_kernel takes 14.5 us (35.4 us with substitution per
+// column, rank-16 updates in vector arithmetic and the inverse by blocks after the
+// factor); about 5,700 cycles per sub-panel, 2,300 of them the elimination.
 // --------------------------------------------------------------------------
 struct Potf2Lds {
-  double M[NBI][NBI + 1];   // lower: the block, then L; strict upper: X[a][b] at M[b][a] (a > b)
+  double M[NBI][NBI + 1];   // lower: the block, then L; strict upper: X[a][b] at M[b][a] (a > b).  On entry
+                            // the 16 x 16 diagonal blocks are whole (symmetric), the rest above zero
   double rd[NBI];           // reciprocal pivots 1 / L_cc = X[c][c]
   int fail;
 };
 
-__device__ __forceinline__ double lane_bcast(double v, int l) {
+// Lane C of each group of 16 lanes, broadcast in the group.
+template <int C> __device__ __forceinline__ double row_lane(double v) {
   const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __hiloint2double(hi, lo);
+  return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, b, 0x150 + C, 0xf, 0xf, true));
 }
 
 // X = L^{-1} element (a, b), a >= b, from its packed place.
@@ -90,135 +102,164 @@ __device__ __forceinline__ void sqrt_rsqrt(double x, double &sq, double &rs) {
   rs = 2.0 * h;
 }
 
-// S.M's lower triangle holds the block (upper triangle ignored), S.fail = 0;
-// all of it visible to the block.  On return the lower triangle holds L_jj,
-// S.rd its reciprocal pivots, S.fail the first failing pivot (1-based) or 0.
-__device__ __forceinline__ void potf2_factor(Potf2Lds &S, int tid) {
-  constexpr int W = 16;
-  for (int jb = 0; jb < NBI; jb += W) {
-    // 1. 16 x 16 diagonal Cholesky in wave 0
-    if (tid < 64) {
-      const int r = tid & (W - 1);
-      double a[W];
+// Elimination of the diagonal block d[] (column q in lane q of each 16-lane
+// group), applied to the columns b[] as well; dv receives pivot c in lane c of
+// each group.  With u = column / pivot, row r is updated by (row r of column c) u.
+// 1 / pivot is the hardware estimate x (relative error e below 2^-20) corrected
+// to x (1 + e + e^2).  SAFE scales each pivot into range first (where 1 / pivot
+// would overflow or lose bits).  Step C updates the rows below C with ud, ub and
+// forms the next pivot's from row C + 1 as soon as that is done, so that the
+// reciprocal's latency is covered by the other rows.
+template <int C, bool SAFE>
+__device__ __forceinline__ void potf2_ratio(const double (&d)[16], const double (&b)[16], double &dv, double &ud,
+                                            double &ub) {
+  double pv = row_lane<C>(d[C]), dc = d[C], bc = b[C];
+  if ((threadIdx.x & 15) == C) dv = pv;
+  if constexpr (SAFE) {
+    const double sc = pv < 1.0 ? 0x1p600 : 0x1p-600;
+    pv *= sc;
+    dc *= sc;
+    bc *= sc;
+  }
+  const double x = __builtin_amdgcn_rcp(pv);
+  const double e = fma(-pv, x, 1.0), dx = dc * x, bx = bc * x, t = fma(e, e, e);
+  ud = fma(dx, t, dx);
+  ub = fma(bx, t, bx);
+}
+template <int C, bool SAFE>
+__device__ __forceinline__ void potf2_step(double (&d)[16], double (&b)[16], double &dv, double ud, double ub) {
+  if constexpr (C < 15) {
+    const double m = -row_lane<C>(d[C + 1]);
+    d[C + 1] = fma(m, ud, d[C + 1]);
+    b[C + 1] = fma(m, ub, b[C + 1]);
+    double udn, ubn;
+    potf2_ratio<C + 1, SAFE>(d, b, dv, udn, ubn);
 #pragma unroll
-      for (int cc = 0; cc < W; ++cc) a[cc] = cc <= r ? S.M[jb + r][jb + cc] : 0.0;
-      int bad = 0;
-#pragma unroll
-      for (int c = 0; c < W; ++c) {
-        double dcc = lane_bcast(a[c], c);
-        if (!(dcc > 0.0)) {
-          if (bad == 0) bad = jb + c + 1;
-          dcc = __builtin_nan("");
-        }
-        double sd, rs;
-        sqrt_rsqrt(dcc, sd, rs);
-        const double l = (r == c) ? sd : a[c] * rs;
-        a[c] = l;
-        if (tid == 0) S.rd[jb + c] = rs;
-#pragma unroll
-        for (int cc = c + 1; cc < W; ++cc) a[cc] -= l * lane_bcast(l, cc);
-      }
-      if (tid < W) {
-#pragma unroll
-        for (int cc = 0; cc < W; ++cc)
-          if (cc <= r) S.M[jb + r][jb + cc] = a[cc];
-      }
-      if (tid == 0 && bad != 0 && S.fail == 0) S.fail = bad;
+    for (int r = C + 2; r < 16; ++r) {
+      const double mr = -row_lane<C>(d[r]);
+      d[r] = fma(mr, ud, d[r]);
+      b[r] = fma(mr, ub, b[r]);
+      asm volatile("" : "+v"(b[r]));   // here and not after the last pivot, with every multiplier kept until then
+      if (r == 8) __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    // 2. TRSM of the block rows below the sub-panel
-    const int R = NBI - (jb + W);
-    if (tid < R) {
-      const int r = jb + W + tid;
-      double x[W];
-#pragma unroll
-      for (int c = 0; c < W; ++c) x[c] = S.M[r][jb + c];
-#pragma unroll
-      for (int c = 0; c < W; ++c) {
-        double s = x[c];
-#pragma unroll
-        for (int m = 0; m < c; ++m) s -= x[m] * S.M[jb + c][jb + m];
-        x[c] = s * S.rd[jb + c];
-      }
-#pragma unroll
-      for (int c = 0; c < W; ++c) S.M[r][jb + c] = x[c];
-    }
-    __syncthreads();
-    // 3. rank-16 update of the lower triangle of columns [jb + 16, 64)
-    if (R > 0) {
-      const int nsplit = 256 / R;
-      const int rr = tid % R, part = tid / R;
-      if (part < nsplit) {
-        const int r = jb + W + rr;
-        double p[W];
-#pragma unroll
-        for (int m = 0; m < W; ++m) p[m] = S.M[r][jb + m];
-        const int per = (R + nsplit - 1) / nsplit;
-        const int cb = jb + W + part * per;
-        const int ce = min(cb + per, r + 1);
-        for (int c = cb; c < ce; ++c) {
-          double s = S.M[r][c];
-#pragma unroll
-          for (int m = 0; m < W; ++m) s -= p[m] * S.M[c][jb + m];
-          S.M[r][c] = s;
-        }
-      }
-    }
-    __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);   // one step's multipliers in registers at a time
+    potf2_step<C + 1, SAFE>(d, b, dv, udn, ubn);
+  }
+}
+template <bool SAFE> __device__ __forceinline__ void potf2_eliminate(double (&d)[16], double (&b)[16], double &dv) {
+  double ud, ub;
+  potf2_ratio<0, SAFE>(d, b, dv, ud, ub);
+  potf2_step<0, SAFE>(d, b, dv, ud, ub);
+}
+
+// Rows c of both column sets scaled by 1 / sqrt(pivot c) (rs of lane c).
+template <int C> __device__ __forceinline__ void potf2_scale(double (&d)[16], double (&b)[16], double rs) {
+  if constexpr (C < 16) {
+    const double f = row_lane<C>(rs);
+    d[C] *= f;
+    b[C] *= f;
+    potf2_scale<C + 1>(d, b, rs);
   }
 }
 
-// X = L^{-1} into the strict upper triangle (transposed) after potf2_factor.
-__device__ __forceinline__ void potf2_invert(Potf2Lds &S, int tid) {
-  constexpr int W = 16;
-  // X_ii: wave i, lane c < 16 solves L_ii x = e_c by forward substitution
-  {
-    const int o = W * (tid >> 6), c = tid & 63;
-    if (c < W) {
-      double x[W];
+// Block (I, C) of the update by sub-panel J: block -= P_I P_C^T over its 16
+// columns, P_p = M[p][16 J ..] (for the sub-panel's own rows: its diagonal
+// block's inverse).  One wave; I, C and J are uniform.
+__device__ __forceinline__ void potf2_block(Potf2Lds &S, int I, int C, int J) {
+  constexpr int W = 16, LD = NBI + 1;
+  const int lane = threadIdx.x & 63, q = lane & (W - 1), g = lane >> 4, jb = W * J;
+  double *M = &S.M[0][0];
+  // element v of a lane: row g + 4 v of block row I, column q of block column C;
+  // a block of the inverse is stored transposed
+  const bool tr = C <= J;
+  double *at = M + (tr ? (W * C + q) * LD + W * I + g : (W * I + g) * LD + W * C + q);
+  const int step = tr ? 4 : 4 * LD;
+  const double *PI = M + (W * I + q) * LD + jb + g, *PC = M + (W * C + q) * LD + jb + g;
+  double pi[4], pc[4];
+  d4 acc;
 #pragma unroll
-      for (int r = 0; r < W; ++r) {
-        double s = 0.0;
-#pragma unroll
-        for (int m = 0; m < r; ++m) s += S.M[o + r][o + m] * x[m];
-        x[r] = r < c ? 0.0 : (r == c ? S.rd[o + r] : -S.rd[o + r] * s);
-      }
-#pragma unroll
-      for (int r = 1; r < W; ++r)
-        if (r > c) S.M[o + c][o + r] = x[r];
-    }
+  for (int s = 0; s < 4; ++s) {
+    pi[s] = PI[4 * s];
+    pc[s] = PC[4 * s];
   }
-  __syncthreads();
-  // X_ij (i > j) by distance: T = sum_{k=j}^{i-1} L_ik X_kj, then X_ij = -X_ii T;
-  // thread (r, c) = (tid / 16, tid % 16) of each block at that distance
-  const int r = tid >> 4, c = tid & 15;
+  const double xd = S.rd[jb + q];
 #pragma unroll
-  for (int dist = 1; dist < NBI / W; ++dist) {
-    const int nblk = NBI / W - dist;
-    double t[NBI / W - 1];
+  for (int v = 0; v < 4; ++v) acc[v] = at[v * step];
 #pragma unroll
-    for (int q = 0; q < nblk; ++q) {
-      const int i = q + dist, j = q, ar = W * i + r, bc = W * j + c;
-      double s = 0.0;
-      for (int k = j; k < i; ++k)
-        for (int m = (k == j ? c : 0); m < W; ++m) s += S.M[ar][W * k + m] * xinv(S, W * k + m, bc);
-      t[q] = s;
+  for (int s = 0; s < 4; ++s) {
+    const int k = 4 * s + g;
+    const double own = k > q ? pc[s] : k == q ? xd : 0.0;
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-pi[s], C == J ? own : pc[s], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) at[v * step] = acc[v];
+}
+
+// Element (r, c) of the block to factor into its place (and its mirror image
+// inside a diagonal 16 x 16 block); elements above the diagonal are ignored.
+__device__ __forceinline__ void potf2_put(Potf2Lds &S, int r, int c, double v) {
+  if (r >= c) {
+    S.M[r][c] = v;
+    if ((r ^ c) < 16) S.M[c][r] = v;
+  } else if ((r ^ c) >= 16) {
+    S.M[r][c] = 0.0;
+  }
+}
+
+// The block is in S.M (potf2_put), S.fail is 0; all of it visible to the block.  On return the lower triangle holds
+// L_jj, the upper triangle and S.rd the inverse, S.fail the first failing pivot
+// (1-based) or 0.
+__device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, int tid) {
+  constexpr int W = 16, NJ = NBI / W, LD = NBI + 1;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double *M = &S.M[0][0];
+#pragma unroll 1
+  for (int J = 0; J < NJ; ++J) {
+    const int jb = J * W;
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));   // addresses are formed again for each J: kept, they would be spilled
+    const int q = lane & (W - 1);
+    if (w == 0) {
+      const bool own = (lane >> 4) == J;   // the diagonal block's rows
+      double d[W], b[W], dv = 1.0;
+      auto load = [&] {
+#pragma unroll
+        for (int r = 0; r < W; ++r) {
+          d[r] = M[(jb + q) * LD + jb + r];
+          const double m = M[lane * LD + jb + r];
+          b[r] = own ? (r == q ? 1.0 : 0.0) : m;
+        }
+      };
+      load();
+      potf2_eliminate<false>(d, b, dv);
+      if (__any(!(dv > 0x1p-900 && dv < 0x1p900))) {
+        load();
+        potf2_eliminate<true>(d, b, dv);
+        const unsigned long long neg = __ballot(!(dv > 0.0));
+        if (neg && lane == 0 && S.fail == 0) S.fail = jb + __ffsll(neg);
+      }
+      double sq, rs;
+      sqrt_rsqrt(dv, sq, rs);   // not a number for a negative pivot
+      potf2_scale<0>(d, b, rs);
+#pragma unroll
+      for (int r = 0; r < W; ++r)
+        M[lane * LD + jb + r] = own && r <= q ? (r == q ? sq : d[r]) : b[r];
+      if (own) S.rd[lane] = rs;
+    } else if (J == 1) {
+      if (w == 3) {
+        potf2_block(S, 3, 3, 0);
+      } else {
+        potf2_block(S, w + 1, 0, 0);
+        potf2_block(S, w + 1, 2, 0);
+      }
+    } else if (J == 2) {
+      potf2_block(S, 3, w == 3 ? 3 : w - 1, 1);
     }
-    // T goes to X_ij's place, so that every thread can read all of it
-#pragma unroll
-    for (int q = 0; q < nblk; ++q) S.M[W * q + c][W * (q + dist) + r] = t[q];
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < nblk; ++q) {
-      const int i = q + dist, j = q;
-      double s = 0.0;
-      for (int m = 0; m <= r; ++m) s += xinv(S, W * i + r, W * i + m) * S.M[W * j + c][W * i + m];
-      t[q] = -s;
+    if (J + 1 < NJ) {
+      potf2_block(S, max(w, J + 1), min(w, J + 1), J);
+      __syncthreads();
     }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < nblk; ++q) S.M[W * q + c][W * (q + dist) + r] = t[q];
-    __syncthreads();
   }
 }
 
@@ -254,12 +295,11 @@ __global__ __launch_bounds__(256) void potf2_inv_kernel(const FactorDesc *__rest
 #pragma unroll
   for (int i = 0; i < NBI * NBI / 256; ++i) {
     const int e = tid + 256 * i, r = e & (NBI - 1), c = e >> 6;
-    S.M[r][c] = (r >= c) ? (double)v[i] : 0.0;
+    potf2_put(S, r, c, (double)v[i]);
   }
   if (tid == 0) S.fail = 0;
   __syncthreads();
-  potf2_factor(S, tid);
-  potf2_invert(S, tid);
+  potf2_factor_invert(S, tid);
   potf2_store<T>(S, d, j, Ad, tid);
 }
 
@@ -547,7 +587,7 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 //   A[I,I] -= L[I,j] L[I,j]^T                      (tiles with r0 < pend: the
 //                                                  diagonal block's update)
 // The tile just below the diagonal block (t = 0) then holds the next diagonal
-// block fully updated and factors and inverts it (potf2_factor, potf2_invert)
+// block fully updated and factors and inverts it (potf2_factor_invert)
 // in the same launch, so a panel takes one potf2_inv launch and one launch per
 // block column.  Each tile reads its own rows of the panel's earlier columns
 // and writes one 64 x 64 block, in place of the right-looking rank-64 updates
@@ -764,12 +804,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r = rl(a, v), c = cl(b, v);
-        S.f.M[r][c] = (r >= c) ? (double)(T)(Dg[c * ld + r] - acc[a][b][v]) : 0.0;
+        potf2_put(S.f, r, c, (double)(T)(Dg[c * ld + r] - acc[a][b][v]));
       }
   if (tid == 0) S.f.fail = 0;
   __syncthreads();
-  potf2_factor(S.f, tid);
-  potf2_invert(S.f, tid);
+  potf2_factor_invert(S.f, tid);
   potf2_store<T>(S.f, d, r0, Dg, tid);
 }
 
