@@ -582,8 +582,7 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 // one 64-row tile I (rows r0 = j + 64 (t + 1) .. r0 + 63) per workgroup:
 //   C      = A[I, j] - A[I, p0:j] A[j, p0:j]^T     (the panel's earlier columns,
 //                                                  MFMA from global via LDS)
-//   L[I,j] = C L_jj^{-T}                           (MFMA, C from registers and
-//                                                  L_jj^{-1} staged in 16-deep chunks)
+//   L[I,j] = C L_jj^{-T}                           (MFMA, both operands from registers)
 //   A[I,I] -= L[I,j] L[I,j]^T                      (tiles with r0 < pend: the
 //                                                  diagonal block's update)
 // The tile just below the diagonal block (t = 0) then holds the next diagonal
@@ -602,13 +601,24 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 // the diagonal factorisations start first; the rest take tiles 1 .. gx - 1 of
 // every theta in the XCD-aware order of xcd_order (Q = ceil(act (gx - 1) / 8)).
 // --------------------------------------------------------------------------
+//
+// Wave w owns rows 16 w .. 16 w + 15 of the tile and all 64 columns, as four
+// 16 x 16 accumulator blocks whose operands are swapped in both precisions: a
+// lane holds row li of the wave and columns 16 b + kcol(v) (v = 0 .. 3).  That is
+// also the layout of an MFMA operand whose step v takes the sub-column kcol(v) of
+// lane group g, so C goes into the TRSM, and the TRSM skips the zero half of
+// L_jj^{-1}, without passing through LDS; the SYRK reads L[I,j] from LDS, only its
+// ten blocks at and below the diagonal.  Bound by the chain of tile 0 (product,
+// TRSM, SYRK, factorisation), in large batches by the MFMA products.  9 theta at
+// n = 3000 in FP64 take 29.8 us per step (35.3 us with 2 x 2 waves of 32 x 32 that
+// staged C and L_jj^{-1} through LDS in 16-deep chunks, two barriers each).
 template <typename T>
 struct PanelLds {
   static constexpr int LDC = NBI + 4;          // LDS row length (elements): conflict-free MFMA operand reads
   static constexpr int PKC = sizeof(T) == 4 ? 32 : 16;   // K chunk of the left-looking product
   union {
-    struct { T As[2][PKC][LDC]; T Bs[2][PKC][LDC]; } g;   // K chunks ([k][row]); chunk 0 also stages
-                                                           // the TRSM and SYRK operands
+    struct { T As[2][PKC][LDC]; T Bs[2][PKC][LDC]; } g;   // K chunks ([k][row])
+    T Ls[NBI][LDC];                                        // L[I, j] ([k][row])
     Potf2Lds f;                                            // the next diagonal block's factorisation
   };
 };
@@ -620,12 +630,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
                                                             int j, int act, int gx, int Q) {
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int VEC = 16 / sizeof(T);
-  constexpr int LDC = PanelLds<T>::LDC, PKC = PanelLds<T>::PKC;
-  constexpr int WTM = 32, WTN = 32, BM = 2, BN = 2;   // 2 x 2 waves, 32 x 32 wave tiles
+  constexpr int LDC = PanelLds<T>::LDC, PKC = PanelLds<T>::PKC, NB = NBI / 16;
   constexpr int LA = PKC * NBI / VEC / 256;           // 16-byte loads per thread per operand chunk
-  constexpr int LX = KC * NBI / VEC / 256;            // ... per 16-deep chunk of L_jj^{-1}
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   typedef __attribute__((address_space(1))) T gT;
+  typedef __attribute__((address_space(1))) const T gcT;
   typedef __attribute__((address_space(1))) const vec_t gcvec;
   typedef typename std::conditional<F64, d4, f4>::type acc_t;
   __shared__ __attribute__((aligned(16))) PanelLds<T> S;
@@ -653,56 +662,22 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
     ks = max(ks, r0 - d.id_row0);
   }
   const int ld = d.ld, K = j - ks;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, li = lane & 15;
-  // tile element (rl(a, v), cl(b, v)) of accumulator component v
-  auto rl = [&](int a, int v) { return wm * WTM + a * 16 + (F64 ? li : 4 * g + v); };
-  auto cl = [&](int b, int v) { return wn * WTN + b * 16 + (F64 ? g + 4 * v : li); };
-  auto zero = [&](acc_t (&c)[BM][BN]) {
-#pragma unroll
-    for (int a = 0; a < BM; ++a)
-#pragma unroll
-      for (int b = 0; b < BN; ++b) c[a][b] = acc_t{0, 0, 0, 0};
-  };
-  // c += X(64 x 16) Y(64 x 16)^T for one 16-deep chunk held [k][row] in LDS
-  auto mfma_chunk = [&](acc_t (&c)[BM][BN], const T (*X)[LDC], const T (*Y)[LDC], int k0) {
-#pragma unroll
-    for (int s = 0; s < KC / 4; ++s) {
-      const int kk = k0 + 4 * g + s;
-      T ya[BM], xb[BN];
-#pragma unroll
-      for (int a = 0; a < BM; ++a) ya[a] = X[kk][wm * WTM + a * 16 + li];
-#pragma unroll
-      for (int b = 0; b < BN; ++b) xb[b] = Y[kk][wn * WTN + b * 16 + li];
-#pragma unroll
-      for (int a = 0; a < BM; ++a)
-#pragma unroll
-        for (int b = 0; b < BN; ++b) {
-          if constexpr (F64) c[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xb[b], ya[a], c[a][b], 0, 0, 0);
-          else c[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[a], xb[b], c[a][b], 0, 0, 0);
-        }
-    }
-  };
-  // columns [k0, k0 + 16) of the tile held in accumulator layout, into LDS as [k][row]
-  auto stage_cols = [&](const acc_t (&c)[BM][BN], T (*dst)[LDC], int k0) {
-#pragma unroll
-    for (int a = 0; a < BM; ++a)
-#pragma unroll
-      for (int b = 0; b < BN; ++b)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int col = cl(b, v) - k0;
-          if (col >= 0 && col < KC) dst[col][rl(a, v)] = c[a][b][v];
-        }
+  auto kcol = [&](int v) { return F64 ? g + 4 * v : 4 * g + v; };
+  auto mfma = [&](T x, T y, acc_t c) {   // c[v] += sum over k of x (column kcol(v)'s) y (row li's)
+    if constexpr (F64) return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
+    else return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);
   };
 
   // 1. acc = A[I, ks:j] A[j, ks:j]^T, double-buffered PKC-deep chunks
-  acc_t acc[BM][BN];
-  zero(acc);
+  acc_t acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = acc_t{0, 0, 0, 0};
+  gT *Cg = gptr((T *)d.A) + (size_t)j * ld + r0 + 16 * w + li;
   if (K > 0) {
-    const __attribute__((address_space(1))) T *Ag = gptr((const T *)d.A) + (size_t)ks * ld + r0;
-    const __attribute__((address_space(1))) T *Bg = gptr((const T *)d.A) + (size_t)ks * ld + j;
+    gcT *Ag = gptr((const T *)d.A) + (size_t)ks * ld + r0;
+    gcT *Bg = gptr((const T *)d.A) + (size_t)ks * ld + j;
     vec_t ra[LA], rb[LA];
     auto gload = [&](int kc) {
 #pragma unroll
@@ -728,83 +703,101 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
       const bool more = kc + PKC < K;
       if (more) gload(kc + PKC);
 #pragma unroll
-      for (int k0 = 0; k0 < PKC; k0 += KC) mfma_chunk(acc, S.g.As[buf], S.g.Bs[buf], k0);
+      for (int s = 0; s < PKC / 4; ++s) {
+        const int kk = 16 * (s >> 2) + 4 * g + (s & 3);
+        const T y = S.g.As[buf][kk][16 * w + li];
+        T x[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) x[b] = S.g.Bs[buf][kk][16 * b + li];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b] = mfma(x[b], y, acc[b]);
+      }
       if (more) lstore(buf ^ 1);
       __syncthreads();
       buf ^= 1;
     }
   }
 
-  // 2. C = A[I, j] - acc (in acc), then L[I, j] = C L_jj^{-T} into lacc over
-  //    16-deep chunks of k (columns of block j): C's columns and rows of
-  //    L_jj^{-1} (column-major: X[n][k] at k * 64 + n) staged in LDS chunk 0
-  gT *Cg = gptr((T *)d.A) + (size_t)j * ld + r0;
+  // 2. C = A[I, j] - acc (in acc), then L[I, j] = C L_jj^{-T} into lacc: column
+  //    block n takes the column blocks k <= n of C (L_jj^{-1} column-major:
+  //    X[n][k] at k * 64 + n, zero above its diagonal)
+  gcT *Li = gptr((const T *)d.linv) + (size_t)(j / NBI) * NBI * NBI + li;
+  acc_t lacc[NB];
 #pragma unroll
-  for (int a = 0; a < BM; ++a)
+  for (int b = 0; b < NB; ++b) {
 #pragma unroll
-    for (int b = 0; b < BN; ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[a][b][v] = Cg[cl(b, v) * ld + rl(a, v)] - acc[a][b][v];
-  const __attribute__((address_space(1))) T *Li = gptr((const T *)d.linv) + (size_t)(j / NBI) * NBI * NBI;
-  acc_t lacc[BM][BN];
-  zero(lacc);
-#pragma unroll
-  for (int k0 = 0; k0 < NBI; k0 += KC) {
-    vec_t xv[LX];
-#pragma unroll
-    for (int it = 0; it < LX; ++it)
-      xv[it] = *reinterpret_cast<gcvec *>(Li + (size_t)k0 * NBI + (size_t)VEC * (it * 256 + tid));
-    stage_cols(acc, S.g.As[0], k0);
-#pragma unroll
-    for (int it = 0; it < LX; ++it) {
-      const int lin = it * 256 + tid, kk = lin / (NBI / VEC), rp = lin % (NBI / VEC);
-      *reinterpret_cast<vec_t *>(&S.g.Bs[0][kk][VEC * rp]) = xv[it];
-    }
-    __syncthreads();
-    mfma_chunk(lacc, S.g.As[0], S.g.Bs[0], 0);
-    __syncthreads();
+    for (int v = 0; v < 4; ++v) acc[b][v] = Cg[(16 * b + kcol(v)) * ld] - acc[b][v];
+    lacc[b] = acc_t{0, 0, 0, 0};
   }
 #pragma unroll
-  for (int a = 0; a < BM; ++a)
+  for (int k = 0; k < NB; ++k) {
+    T x[NB][4];
 #pragma unroll
-    for (int b = 0; b < BN; ++b)
+    for (int n = k; n < NB; ++n)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) Cg[cl(b, v) * ld + rl(a, v)] = lacc[a][b][v];
+      for (int v = 0; v < 4; ++v) x[n][v] = Li[(16 * k + kcol(v)) * NBI + 16 * n];
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int n = k; n < NB; ++n) lacc[n] = mfma(x[n][v], acc[k][v], lacc[n]);
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Cg[(16 * b + kcol(v)) * ld] = lacc[b][v];
   if (r0 >= pend) return;
 
-  // 3. diagonal block of the tile's rows: D = L[I, j] L[I, j]^T (into acc)
-  zero(acc);
-#pragma unroll
-  for (int k0 = 0; k0 < NBI; k0 += KC) {
-    stage_cols(lacc, S.g.As[0], k0);
-    __syncthreads();
-    mfma_chunk(acc, S.g.As[0], S.g.As[0], 0);
-    __syncthreads();
-  }
+  // 3. diagonal block of the tile's rows: D = L[I, j] L[I, j]^T, the blocks (I, J)
+  //    with J <= I: (0,0) (3,3) | (1,0) (1,1) | (2,0) (2,1) (2,2) | (3,0) (3,1) (3,2)
+  //    on waves 0 .. 3 (I, J below); element v of a lane: row li, column kcol(v)
+  constexpr int U = 3;
+  auto bI = [&](int u) { return w == 0 && u == 1 ? 3 : w; };
+  auto bJ = [&](int u) { return w == 0 ? (u == 1 ? 3 : 0) : u; };
+  const int nu = w < 2 ? 2 : 3;
   gT *Dg = gptr((T *)d.A) + (size_t)r0 * ld + r0;
+  T dg[U][4];
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (u < nu)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dg[u][v] = Dg[(16 * bJ(u) + kcol(v)) * ld + 16 * bI(u) + li];
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) S.Ls[16 * b + kcol(v)][16 * w + li] = lacc[b][v];
+  __syncthreads();
+  acc_t da[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    da[u] = acc_t{0, 0, 0, 0};
+    if (u < nu)
+#pragma unroll
+      for (int k = 0; k < NBI; k += 4)
+        da[u] = mfma(S.Ls[k + g][16 * bJ(u) + li], S.Ls[k + g][16 * bI(u) + li], da[u]);
+  }
   if (t != 0) {
 #pragma unroll
-    for (int a = 0; a < BM; ++a)
-#pragma unroll
-      for (int b = 0; b < BN; ++b)
+    for (int u = 0; u < U; ++u)
+      if (u < nu)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int r = rl(a, v), c = cl(b, v);
-          if (r >= c) Dg[c * ld + r] = Dg[c * ld + r] - acc[a][b][v];
+          const int r = 16 * bI(u) + li, c = 16 * bJ(u) + kcol(v);
+          if (r >= c) Dg[c * ld + r] = dg[u][v] - da[u][v];
         }
     return;
   }
 
   // 4. tile 0: the block at r0 = j + 64 has had every update of the panel's
   //    earlier columns; factor and invert it in LDS, store L and its inverse
+  __syncthreads();   // every wave has read L[I, j]
 #pragma unroll
-  for (int a = 0; a < BM; ++a)
-#pragma unroll
-    for (int b = 0; b < BN; ++b)
+  for (int u = 0; u < U; ++u)
+    if (u < nu)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int r = rl(a, v), c = cl(b, v);
-        potf2_put(S.f, r, c, (double)(T)(Dg[c * ld + r] - acc[a][b][v]));
+        const int r = 16 * bI(u) + li, c = 16 * bJ(u) + kcol(v);
+        potf2_put(S.f, r, c, (double)(T)(dg[u][v] - da[u][v]));
+        if (bI(u) != bJ(u)) S.f.M[c][r] = 0.0;
       }
   if (tid == 0) S.f.fail = 0;
   __syncthreads();
