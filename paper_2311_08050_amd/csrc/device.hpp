@@ -63,6 +63,11 @@ struct ThetaDesc {
   void *W; int ldw; int Nw; int Ncw;    // big working matrix (double or float): Nw rows, Ncw columns
   double *S; int lds; int Ns; int k_pad;   // small (kriging) system working matrix
   double *P; int ldp; int Np; int ns_pad;  // prior-build working matrix
+  // structured prior pass (behind P): KRON n_t matrices of kN x kN, the
+  // constraint rows in the temporal eigenbasis (Ct) and the basis's cosines;
+  // EXPCOV the rows C L (Ct, k x n_pad)
+  double *K; int kN;
+  double *Ct, *ctab;
   double *x;       // current iterate / linearisation point [n_pad]
   double *r;       // right-hand side / new iterate [n_pad]
   double *xn;      // refined new iterate [n_pad] (mixed precision)

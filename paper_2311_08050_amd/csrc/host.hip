@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <limits>
+#include <tuple>
 
 #include "device.hpp"
 #include "host.hpp"
@@ -447,7 +448,19 @@ struct Plan {
          bytes = 0;
   int ns_real = 0;
   bool needs_prior_build = false;
+  // structured prior pass, in the region of W behind P
+  bool structured = false;
+  size_t off_K = 0, off_klinv = 0, off_ctab = 0, off_Ct = 0;
 };
+
+// The structured prior pass applies to priors the library builds: KRON as n_t
+// blocks of order n_s (padded to PADN, with the padded constraint rows below), as
+// long as its matrices fit the working matrix's region or 128 MB, whichever is
+// more (only long, narrow fields do not: n_t above 200 with n_s padded several
+// times over); EXPCOV for up to 16 constraint rows, whose products it
+// forms one by one.  Everything else takes the bordered factorisation of Q_prior.
+static constexpr size_t STRUCTURED_MIN = (size_t)128 << 20;
+static constexpr int STRUCTURED_MAX_NT = 4096, STRUCTURED_MAX_K = 16;
 
 enum Mode { MODE_LAPLACE = 0, MODE_VAR = 1, MODE_LOGDET = 2 };
 
@@ -511,7 +524,23 @@ static Plan make_plan(const inla_model &m, const double *th, Mode mode, bool aux
   p.off_W = off;
   const size_t wbytes = sizeof(double) * (size_t)t.ldw * t.Ncw;
   const size_t pbytes = sizeof(double) * (size_t)t.ldp * t.Np;
-  off += align256(std::max(wbytes, pbytes));
+  size_t rbytes = std::max(wbytes, pbytes);
+  if (mode == MODE_LAPLACE && !aux && p.needs_prior_build) {
+    size_t o = align256(pbytes);
+    if (m.prior == PRIOR_KRON) {
+      t.kN = t.ns_pad + t.k_pad;
+      p.off_K = o;     o += align256(sizeof(double) * (size_t)m.n_t * t.kN * t.kN);
+      p.off_klinv = o; o += align256(sizeof(double) * (size_t)m.n_t * t.ns_pad * NBI);
+      p.off_ctab = o;  o += align256(sizeof(double) * 4 * (size_t)m.n_t);
+      p.off_Ct = o;    o += align256(sizeof(double) * (size_t)m.n * m.k);
+      p.structured = m.n_t <= STRUCTURED_MAX_NT && o <= std::max(rbytes, STRUCTURED_MIN);
+    } else {
+      p.off_Ct = o;    o += align256(sizeof(double) * (size_t)m.k * t.n_pad);
+      p.structured = m.k <= STRUCTURED_MAX_K;
+    }
+    if (p.structured) rbytes = std::max(rbytes, o);
+  }
+  off += align256(rbytes);
   p.off_S = off; off += align256(sizeof(double) * (size_t)t.lds * std::max(t.k_pad, 1));
   p.off_vec = off;
   off += align256(sizeof(double) * (size_t)(5 * t.n_pad + 3 * std::max(t.k_pad, 64) + 2 * t.ldw + DRES_COUNT));
@@ -536,6 +565,9 @@ static void bind(Plan &p, char *base) {
   t.Qp = (double *)(base + p.off_Qp);
   t.W = (void *)(base + p.off_W);
   t.P = (double *)t.W;   // the prior build finishes before the working matrix is assembled
+  t.K = (double *)(base + p.off_W + p.off_K);
+  t.ctab = (double *)(base + p.off_W + p.off_ctab);
+  t.Ct = (double *)(base + p.off_W + p.off_Ct);
   t.S = (double *)(base + p.off_S);
   double *v = (double *)(base + p.off_vec);
   t.x = v; v += t.n_pad;
@@ -663,6 +695,72 @@ static int prior_build(Batch &b, const std::vector<int> &ids) {
   double bytes = 0;
   for (int i : ids) bytes += 8.0 * 0.5 * b.plans[i].t.n * (b.plans[i].t.n + 1.0);
   launch_prior_assemble(b.ctx, d, (int)ids.size(), max_over(b, ids, &ThetaDesc::n_pad), bytes);
+  return b.ctx.check();
+}
+
+// The structured prior pass of `ids` (all of them planned for it; the prior build
+// has just run and P is intact): log|Q_prior| and the prior's kriging system into
+// the slots that PASS_PRIOR fills.  A failed pivot sets the theta's F_BIG status,
+// whatever block it was met in.
+static int structured_prior(Batch &b, const std::vector<int> &ids) {
+  PrecScope tag(b.ctx, INLA_PREC_FP64);
+  std::vector<int> kron, expc, first;
+  std::map<std::tuple<const double *, int, int, int>, double *> seen;   // rows of one C are shared
+  for (int i : ids) {
+    ThetaDesc &t = b.plans[i].t;
+    (t.prior == PRIOR_KRON ? kron : expc).push_back(i);
+    if (t.prior != PRIOR_KRON || t.k == 0) continue;
+    const auto at = seen.emplace(std::make_tuple(t.C, t.k, t.n_s, t.n_t), t.Ct);
+    if (at.second) first.push_back(i);
+    t.Ct = at.first->second;
+  }
+  int rc;
+  if (!first.empty()) {
+    ThetaDesc *d = upload_td(b, first);
+    if (!d) return INLA_ERR_NOMEM;
+    launch_kron_rows(b.ctx, d, (int)first.size(), max_over(b, first, &ThetaDesc::n_s),
+                     max_over(b, first, &ThetaDesc::n_t), max_over(b, first, &ThetaDesc::k));
+  }
+  // batches of thetas with at most 16384 blocks (their descriptors pass through
+  // the upload ring)
+  for (size_t s = 0; s < kron.size();) {
+    std::vector<int> part;
+    std::vector<HostFactor> fs;
+    for (; s < kron.size(); ++s) {
+      const Plan &p = b.plans[kron[s]];
+      const ThetaDesc &t = p.t;
+      if (!part.empty() && fs.size() + t.n_t > 16384) break;
+      part.push_back(kron[s]);
+      for (int i = 0; i < t.n_t; ++i) {
+        HostFactor h{};
+        h.d.A = t.K + (size_t)i * t.kN * t.kN;
+        h.d.linv = (double *)(b.bases[kron[s]] + p.off_W + p.off_klinv) + (size_t)i * t.ns_pad * NBI;
+        h.d.info = b.dinfo + 4 * kron[s] + F_BIG;
+        h.d.ld = h.d.nrows = h.d.ncols = t.kN;
+        h.d.nf = t.ns_pad;
+        h.d.id_row0 = std::numeric_limits<int>::max();
+        h.n_real = t.n_s; h.kb_real = h.ks_real = t.k;
+        fs.push_back(h);
+      }
+    }
+    ThetaDesc *d = upload_td(b, part);
+    if (!d) return INLA_ERR_NOMEM;
+    launch_kron_assemble(b.ctx, d, (int)part.size(), max_over(b, part, &ThetaDesc::kN),
+                         max_over(b, part, &ThetaDesc::n_t));
+    if ((rc = factor_batch(b.ctx, fs, INLA_PREC_FP64))) return rc;
+    launch_kron_schur(b.ctx, d, (int)part.size(), max_over(b, part, &ThetaDesc::k_pad));
+  }
+  if (!expc.empty()) {
+    ThetaDesc *d = upload_td(b, expc);
+    if (!d) return INLA_ERR_NOMEM;
+    launch_expcov_schur(b.ctx, d, (int)expc.size(), max_over(b, expc, &ThetaDesc::n), max_over(b, expc, &ThetaDesc::k),
+                        max_over(b, expc, &ThetaDesc::k_pad));
+  }
+  ThetaDesc *d = upload_td(b, ids);
+  if (!d) return INLA_ERR_NOMEM;
+  launch_structured_logdet(b.ctx, d, (int)ids.size());
+  if ((rc = run_factor(b, ids, F_SMALL, MODE_LAPLACE))) return rc;
+  launch_kriging_solve(b.ctx, d, (int)ids.size());
   return b.ctx.check();
 }
 
@@ -1018,6 +1116,14 @@ static std::vector<std::pair<int, int>> chunks(Ctx &ctx, int B, const inla_model
   return out;
 }
 
+// Whether some theta's prior takes the bordered factorisation (on the aux stream
+// with overlap on).
+static bool needs_prior_factor(int B, const inla_model *models, const double *theta, int ldtheta) {
+  for (int i = 0; i < B; ++i)
+    if (!make_plan(models[i], theta + (size_t)i * ldtheta, MODE_LAPLACE).structured) return true;
+  return false;
+}
+
 // The whole per-theta evaluation for one chunk.  `prec` selects the precision
 // of the Newton and final-pass factorisations (the prior pass is always FP64).
 // A theta whose mixed-precision refinement does not converge is re-evaluated
@@ -1029,8 +1135,9 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
   // overlap on it runs on the aux stream, in its own workspace, while the
   // caller's stream runs the Newton iteration; its results are read after the
   // iteration.  Every kernel computes what it would in order, so the results
-  // are identical either way.
-  const bool overlap = ctx.overlap && ctx.aux_ready() == INLA_OK;
+  // are identical either way.  Priors of the structured pass need neither: it
+  // runs in order, ahead of the Newton iteration.
+  const bool overlap = ctx.overlap && needs_prior_factor(B, models, theta, ldtheta) && ctx.aux_ready() == INLA_OK;
   Batch b(ctx), pb(ctx);
   int rc = setup(b, B, models, theta, ldtheta, MODE_LAPLACE, overlap ? &pb : nullptr);
   if (rc) { (void)ctx.sync_all(); teardown(pb); teardown(b); return rc; }
@@ -1076,8 +1183,39 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
     return true;
   };
   if ((rc = prior_build(b, all))) return fail(rc);
-  if (overlap) {
-    if (!all.empty()) {
+  std::vector<int> fact;   // priors to factor
+  {
+    std::vector<int> str;
+    for (int i : all) (b.plans[i].structured ? str : fact).push_back(i);
+    if (!str.empty()) {
+      if ((rc = structured_prior(b, str))) return fail(rc);
+      if ((rc = readback(b))) return fail(rc);
+      bool refused = false;
+      std::vector<int> build;
+      for (int i : str) {
+        // any failure is left to the general pass, which names the failing minor
+        // of Q_prior itself
+        if (b.hinfo[4 * i + F_PRIOR] == 0 && std::isfinite(b.hdres[DRES_COUNT * i + DRES_LOGDET_L]) && prior_ok(b, i)) {
+          ok.push_back(i);
+        } else {
+          res[i] = inla_result{};
+          fact.push_back(i);
+          refused = true;
+        }
+      }
+      if (refused) {
+        std::sort(fact.begin(), fact.end());
+        for (int i : fact)
+          if (b.plans[i].structured &&
+              (hipMemsetAsync(b.dinfo + 4 * i + F_BIG, 0, sizeof(int) * 2, ctx.stream) != hipSuccess ||
+               hipMemsetAsync(b.plans[i].t.dres, 0, sizeof(double) * DRES_COUNT, ctx.stream) != hipSuccess))
+            return fail(INLA_ERR_HIP);
+      }
+    }
+  }
+  const bool aux = overlap && !fact.empty();
+  if (aux) {
+    {
       // the prior build's status travels with the prior pass's (the Newton
       // iteration clears the main batch's status slots)
       if (hipMemcpyAsync(pb.dinfo, b.dinfo, sizeof(int) * 4 * B, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess ||
@@ -1085,18 +1223,19 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
         return fail(INLA_ERR_HIP);
       {
         AuxScope lane(ctx);
-        rc = run_pass(pb, all, PASS_PRIOR, INLA_PREC_FP64);
+        rc = run_pass(pb, fact, PASS_PRIOR, INLA_PREC_FP64);
       }
       if (rc) return fail(rc);
       if (hipEventRecord(ctx.ev_d, ctx.aux) != hipSuccess) return fail(INLA_ERR_HIP);
     }
-    ok = all;   // prior failures are sorted out after the Newton iteration
-  } else {
-    if ((rc = run_pass(b, all, PASS_PRIOR, INLA_PREC_FP64))) return fail(rc);
+    ok.insert(ok.end(), fact.begin(), fact.end());   // prior failures are sorted out after the Newton iteration
+  } else if (!fact.empty()) {
+    if ((rc = run_pass(b, fact, PASS_PRIOR, INLA_PREC_FP64))) return fail(rc);
     if ((rc = readback(b))) return fail(rc);
-    for (int i : all)
+    for (int i : fact)
       if (prior_ok(b, i)) ok.push_back(i);
   }
+  std::sort(ok.begin(), ok.end());
   // Newton iteration (warm-start vectors were checked for finiteness by the
   // first assembly: a non-finite W or b sets the flag).
   std::vector<int> active = ok, done, redo;
@@ -1192,12 +1331,12 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
     }
     active.swap(next);
   }
-  if (overlap && !all.empty()) {
+  if (aux) {
     // the prior pass: its status and log-determinants
     if (hipStreamWaitEvent(ctx.stream, ctx.ev_d, 0) != hipSuccess) return fail(INLA_ERR_HIP);
     if ((rc = readback(pb))) return fail(rc);
     std::vector<char> bad(B, 0);
-    for (int i : all)
+    for (int i : fact)
       if (!prior_ok(pb, i)) {
         // reported as without overlap: the status alone, no Newton work
         const int code = res[i].info;
@@ -1524,7 +1663,8 @@ static int mode_or_eval(inla_handle *h, int32_t B, const inla_model *models, con
   if (opts && opts->prec != INLA_PREC_FP64)
     for (int i = 0; i < B; ++i)
       if (models[i].m > 0) return INLA_ERR_UNSUPPORTED;   // general design matrices are evaluated in FP64
-  for (auto c : chunks(h->ctx, B, models, theta, ldtheta, MODE_LAPLACE, h->ctx.overlap)) {
+  for (auto c : chunks(h->ctx, B, models, theta, ldtheta, MODE_LAPLACE,
+                       h->ctx.overlap && needs_prior_factor(B, models, theta, ldtheta))) {
     rc = eval_chunk(h->ctx, c.second - c.first, models + c.first, theta + (size_t)c.first * ldtheta, ldtheta,
                     x + c.first, opts, res + c.first, laplace);
     if (rc) return rc;

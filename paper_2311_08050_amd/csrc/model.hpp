@@ -13,6 +13,14 @@ __device__ __forceinline__ int round_up_dev(int v, int m) { return (v + m - 1) /
 // assembly (k_model.hip)
 void launch_expcov_bordered(Ctx &ctx, const ThetaDesc *dtd, int B, int Np_max);
 void launch_prior_assemble(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, double bytes);
+// structured prior pass: constraint rows in the temporal eigenbasis (one theta
+// per distinct C), the n_t bordered matrices, the kriging system; the same for
+// the exponential covariance; log|Q_prior|
+void launch_kron_rows(Ctx &ctx, const ThetaDesc *dtd, int B, int ns_max, int nt_max, int k_max);
+void launch_kron_assemble(Ctx &ctx, const ThetaDesc *dtd, int B, int N_max, int nt_max);
+void launch_kron_schur(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max);
+void launch_expcov_schur(Ctx &ctx, const ThetaDesc *dtd, int B, int n_max, int k_max, int kp_max);
+void launch_structured_logdet(Ctx &ctx, const ThetaDesc *dtd, int B);
 // with_lik and m_max > 0: the per-observation terms of general design
 // matrices are computed first
 void launch_assemble(Ctx &ctx, const ThetaDesc *dtd, int B, int N_max, int with_lik, int want_xqx, int border,
