@@ -37,13 +37,15 @@ struct FactorDesc {
   int nrows;       // multiple of PADN
   int ncols;       // nf <= ncols <= nrows, multiple of PADN
   int id_row0;     // first row of an identity border block (INT_MAX if none)
-  int pad_;
-  // BF16 copies of the current panel for the BF16 trailing update, two slots
-  // (panel parity): slot s holds entry (k-group g, row r) = the eight panel
-  // values of row r at k = p0 + 8g .. p0 + 8g + 7 as 16 bytes at
-  // pbf[s * pbf_slot + g * nf + r]; rows [p0 + nb, nf) are written
+  // packed BF16 copies of the current panel for the trailing updates with BF16
+  // MFMA, one or two slots (by panel parity).  An entry holds the eight values of
+  // one row at k = p0 + 8 g .. p0 + 8 g + 7 (16 bytes, an MFMA operand); plane q,
+  // group g, row r is entry pbf[slot + (q G + g) prows + r] (G = nb / 8 groups).
+  // One plane: the values rounded to BF16, rows [p0 + nb, nf).  Three planes: hi,
+  // mid and lo parts that add up to the FP32 value, rows [p0 + nb, nrows).
+  int prows;
   void *pbf;
-  int64_t pbf_slot;  // entries per slot
+  int64_t pbf_slot;  // entries from one slot to the other (0: one slot)
 };
 
 // Likelihood / prior kinds (values match the C header).

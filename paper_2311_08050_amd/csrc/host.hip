@@ -650,6 +650,13 @@ static int run_factor(Batch &b, const std::vector<int> &ids, int which, Mode mod
     const Plan &p = b.plans[i];
     const size_t lo = which == F_SMALL ? p.off_linv_small : p.off_linv;
     HostFactor h = factor_of(p, which, b.dinfo + 4 * i + which, (void *)(b.bases[i] + lo), mode);
+    if (which == F_BIG && mode == MODE_LAPLACE && prec != INLA_PREC_FP64) {
+      // the working matrix's region is sized for FP64: an FP32 factor leaves its
+      // second half for the packed panel copies
+      const size_t half = align256(sizeof(float) * (size_t)p.t.ldw * p.t.Ncw);
+      h.pack = b.bases[i] + p.off_W + half;
+      h.pack_bytes = p.off_S - p.off_W - half;
+    }
     if (h.d.nf > 0) fs.push_back(h);
   }
   return factor_batch(b.ctx, fs, prec);

@@ -20,6 +20,10 @@ struct HostFactor {
   int n_real;    // real factor columns (< nf means identity padding)
   int kb_real;   // real border rows starting at row nf
   int ks_real;   // real Schur columns starting at column nf
+  // device memory the factorisation may use for packed panel copies (FP32 and
+  // BF16; null: none beyond the handle's own for one BF16 plane)
+  char *pack;
+  size_t pack_bytes;
 };
 
 // Blocked-Cholesky configuration: panel width, trailing tile, lookahead.

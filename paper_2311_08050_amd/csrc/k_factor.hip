@@ -825,19 +825,29 @@ typedef __attribute__((address_space(1))) const bf8 gcbf8;
 
 __device__ __forceinline__ int bf_slot(int r) { return r ^ ((r >> 4) & 3); }
 
-// Packed BF16 copy of the panel [p0, pend) for rows [pend, nf): one thread per
-// (row, group of eight k), slot (p0 / nb) & 1.
-__global__ __launch_bounds__(256) void panel_bf16_kernel(const FactorDesc *__restrict__ descs, int p0, int nb) {
+// Packed copy of the panel [p0, pend): one thread per (row, group of eight k),
+// one plane (rows [pend, nf)) or three (rows [pend, nrows)).
+template <int PLANES>
+__global__ __launch_bounds__(256) void panel_pack_kernel(const FactorDesc *__restrict__ descs, int p0, int nb) {
   const FactorDesc d = descs[blockIdx.z];
   const int pend = min(p0 + nb, d.nf);
   const int r = pend + blockIdx.x * 256 + threadIdx.x, gk = blockIdx.y;
-  if (r >= d.nf || p0 + 8 * gk >= pend) return;
+  if (r >= (PLANES == 1 ? d.nf : d.nrows) || p0 + 8 * gk >= pend) return;
   const __attribute__((address_space(1))) float *src = gptr((const float *)d.A) + (size_t)(p0 + 8 * gk) * d.ld + r;
-  bf8 v;
+  float v[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = (__bf16)src[(size_t)i * d.ld];
-  bf8 *dst = (bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot + (size_t)gk * d.nf + r;
-  *gptr(dst) = v;
+  for (int i = 0; i < 8; ++i) v[i] = src[(size_t)i * d.ld];
+  bf8 *dst = (bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot + (size_t)gk * d.prows + r;
+#pragma unroll
+  for (int q = 0; q < PLANES; ++q) {
+    bf8 e;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      e[i] = (__bf16)v[i];       // round to nearest even
+      v[i] -= (float)e[i];       // exact
+    }
+    *gptr(dst + (size_t)q * (nb / 8) * d.prows) = e;
+  }
 }
 
 template <int TM, int TN>
@@ -856,10 +866,10 @@ __global__ __launch_bounds__(256, 2) void trail_bf16_kernel(const FactorDesc *__
   int row0, col0, ks, ke;
   if (!update_tile(d, kind, p0, nb, TM, TN, 1, bx, row0, col0, ks, ke)) return;
   const int ld = d.ld;
-  // the packed panel: entry (group g, row r) at P[g * nf + r]; k = ks + 8 g
+  // the packed panel: entry (group g, row r) at P[g * prows + r]; k = ks + 8 g
   gcbf8 *P = gptr((const bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot);
   gT *Cg = gptr((float *)d.A) + (size_t)col0 * ld + row0;
-  const int K = ke - ks, nf = d.nf;
+  const int K = ke - ks, prows = d.prows;
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w / WN, wn = w % WN;
@@ -877,12 +887,12 @@ __global__ __launch_bounds__(256, 2) void trail_bf16_kernel(const FactorDesc *__
 #pragma unroll
     for (int i = 0; i < EA; ++i) {
       const int e = i * 256 + tid, eg = e / TM, er = e % TM;
-      ra[i] = P[(size_t)(g0 + eg) * nf + row0 + er];
+      ra[i] = P[(size_t)(g0 + eg) * prows + row0 + er];
     }
 #pragma unroll
     for (int i = 0; i < EB; ++i) {
       const int e = i * 256 + tid, eg = e / TN, er = e % TN;
-      rb[i] = P[(size_t)(g0 + eg) * nf + col0 + er];
+      rb[i] = P[(size_t)(g0 + eg) * prows + col0 + er];
     }
   };
   auto lstore = [&](int buf) {
@@ -924,6 +934,95 @@ __global__ __launch_bounds__(256, 2) void trail_bf16_kernel(const FactorDesc *__
   auto rl = [&](int a, int v) { return wm * WTM + a * 16 + 4 * g + v; };
   auto cl = [&](int b, int v) { (void)v; return wn * WTN + b * 16 + li; };
   subtract_tile<float, BM, BN>(Cg, ld, acc, rl, cl, row0 < col0 + TN, row0, col0);
+}
+
+// --------------------------------------------------------------------------
+// Trailing update of an FP32 factorisation on the BF16 matrix units.  Each panel
+// value a is split exactly into BF16 parts a1 + a2 + a3 (panel_pack_kernel), and a
+// product a b is the sum of a3 b1, a1 b3, a2 b2, a2 b1, a1 b2 and a1 b1, smallest
+// first, accumulated in FP32; what is left out (a2 b3, a3 b2, a3 b3) is below
+// 2^-25 of the product, half an FP32 rounding, and 32 products cost six rounded
+// additions to the accumulator where v_mfma_f32_16x16x4f32 makes 32.  Six passes
+// at 16 times the FP32 matrix rate: 2.7 times the FP32 bound (417 against 157 TF).
+// Tile 128 x 128, 2 x 2 waves, K chunks of 32 in one LDS buffer of 48 KB with the
+// next chunk in registers, two workgroups per CU by registers: larger wave tiles
+// would leave LDS reads (three planes of both operands per chunk) further from
+// the bound but not fit the accumulators twice.  SEL as in update_tile.
+// Trailing updates of 25 theta at n = 8192 (two factorisations): 48.0 ms with 2.6 ms
+// of packing (74.1 ms on v_mfma_f32_16x16x4f32); that is 180 TF of FP32 products,
+// 1.08 PF on the BF16 units, the rate a large BF16 library product reaches (1.06).
+// Error of log|S| at n = 1024: 6.6e-7 relative (2.1e-6 on the FP32 units).
+// --------------------------------------------------------------------------
+template <int SEL>
+__global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *__restrict__ descs, int kind, int p0,
+                                                             int nb) {
+  constexpr int TM = 128, KCH = 32, KG = KCH / 8, NP = 3, WT = 64, BM = 4, BN = 4;
+  constexpr int E = NP * KG * TM / 256;   // entries per thread, operand and chunk
+  typedef __attribute__((address_space(1))) float gT;
+  __shared__ bf8 As[NP * KG][TM];         // [plane KG + group][slot]
+  __shared__ bf8 Bs[NP * KG][TM];
+
+  int bx, by;
+  xcd_order(bx, by);
+  const FactorDesc d = descs[by];
+  int row0, col0, ks, ke;
+  if (!update_tile(d, kind, p0, nb, TM, TM, SEL, bx, row0, col0, ks, ke)) return;
+  const int ld = d.ld, prows = d.prows, K = ke - ks;
+  gcbf8 *P = gptr((const bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot);
+  gT *Cg = gptr((float *)d.A) + (size_t)col0 * ld + row0;
+
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wm = w >> 1, wn = w & 1;
+  const int g = lane >> 4, li = lane & 15;
+
+  f4 acc[BM][BN];
+#pragma unroll
+  for (int a = 0; a < BM; ++a)
+#pragma unroll
+    for (int b = 0; b < BN; ++b) acc[a][b] = f4{0, 0, 0, 0};
+
+  bf8 ra[E], rb[E];
+  auto gload = [&](int kc) {
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int e = i * 256 + tid, pg = e / TM, er = e % TM;   // pg = plane KG + group
+      gcbf8 *src = P + (size_t)((pg / KG) * (nb / 8) + kc / 8 + pg % KG) * prows + er;
+      ra[i] = src[row0];
+      rb[i] = src[col0];
+    }
+  };
+  gload(0);
+  for (int kc = 0; kc < K; kc += KCH) {
+    if (kc) __syncthreads();   // every wave is done reading the buffer
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int e = i * 256 + tid, pg = e / TM, s = bf_slot(e % TM);
+      As[pg][s] = ra[i];
+      Bs[pg][s] = rb[i];
+    }
+    __syncthreads();
+    if (kc + KCH < K) gload(kc + KCH);
+    bf8 xb[NP][BN];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int b = 0; b < BN; ++b) xb[q][b] = Bs[q * KG + g][bf_slot(wn * WT + b * 16 + li)];
+#pragma unroll
+    for (int a = 0; a < BM; ++a) {
+      bf8 ya[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) ya[q] = As[q * KG + g][bf_slot(wm * WT + a * 16 + li)];
+      constexpr int QA[6] = {2, 0, 1, 1, 0, 0}, QB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int s = 0; s < 6; ++s)
+#pragma unroll
+        for (int b = 0; b < BN; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[QA[s]], xb[QB[s]][b], acc[a][b], 0, 0, 0);
+    }
+  }
+  auto rl = [&](int a, int v) { return wm * WT + a * 16 + 4 * g + v; };
+  auto cl = [&](int b, int v) { (void)v; return wn * WT + b * 16 + li; };
+  subtract_tile<float, BM, BN>(Cg, ld, acc, rl, cl, row0 < col0 + TM, row0, col0);
 }
 
 // --------------------------------------------------------------------------
@@ -1008,8 +1107,24 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fs[a].d.nf > fs[b].d.nf; });
   std::vector<FactorDesc> hd(B);
   for (int i = 0; i < B; ++i) hd[i] = fs[order[i]].d;
-  const bool split = std::is_same<T, float>::value && bf16_trail;
-  if (split) {
+  // Packed panel copies (FP32 storage): three planes where every theta brings the
+  // memory for them and the tile is the split kernel's (from a padded order of 640
+  // on, the second half of an evaluation's working matrix is enough), else one for
+  // BF16 updates.  A tuned 64 x 64 tile keeps the FP32 units.
+  const bool f32 = std::is_same<T, float>::value;
+  const int slots = look_cfg && ctx.lookahead && ctx.lane == 0 && ctx.pg_mode == Ctx::PG_OFF ? 2 : 1;
+  auto plane = [&](int i) { return (size_t)(nb / 8) * hd[i].nrows; };   // entries
+  int planes = f32 && (bf16_trail || tm == 128) ? 3 : 0;
+  for (int i = 0; i < B && planes == 3; ++i)
+    if (!fs[order[i]].pack || 16 * 3 * slots * plane(i) > fs[order[i]].pack_bytes) planes = 0;
+  if (f32 && bf16_trail && planes == 0) planes = 1;
+  if (planes == 3) {
+    for (int i = 0; i < B; ++i) {
+      hd[i].pbf = fs[order[i]].pack;
+      hd[i].pbf_slot = slots == 2 ? (int64_t)(3 * plane(i)) : 0;
+      hd[i].prows = hd[i].nrows;
+    }
+  } else if (planes == 1) {
     // two slots of the packed BF16 panel copy per theta (16-byte entries)
     size_t entries = 0;
     for (int i = 0; i < B; ++i) entries += 2 * (size_t)(nb / 8) * hd[i].nf;
@@ -1019,6 +1134,7 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
     for (int i = 0; i < B; ++i) {
       hd[i].pbf = base + 16 * off;
       hd[i].pbf_slot = (int64_t)(nb / 8) * hd[i].nf;
+      hd[i].prows = hd[i].nf;
       off += 2 * (size_t)hd[i].pbf_slot;
     }
   }
@@ -1085,28 +1201,30 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
       }
     });
   };
-  // the packed BF16 copy of panel p0 for the BF16 trailing update, on ctx.stream
+  // the packed copy of panel p0 for its trailing update, on ctx.stream
   auto panel_copy = [&](int p0) {
     const int act = active(p0);
     int rows = 0;
     double by = 0;
     for (int i = 0; i < act; ++i) {
       const HostFactor &h = fs[order[i]];
-      const int pend = std::min(p0 + nb, h.d.nf);
-      rows = std::max(rows, h.d.nf - pend);
-      by += 6.0 * std::max(0, h.n_real - pend) * (double)std::max(0, std::min(pend, h.n_real) - p0);
+      const int pend = std::min(p0 + nb, h.d.nf), last = planes == 3 ? h.d.nrows : h.d.nf;
+      rows = std::max(rows, last - pend);
+      const double real = planes == 3 ? count_rows_real(h, pend) : std::max(0, h.n_real - pend);
+      by += (4.0 + 2.0 * planes) * real * (double)std::max(0, std::min(pend, h.n_real) - p0);
     }
     if (rows <= 0) return;
     ctx.launch(INLA_K_PANEL, 0.0, by, [&] {
-      hipLaunchKernelGGL(panel_bf16_kernel, dim3((rows + 255) / 256, nb / 8, act), dim3(256), 0, ctx.stream, dd, p0,
-                         nb);
+      const dim3 grid((rows + 255) / 256, nb / 8, act);
+      if (planes == 3) hipLaunchKernelGGL(panel_pack_kernel<3>, grid, dim3(256), 0, ctx.stream, dd, p0, nb);
+      else hipLaunchKernelGGL(panel_pack_kernel<1>, grid, dim3(256), 0, ctx.stream, dd, p0, nb);
     });
   };
   auto panel = [&](int p0) -> int {
     std::vector<int64_t> key = key0;
     key.push_back(p0);
     const int rc = panel_seq(p0, key);
-    if (!rc && split) panel_copy(p0);
+    if (!rc && planes) panel_copy(p0);
     return rc;
   };
   // the trailing update of kind TRAIL (everything right of the panel), TRAIL_A
@@ -1114,7 +1232,7 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
   // enqueued on ctx.stream
   auto trail = [&](int p0, int kind) {
     const int act = active(p0);
-    const int TT = split ? 128 : tm;   // the BF16 split path has 128 x 128 tiles only
+    const int TT = planes ? 128 : tm;   // the BF16 units' kernels have 128 x 128 tiles only
     int gx = 0;
     double fl = 0, by = 0, fl_q = 0, by_q = 0;   // all tiles; tiles of the factored rows only
     bool rows_q = false;                          // some theta has factored rows in the region
@@ -1138,18 +1256,25 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
     }
     if (gx == 0) return;
     gx = round_up(gx, 8);   // xcd_order needs a grid of a multiple of 8 workgroups
-    if (split) {
+    if (bf16_trail && f32) {
       // BF16 operands for the factored rows only: the border rows carry the
       // constraint rows and the right-hand side, whose Schur block (C Q^{-1}
-      // C^T and C Q^{-1} b) arises by cancellation and keeps FP32 operands
+      // C^T and C Q^{-1} b) arises by cancellation and keeps FP32 accuracy
       if (rows_q)
         ctx.launch(INLA_K_TRAIL, fl_q, by_q, [&] {
           hipLaunchKernelGGL((trail_bf16_kernel<128, 128>), dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind, p0,
                              nb);
         });
       ctx.launch(INLA_K_BORDER, fl - fl_q, by - by_q, [&] {
-        hipLaunchKernelGGL((gemm_update_kernel<T, 128, 128, 2>), dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind,
-                           p0, nb);
+        if (planes == 3)
+          hipLaunchKernelGGL(trail_split_kernel<2>, dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind, p0, nb);
+        else
+          hipLaunchKernelGGL((gemm_update_kernel<T, 128, 128, 2>), dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind,
+                             p0, nb);
+      });
+    } else if (planes == 3) {
+      ctx.launch(INLA_K_TRAIL, fl, by, [&] {
+        hipLaunchKernelGGL(trail_split_kernel<0>, dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind, p0, nb);
       });
     } else {
       const bool aux = ctx.lane == 1;
