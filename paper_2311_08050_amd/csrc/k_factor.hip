@@ -104,7 +104,7 @@ __device__ __forceinline__ void sqrt_rsqrt(double x, double &sq, double &rs) {
 
 // Elimination of the diagonal block d[] (column q in lane q of each 16-lane
 // group), applied to the columns b[] as well; dv receives pivot c in lane c of
-// each group.  With u = column / pivot, row r is updated by (row r of column c) u.
+// each group.  With u = -column / pivot, row r is updated by (row r of column c) u.
 // 1 / pivot is the hardware estimate x (relative error e below 2^-20) corrected
 // to x (1 + e + e^2).  SAFE scales each pivot into range first (where 1 / pivot
 // would overflow or lose bits).  Step C updates the rows below C with ud, ub and
@@ -122,21 +122,21 @@ __device__ __forceinline__ void potf2_ratio(const double (&d)[16], const double 
     bc *= sc;
   }
   const double x = __builtin_amdgcn_rcp(pv);
-  const double e = fma(-pv, x, 1.0), dx = dc * x, bx = bc * x, t = fma(e, e, e);
+  const double e = fma(-pv, x, 1.0), dx = -dc * x, bx = -bc * x, t = fma(e, e, e);
   ud = fma(dx, t, dx);
   ub = fma(bx, t, bx);
 }
 template <int C, bool SAFE>
 __device__ __forceinline__ void potf2_step(double (&d)[16], double (&b)[16], double &dv, double ud, double ub) {
   if constexpr (C < 15) {
-    const double m = -row_lane<C>(d[C + 1]);
+    const double m = row_lane<C>(d[C + 1]);
     d[C + 1] = fma(m, ud, d[C + 1]);
     b[C + 1] = fma(m, ub, b[C + 1]);
     double udn, ubn;
     potf2_ratio<C + 1, SAFE>(d, b, dv, udn, ubn);
 #pragma unroll
     for (int r = C + 2; r < 16; ++r) {
-      const double mr = -row_lane<C>(d[r]);
+      const double mr = row_lane<C>(d[r]);
       d[r] = fma(mr, ud, d[r]);
       b[r] = fma(mr, ub, b[r]);
       asm volatile("" : "+v"(b[r]));   // here and not after the last pivot, with every multiplier kept until then
@@ -165,9 +165,9 @@ template <int C> __device__ __forceinline__ void potf2_scale(double (&d)[16], do
 // Block (I, C) of the update by sub-panel J: block -= P_I P_C^T over its 16
 // columns, P_p = M[p][16 J ..] (for the sub-panel's own rows: its diagonal
 // block's inverse).  One wave; I, C and J are uniform.
-__device__ __forceinline__ void potf2_block(Potf2Lds &S, int I, int C, int J) {
+__device__ __forceinline__ void potf2_block(Potf2Lds &S, int I, int C, int J, int lane) {
   constexpr int W = 16, LD = NBI + 1;
-  const int lane = threadIdx.x & 63, q = lane & (W - 1), g = lane >> 4, jb = W * J;
+  const int q = lane & (W - 1), g = lane >> 4, jb = W * J;
   double *M = &S.M[0][0];
   // element v of a lane: row g + 4 v of block row I, column q of block column C;
   // a block of the inverse is stored transposed
@@ -206,12 +206,33 @@ __device__ __forceinline__ void potf2_put(Potf2Lds &S, int r, int c, double v) {
   }
 }
 
-// The block is in S.M (potf2_put), S.fail is 0; all of it visible to the block.  On return the lower triangle holds
-// L_jj, the upper triangle and S.rd the inverse, S.fail the first failing pivot
-// (1-based) or 0.
-__device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, int tid) {
+// Sub-panel J of the factored block: columns 16 J .. of L over the lower triangle
+// at Ad (column-major, ld), rows 16 J .. of the inverse into its slot Li.  Threads
+// [0, nthr).
+template <typename T>
+__device__ __forceinline__ void potf2_store(const Potf2Lds &S, int J, __attribute__((address_space(1))) T *Ad, int ld,
+                                            __attribute__((address_space(1))) T *Li, int thr, int nthr) {
+  constexpr int W = 16;
+#pragma unroll 1
+  for (int e = thr; e < W * NBI; e += nthr) {
+    const int r = e & (NBI - 1), c = W * J + (e >> 6);
+    if (r >= c) Ad[(size_t)c * ld + r] = (T)S.M[r][c];
+    const int xr = W * J + (e & (W - 1)), xc = e >> 4;
+    Li[xc * NBI + xr] = (T)(xr >= xc ? xinv(S, xr, xc) : 0.0);   // column-major (L^{-1})[r][c]
+  }
+}
+
+// The block is in S.M (potf2_put), S.fail is 0; all of it visible to the block.
+// On return the lower triangle holds L_jj, the upper triangle and S.rd the
+// inverse, S.fail the first failing pivot (1-based) or 0; L_jj and the inverse are
+// written to their places (j: the block's first column) and a failing pivot to
+// d.info.  Waves 1 .. 3 store a finished sub-panel while wave 0 eliminates the next.
+template <typename T>
+__device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, const FactorDesc &d, int j,
+                                                    __attribute__((address_space(1))) T *Ad, int tid) {
   constexpr int W = 16, NJ = NBI / W, LD = NBI + 1;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __attribute__((address_space(1))) T *Li = gptr((T *)d.linv) + (size_t)(j / NBI) * NBI * NBI;
   double *M = &S.M[0][0];
 #pragma unroll 1
   for (int J = 0; J < NJ; ++J) {
@@ -241,40 +262,31 @@ __device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, int tid) {
       double sq, rs;
       sqrt_rsqrt(dv, sq, rs);   // not a number for a negative pivot
       potf2_scale<0>(d, b, rs);
+      // the block's own rows hold L up to their diagonal and the inverse beyond it
+      const int upto = own ? q : -1;
 #pragma unroll
-      for (int r = 0; r < W; ++r)
-        M[lane * LD + jb + r] = own && r <= q ? (r == q ? sq : d[r]) : b[r];
+      for (int r = 0; r < W; ++r) M[lane * LD + jb + r] = r <= upto ? d[r] : b[r];
       if (own) S.rd[lane] = rs;
-    } else if (J == 1) {
-      if (w == 3) {
-        potf2_block(S, 3, 3, 0);
-      } else {
-        potf2_block(S, w + 1, 0, 0);
-        potf2_block(S, w + 1, 2, 0);
+    } else {
+      if (J == 1) {
+        if (w == 3) {
+          potf2_block(S, 3, 3, 0, lane);
+        } else {
+          potf2_block(S, w + 1, 0, 0, lane);
+          potf2_block(S, w + 1, 2, 0, lane);
+        }
+      } else if (J == 2) {
+        potf2_block(S, 3, w == 3 ? 3 : w - 1, 1, lane);
       }
-    } else if (J == 2) {
-      potf2_block(S, 3, w == 3 ? 3 : w - 1, 1);
+      if (J > 0) potf2_store<T>(S, J - 1, Ad, d.ld, Li, 64 * (w - 1) + lane, 192);
     }
     __syncthreads();
     if (J + 1 < NJ) {
-      potf2_block(S, max(w, J + 1), min(w, J + 1), J);
+      potf2_block(S, max(w, J + 1), min(w, J + 1), J, lane);
       __syncthreads();
     }
   }
-}
-
-// Writes L_jj over the block's lower triangle at Ad (column-major, ld) and its
-// inverse into slot j / 64 of d.linv; records a failing pivot in d.info.
-template <typename T>
-__device__ __forceinline__ void potf2_store(const Potf2Lds &S, const FactorDesc &d, int j,
-                                            __attribute__((address_space(1))) T *Ad, int tid) {
-  __attribute__((address_space(1))) T *Li = gptr((T *)d.linv) + (size_t)(j / NBI) * NBI * NBI;
-#pragma unroll 4
-  for (int i = 0; i < NBI * NBI / 256; ++i) {
-    const int e = tid + 256 * i, r = e & (NBI - 1), c = e >> 6;
-    if (r >= c) Ad[(size_t)c * d.ld + r] = (T)S.M[r][c];
-    Li[c * NBI + r] = (T)(r >= c ? xinv(S, r, c) : 0.0);   // column-major (L^{-1})[r][c]
-  }
+  potf2_store<T>(S, NJ - 1, Ad, d.ld, Li, tid, 256);
   if (tid == 0 && S.fail != 0 && *d.info == 0) *d.info = j + S.fail;
 }
 
@@ -299,8 +311,7 @@ __global__ __launch_bounds__(256) void potf2_inv_kernel(const FactorDesc *__rest
   }
   if (tid == 0) S.fail = 0;
   __syncthreads();
-  potf2_factor_invert(S, tid);
-  potf2_store<T>(S, d, j, Ad, tid);
+  potf2_factor_invert<T>(S, d, j, Ad, tid);
 }
 
 // XCD-aware workgroup order.  The hardware hands the workgroup with linear id
@@ -597,9 +608,15 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 // so a tile of them starts its K range at r0 - id_row0 and is skipped when
 // that is past the block column.
 //
-// Grid: act + 8 Q workgroups.  The first act (one per theta) take tile 0, so
-// the diagonal factorisations start first; the rest take tiles 1 .. gx - 1 of
-// every theta in the XCD-aware order of xcd_order (Q = ceil(act (gx - 1) / 8)).
+// Tile 0 is the critical one, so its product is taken off it: while step j runs,
+// one more workgroup per theta updates the tile that will be step j + 1's tile 0
+// by the block columns before j (complete by then), which leaves that step the
+// 64-deep product with block column j.
+//
+// Grid: act (1 + pre) + 8 Q workgroups.  The first act (one per theta) take tile 0,
+// so the diagonal factorisations start first, then (pre) the next step's tiles; the
+// rest take tiles 1 .. gx - 1 of every theta in the XCD-aware order of xcd_order
+// (Q = ceil(act (gx - 1) / 8)).
 // --------------------------------------------------------------------------
 //
 // Wave w owns rows 16 w .. 16 w + 15 of the tile and all 64 columns, as four
@@ -609,9 +626,11 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 // lane group g, so C goes into the TRSM, and the TRSM skips the zero half of
 // L_jj^{-1}, without passing through LDS; the SYRK reads L[I,j] from LDS, only its
 // ten blocks at and below the diagonal.  Bound by the chain of tile 0 (product,
-// TRSM, SYRK, factorisation), in large batches by the MFMA products.  9 theta at
-// n = 3000 in FP64 take 29.8 us per step (35.3 us with 2 x 2 waves of 32 x 32 that
-// staged C and L_jj^{-1} through LDS in 16-deep chunks, two barriers each).
+// TRSM, SYRK, factorisation), in large batches by the MFMA products.  Tile 0's
+// chain takes 45,000 cycles in FP64 and 40,000 in FP32 at every column, 23,000 of
+// them the factorisation (65,000 and 50,000 on average with the product over the
+// whole panel, and TRSM operands and results staged in 16-deep chunks before that):
+// one matrix of order 1000 463 us (622), 9 of order 3000 2.82 ms (3.36).
 template <typename T>
 struct PanelLds {
   static constexpr int LDC = NBI + 4;          // LDS row length (elements): conflict-free MFMA operand reads
@@ -623,11 +642,30 @@ struct PanelLds {
   };
 };
 
+// Elements of a tile through a buffer resource: a uniform base, one 32-bit lane
+// offset for the whole tile and a scalar offset per access (both in bytes), where
+// 64-bit addresses would hold two registers per element over the kernel's length.
+// The resource spans 2 GB from the base (a 64-column tile ends well before that).
+template <typename T> struct TileBuf {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit TileBuf(const void *base)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000)) {}
+  __device__ __forceinline__ T load(unsigned lane_off, unsigned off) const {
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, off, 0));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_off, off, 0));
+  }
+  __device__ __forceinline__ void store(T v, unsigned lane_off, unsigned off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane_off, off, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane_off, off, 0);
+  }
+};
+
 // Four workgroups per CU in FP32; three in FP64, whose registers would
 // otherwise spill at the 128-register budget of four.
 template <typename T>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel(const FactorDesc *__restrict__ descs, int p0, int nb,
-                                                            int j, int act, int gx, int Q) {
+                                                            int j, int act, int gx, int Q, int pre) {
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int VEC = 16 / sizeof(T);
   constexpr int LDC = PanelLds<T>::LDC, PKC = PanelLds<T>::PKC, NB = NBI / 16;
@@ -639,13 +677,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   typedef typename std::conditional<F64, d4, f4>::type acc_t;
   __shared__ __attribute__((aligned(16))) PanelLds<T> S;
 
-  int th, t;
+  int th, t;   // t = -1: the next step's tile 0 ahead of time
   {
     const int L = blockIdx.x;
     if (L < act) {
       th = L; t = 0;
+    } else if (L < act * (1 + pre)) {
+      th = L - act; t = -1;
     } else {
-      const int L2 = L - act, G = (L2 & 7) * Q + (L2 >> 3);
+      const int L2 = L - act * (1 + pre), G = (L2 & 7) * Q + (L2 >> 3);
       if (gx <= 1 || G >= act * (gx - 1)) return;
       th = G / (gx - 1);
       t = 1 + G % (gx - 1);
@@ -653,10 +693,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   }
   const FactorDesc d = descs[th];
   if (j >= d.nf) return;
-  const int r0 = j + NBI * (t + 1);
-  if (r0 >= d.nrows) return;
   const int pend = min(p0 + nb, d.nf);
-  int ks = p0;
+  const int r0 = t < 0 ? j + 2 * NBI : j + NBI * (t + 1), c0 = t < 0 ? j + NBI : j;   // tile rows and columns
+  if (r0 >= (t < 0 ? pend : d.nrows)) return;
+  // (the step before updated this step's tile 0 up to block column j - 64)
+  int ks = t == 0 && j >= p0 + 2 * NBI && r0 < pend ? j - NBI : p0;
   if (r0 >= d.id_row0) {
     if (r0 - d.id_row0 >= j + NBI) return;   // zero in block column j: nothing to do
     ks = max(ks, r0 - d.id_row0);
@@ -665,19 +706,46 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, li = lane & 15;
   auto kcol = [&](int v) { return F64 ? g + 4 * v : 4 * g + v; };
+  // ... = klane + kstep(v): a tile's element (row li of the wave, column 16 b +
+  // kcol(v)) is addressed by a uniform pointer per (b, v) and one lane offset
+  const int klane = F64 ? g : 4 * g;
+  auto kstep = [&](int b, int v) { return 16 * b + (F64 ? 4 * v : v); };
   auto mfma = [&](T x, T y, acc_t c) {   // c[v] += sum over k of x (column kcol(v)'s) y (row li's)
     if constexpr (F64) return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);
   };
 
-  // 1. acc = A[I, ks:j] A[j, ks:j]^T, double-buffered PKC-deep chunks
+  // 1. acc = A[I, ks:j] A[c0, ks:j]^T, double-buffered PKC-deep chunks.  The tile
+  //    itself and the first KX column blocks of L_jj^{-1} (column-major: X[n][k] at
+  //    k * 64 + n, zero above its diagonal) are read behind the first chunk.
   acc_t acc[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = acc_t{0, 0, 0, 0};
-  gT *Cg = gptr((T *)d.A) + (size_t)j * ld + r0 + 16 * w + li;
+  const TileBuf<T> Cb((const T *)d.A + (size_t)c0 * ld + r0 + 16 * w);
+  const TileBuf<T> Xb((const T *)d.linv + (size_t)(j / NBI) * NBI * NBI);
+  const unsigned lds = ld * (unsigned)sizeof(T);
+  const unsigned cl = (unsigned)((klane * ld + li) * sizeof(T));
+  const unsigned xl = (unsigned)((klane * NBI + li) * sizeof(T));
+  constexpr int KX = F64 ? 1 : NB;
+  T cv[NB][4], xp[KX][NB][4];
+  auto xload = [&](int k, T (&x)[NB][4]) {
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (n >= k) x[n][v] = Xb.load(xl, (kstep(k, v) * NBI + 16 * n) * sizeof(T));
+  };
+  auto tile_loads = [&] {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) cv[b][v] = Cb.load(cl, kstep(b, v) * lds);
+#pragma unroll
+    for (int k = 0; k < KX; ++k) xload(k, xp[k]);
+  };
   if (K > 0) {
     gcT *Ag = gptr((const T *)d.A) + (size_t)ks * ld + r0;
-    gcT *Bg = gptr((const T *)d.A) + (size_t)ks * ld + j;
+    gcT *Bg = gptr((const T *)d.A) + (size_t)ks * ld + c0;
     vec_t ra[LA], rb[LA];
     auto gload = [&](int kc) {
 #pragma unroll
@@ -696,6 +764,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
       }
     };
     gload(0);
+    tile_loads();
     lstore(0);
     __syncthreads();
     int buf = 0;
@@ -716,35 +785,39 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
       __syncthreads();
       buf ^= 1;
     }
+  } else {
+    tile_loads();
   }
 
   // 2. C = A[I, j] - acc (in acc), then L[I, j] = C L_jj^{-T} into lacc: column
-  //    block n takes the column blocks k <= n of C (L_jj^{-1} column-major:
-  //    X[n][k] at k * 64 + n, zero above its diagonal)
-  gcT *Li = gptr((const T *)d.linv) + (size_t)(j / NBI) * NBI * NBI + li;
+  //    block n takes the column blocks k <= n of C
   acc_t lacc[NB];
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[b][v] = Cg[(16 * b + kcol(v)) * ld] - acc[b][v];
+    for (int v = 0; v < 4; ++v) acc[b][v] = cv[b][v] - acc[b][v];
     lacc[b] = acc_t{0, 0, 0, 0};
+  }
+  if (t < 0) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Cb.store(acc[b][v], cl, kstep(b, v) * lds);
+    return;
   }
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
-    T x[NB][4];
-#pragma unroll
-    for (int n = k; n < NB; ++n)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) x[n][v] = Li[(16 * k + kcol(v)) * NBI + 16 * n];
+    T xk[NB][4];
+    if (k >= KX) xload(k, xk);
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-      for (int n = k; n < NB; ++n) lacc[n] = mfma(x[n][v], acc[k][v], lacc[n]);
+      for (int n = k; n < NB; ++n) lacc[n] = mfma(k < KX ? xp[k < KX ? k : 0][n][v] : xk[n][v], acc[k][v], lacc[n]);
   }
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Cg[(16 * b + kcol(v)) * ld] = lacc[b][v];
+    for (int v = 0; v < 4; ++v) Cb.store(lacc[b][v], cl, kstep(b, v) * lds);
   if (r0 >= pend) return;
 
   // 3. diagonal block of the tile's rows: D = L[I, j] L[I, j]^T, the blocks (I, J)
@@ -755,12 +828,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   auto bJ = [&](int u) { return w == 0 ? (u == 1 ? 3 : 0) : u; };
   const int nu = w < 2 ? 2 : 3;
   gT *Dg = gptr((T *)d.A) + (size_t)r0 * ld + r0;
+  const TileBuf<T> Db((const T *)d.A + (size_t)r0 * ld + r0);
   T dg[U][4];
 #pragma unroll
   for (int u = 0; u < U; ++u)
     if (u < nu)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dg[u][v] = Dg[(16 * bJ(u) + kcol(v)) * ld + 16 * bI(u) + li];
+      for (int v = 0; v < 4; ++v) {   // (a diagonal block's upper half is read from its lower)
+        const int r = 16 * bI(u) + li, c = 16 * bJ(u) + kcol(v);
+        dg[u][v] = Db.load((unsigned)((min(r, c) * ld + max(r, c)) * sizeof(T)), 0);
+      }
 #pragma unroll
   for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -796,13 +873,12 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r = 16 * bI(u) + li, c = 16 * bJ(u) + kcol(v);
-        potf2_put(S.f, r, c, (double)(T)(dg[u][v] - da[u][v]));
+        S.f.M[r][c] = (double)(T)(dg[u][v] - da[u][v]);
         if (bI(u) != bJ(u)) S.f.M[c][r] = 0.0;
       }
   if (tid == 0) S.f.fail = 0;
   __syncthreads();
-  potf2_factor_invert(S.f, tid);
-  potf2_store<T>(S.f, d, r0, Dg, tid);
+  potf2_factor_invert<T>(S.f, d, r0, Dg, tid);
 }
 
 // --------------------------------------------------------------------------
@@ -1194,9 +1270,10 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
         }
         if (gx == 0) continue;
         const int Q = (act * (gx - 1) + 7) / 8;
+        const int pre = j > p0 && j + 2 * NBI < p0 + nb ? 1 : 0;
         ctx.launch(INLA_K_PANEL, fl, by, [&] {
-          hipLaunchKernelGGL(panel_step_kernel<T>, dim3(act + 8 * Q), dim3(256), 0, ctx.stream, pd, p0, nb, j, act,
-                             gx, Q);
+          hipLaunchKernelGGL(panel_step_kernel<T>, dim3(act * (1 + pre) + 8 * Q), dim3(256), 0, ctx.stream, pd, p0,
+                             nb, j, act, gx, Q, pre);
         });
       }
     });

@@ -45,3 +45,29 @@ def test_first_failing_pivot(lib, bad, value):
     Q[bad - 1, bad - 1] = value
     ld, info, _ = _factor(lib, Q)
     assert info == bad and np.isnan(ld)
+
+
+@pytest.mark.parametrize("prec,unit", [("fp64", EPS), ("fp32", 2.0 ** -23)])
+@pytest.mark.parametrize("nb", [128, 256, 512])
+def test_panels_of_an_uneven_batch(lib, prec, unit, nb):
+    """Every panel step's tile 0 (updated one step ahead inside a panel, not at
+    its first two columns nor at its end), with panels that end early in some
+    matrices of the batch."""
+    import torch
+    ns = [65, 128, 129, 192, 257, 320, 385, 513, 577, 640, 769, 1025]
+    Qs = [synth.random_spd(n, seed=n) for n in ns]
+    mats = [torch.as_tensor(Q).cuda() for Q in Qs]
+    try:
+        lib.tune_set(prec, max(ns), len(ns), nb, 64, 0)
+        ld, info = lib.logdet(mats, prec=prec)
+    finally:
+        lib.tune_set(prec, max(ns), len(ns))
+    assert not info.any()
+    for Q, m, v in zip(Qs, mats, ld):
+        L = np.triu(m.cpu().numpy()).T
+        n = len(Q)
+        # as above, the bound of a blocked Cholesky with explicit block inverses
+        # (condition at most 10 here)
+        assert np.max(np.abs(L @ L.T - Q)) <= 2 * (n + 1) * unit * np.max(np.diag(Q))
+        ref = np.linalg.slogdet(Q)[1]
+        assert abs(v - ref) <= 4 * n * unit * max(1.0, abs(ref))
