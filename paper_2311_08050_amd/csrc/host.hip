@@ -63,7 +63,25 @@ int Ctx::sync_all() {
 static bool ring_wrap(Ctx &c) {
   if (c.sync_all() != INLA_OK) return false;
   c.ring_off = 0;
+  c.recent.clear();
   return true;
+}
+
+void *Ctx::pin_reserve(int slot, size_t bytes) {
+  if (bytes <= pin_size[slot]) return pin[slot];
+  if (pin[slot]) {
+    if (sync_all() != INLA_OK) return nullptr;
+    (void)hipHostFree(pin[slot]);
+    pin[slot] = nullptr;
+    pin_size[slot] = 0;
+  }
+  if (hipHostMalloc(&pin[slot], bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    pin[slot] = nullptr;
+    return nullptr;
+  }
+  pin_size[slot] = bytes;
+  return pin[slot];
 }
 
 void *Ctx::upload(const void *src, size_t bytes) {
@@ -81,10 +99,17 @@ void *Ctx::upload(const void *src, size_t bytes) {
     return pg.dbase + off;
   }
   if (padded > ring_size) return nullptr;
+  for (const Recent &r : recent)
+    if (r.bytes == bytes && r.stream == stream && std::memcmp(ring_host + r.off, src, bytes) == 0) return ring + r.off;
   if (ring_off + padded > ring_size && !ring_wrap(*this)) return nullptr;
+  if (recent.size() >= 8) recent.erase(recent.begin());
+  recent.push_back({ring_off, bytes, stream});
   std::memcpy(ring_host + ring_off, src, bytes);
   void *dst = ring + ring_off;
-  if (hipMemcpyAsync(dst, ring_host + ring_off, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return nullptr;
+  if (hipMemcpyAsync(dst, ring_host + ring_off, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) {
+    recent.pop_back();
+    return nullptr;
+  }
   ring_off += padded;
   return dst;
 }
@@ -438,6 +463,8 @@ Ctx::~Ctx() {
   if (gh) (void)hipFree(gh);
   if (ring) (void)hipFree(ring);
   if (ring_host) (void)hipHostFree(ring_host);
+  for (void *p : pin)
+    if (p) (void)hipHostFree(p);
 }
 
 // ------------------------------------------------------------------ planning
@@ -593,11 +620,11 @@ struct Batch {
   Ctx &ctx;
   std::vector<Plan> plans;
   std::vector<char *> bases;
+  double *dres = nullptr;      // device [B * DRES_COUNT]: every theta's result slots, then dinfo
   int *dinfo = nullptr;        // device [B * 4]: prior-build, big, small, spare
-  double *ddres_all = nullptr; // device copy target list not needed: dres live in workspace
   std::vector<int> hinfo;
   std::vector<double> hdres;
-  double *pin = nullptr;       // pinned staging for results
+  double *pin = nullptr;       // pinned staging for results (the handle's)
   std::vector<ThetaDesc> last_td;   // host copy of the last uploaded descriptor array
   char *design = nullptr;           // device: CSC and A^T A patterns of the general design matrices
   explicit Batch(Ctx &c) : ctx(c) {}
@@ -662,19 +689,26 @@ static int run_factor(Batch &b, const std::vector<int> &ids, int which, Mode mod
   return factor_batch(b.ctx, fs, prec);
 }
 
-// Read back dres and info of every theta (one synchronisation).
+// Device block of a batch's results and status words, and the staging for it.
+static size_t results_bytes(int B) { return (sizeof(double) * DRES_COUNT + sizeof(int) * 4) * (size_t)B; }
+static int bind_results(Batch &b, char *block, int slot) {
+  const int B = (int)b.plans.size();
+  b.dres = (double *)block;
+  b.dinfo = (int *)(b.dres + (size_t)DRES_COUNT * B);
+  for (int i = 0; i < B; ++i) b.plans[i].t.dres = b.dres + (size_t)DRES_COUNT * i;
+  b.pin = (double *)b.ctx.pin_reserve(slot, results_bytes(B));
+  if (!b.pin) return INLA_ERR_NOMEM;
+  return hipMemsetAsync(block, 0, results_bytes(B), b.ctx.stream) == hipSuccess ? INLA_OK : INLA_ERR_HIP;
+}
+
+// Read back dres and info of every theta (one copy, one synchronisation).
 static int readback(Batch &b) {
   const int B = (int)b.plans.size();
-  for (int i = 0; i < B; ++i) {
-    if (hipMemcpyAsync(b.pin + DRES_COUNT * i, b.plans[i].t.dres, sizeof(double) * DRES_COUNT, hipMemcpyDeviceToHost,
-                       b.ctx.stream) != hipSuccess)
-      return INLA_ERR_HIP;
-  }
-  int *ipin = (int *)(b.pin + DRES_COUNT * B);
-  if (hipMemcpyAsync(ipin, b.dinfo, sizeof(int) * 4 * B, hipMemcpyDeviceToHost, b.ctx.stream) != hipSuccess)
+  if (hipMemcpyAsync(b.pin, b.dres, results_bytes(B), hipMemcpyDeviceToHost, b.ctx.stream) != hipSuccess ||
+      hipStreamSynchronize(b.ctx.stream) != hipSuccess)
     return INLA_ERR_HIP;
-  if (hipStreamSynchronize(b.ctx.stream) != hipSuccess) return INLA_ERR_HIP;
-  b.hdres.assign(b.pin, b.pin + DRES_COUNT * B);
+  const int *ipin = (const int *)(b.pin + (size_t)DRES_COUNT * B);
+  b.hdres.assign(b.pin, b.pin + (size_t)DRES_COUNT * B);
   b.hinfo.assign(ipin, ipin + 4 * B);
   return b.ctx.check();
 }
@@ -909,34 +943,30 @@ static int setup(Batch &b, int B, const inla_model *models, const double *theta,
       total += bs[q]->plans[i].bytes;
     }
   }
-  const size_t info_off = total;
-  total += nb * align256(sizeof(int) * 4 * B);
+  const size_t res_off = total;
+  total += nb * align256(results_bytes(B));
   if (!b.ctx.reserve(total)) return INLA_ERR_NOMEM;
   for (int q = 0; q < nb; ++q) {
     Batch &x = *bs[q];
     x.bases.resize(B);
+    std::vector<VecCopy> zero;
     for (int i = 0; i < B; ++i) {
       x.bases[i] = b.ctx.ws + offs[q][i];
       bind(x.plans[i], x.bases[i]);
-      if (q == 1) x.plans[i].t.Qp = b.plans[i].t.Qp;
+      ThetaDesc &t = x.plans[i].t;
+      if (q == 1) {
+        t.Qp = b.plans[i].t.Qp;
+        zero.push_back({t.x, nullptr, 0, t.n_pad});   // the prior pass never reads its iterate; clear it all the same
+      }
     }
-    x.dinfo = (int *)(b.ctx.ws + info_off + q * align256(sizeof(int) * 4 * B));
-    if (hipMemsetAsync(x.dinfo, 0, sizeof(int) * 4 * B, b.ctx.stream) != hipSuccess) return INLA_ERR_HIP;
-    for (int i = 0; i < B; ++i) {
-      const ThetaDesc &t = x.plans[i].t;
-      if (hipMemsetAsync(t.dres, 0, sizeof(double) * DRES_COUNT, b.ctx.stream) != hipSuccess) return INLA_ERR_HIP;
-      // the prior pass never reads its iterate; zero it all the same
-      if (q == 1 && hipMemsetAsync(t.x, 0, sizeof(double) * t.n_pad, b.ctx.stream) != hipSuccess) return INLA_ERR_HIP;
-    }
-    if (hipHostMalloc(&x.pin, sizeof(double) * DRES_COUNT * B + sizeof(int) * 4 * B + 64) != hipSuccess)
-      return INLA_ERR_NOMEM;
+    int rc = bind_results(x, b.ctx.ws + res_off + q * align256(results_bytes(B)), q);
+    if (!rc) rc = copy_vectors(b.ctx, zero);
+    if (rc) return rc;
   }
   return setup_design(b, models, B);
 }
 
 static void teardown(Batch &b) {
-  if (b.pin) (void)hipHostFree(b.pin);
-  b.pin = nullptr;
   if (b.design) {
     (void)hipStreamSynchronize(b.ctx.stream);
     (void)hipFree(b.design);
@@ -1104,6 +1134,14 @@ static int validate_common(inla_handle *h, int B, const inla_model *models, cons
 static std::vector<std::pair<int, int>> chunks(Ctx &ctx, int B, const inla_model *models, const double *theta,
                                                int ldtheta, Mode mode, bool aux = false) {
   std::vector<std::pair<int, int>> out;
+  // a batch that the workspace already holds goes in one piece (the query of the
+  // device's free memory costs more than a small call's launches)
+  size_t all = 0;
+  for (int i = 0; i < B; ++i) {
+    const double *th = theta + (size_t)i * ldtheta;
+    all += make_plan(models[i], th, mode).bytes + (aux ? make_plan(models[i], th, mode, true).bytes : 0) + 8192;
+  }
+  if (all <= ctx.ws_size) return {{0, B}};
   const size_t cap = budget(ctx);
   int s = 0;
   while (s < B) {
@@ -1157,6 +1195,7 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
   const int max_ir = 10;
   const double tol_ir = 1e-13;
   std::vector<int> all, ok;
+  std::vector<VecCopy> vecs;
   for (int i = 0; i < B; ++i) {
     res[i] = inla_result{};
     const ThetaDesc &t = b.plans[i].t;
@@ -1164,18 +1203,14 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
     for (int j = 0; j < ldtheta && j <= n_prior_params(t.prior); ++j) finite = finite && std::isfinite(theta[(size_t)i * ldtheta + j]);
     if (!finite) { res[i].info = INLA_INFO_NONFINITE; continue; }
     all.push_back(i);
-    if (warm) {
-      if (hipMemcpyAsync(t.x, x[i], sizeof(double) * t.n, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess) { teardown(pb); teardown(b); return INLA_ERR_HIP; }
-      if (t.n_pad > t.n && hipMemsetAsync(t.x + t.n, 0, sizeof(double) * (t.n_pad - t.n), ctx.stream) != hipSuccess) { teardown(pb); teardown(b); return INLA_ERR_HIP; }
-    } else if (hipMemsetAsync(t.x, 0, sizeof(double) * t.n_pad, ctx.stream) != hipSuccess) {
-      teardown(pb); teardown(b); return INLA_ERR_HIP;
-    }
-    if (mixed && (hipMemsetAsync(t.lam, 0, sizeof(double) * std::max(t.k_pad, 64), ctx.stream) != hipSuccess ||
-                  hipMemsetAsync(t.xn, 0, sizeof(double) * t.n_pad, ctx.stream) != hipSuccess)) {
-      teardown(pb); teardown(b); return INLA_ERR_HIP;
+    vecs.push_back({t.x, warm ? x[i] : nullptr, t.n, t.n_pad});
+    if (mixed) {
+      vecs.push_back({t.lam, nullptr, 0, std::max(t.k_pad, 64)});
+      vecs.push_back({t.xn, nullptr, 0, t.n_pad});
     }
   }
   auto fail = [&](int r) { (void)ctx.sync_all(); teardown(pb); teardown(b); return r; };
+  if ((rc = copy_vectors(ctx, vecs))) return fail(rc);
   // prior-pass status and results of theta i (from the host copy read back
   // from `pp`); returns whether theta i passed
   auto prior_ok = [&](Batch &pp, int i) {
@@ -1358,11 +1393,12 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
     redo.swap(keep);
   }
   // copy the modes out
+  vecs.clear();
   for (int i : ok) {
-    if (failed[i]) continue;
     const ThetaDesc &t = b.plans[i].t;
-    if (hipMemcpyAsync(x[i], t.x, sizeof(double) * t.n, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
+    if (!failed[i]) vecs.push_back({x[i], t.x, t.n, t.n});
   }
+  if ((rc = copy_vectors(ctx, vecs))) return fail(rc);
   if (laplace) {
     std::vector<int> fin;
     for (int i : done) if (!failed[i]) fin.push_back(i);
@@ -1435,14 +1471,15 @@ static int var_chunk(Ctx &ctx, int B, const inla_model *models, const double *th
   if (rc) { teardown(b); return rc; }
   auto fail = [&](int r) { teardown(b); return r; };
   std::vector<int> all;
+  std::vector<VecCopy> vecs;
   for (int i = 0; i < B; ++i) {
     info[i] = 0;
     ThetaDesc &t = b.plans[i].t;
     t.out = var[i];
-    if (hipMemcpyAsync(t.x, xm[i], sizeof(double) * t.n, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
-    if (t.n_pad > t.n && hipMemsetAsync(t.x + t.n, 0, sizeof(double) * (t.n_pad - t.n), ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
+    vecs.push_back({t.x, xm[i], t.n, t.n_pad});
     all.push_back(i);
   }
+  if ((rc = copy_vectors(ctx, vecs))) return fail(rc);
   if ((rc = prior_build(b, all))) return fail(rc);
   ThetaDesc *d = upload_td(b, all);
   if (!d) return fail(INLA_ERR_NOMEM);
@@ -1476,6 +1513,7 @@ static int vb_chunk(Ctx &ctx, int B, const inla_model *models, const double *the
   if (rc) { teardown(b); return rc; }
   auto fail = [&](int r) { teardown(b); return r; };
   std::vector<int> all;
+  std::vector<VecCopy> vecs;
   for (int i = 0; i < B; ++i) {
     iters[i] = 0;
     info[i] = 0;
@@ -1483,10 +1521,10 @@ static int vb_chunk(Ctx &ctx, int B, const inla_model *models, const double *the
     t.vb_var = var[i];
     t.gh = ctx.gh;
     t.ngh = ngh;
-    if (hipMemcpyAsync(t.x, x[i], sizeof(double) * t.n, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
-    if (t.n_pad > t.n && hipMemsetAsync(t.x + t.n, 0, sizeof(double) * (t.n_pad - t.n), ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
+    vecs.push_back({t.x, x[i], t.n, t.n_pad});
     all.push_back(i);
   }
+  if ((rc = copy_vectors(ctx, vecs))) return fail(rc);
   if ((rc = prior_build(b, all))) return fail(rc);
   std::vector<int> active = all;
   for (int it = 1; it <= max_iter && !active.empty(); ++it) {
@@ -1508,10 +1546,10 @@ static int vb_chunk(Ctx &ctx, int B, const inla_model *models, const double *the
     }
     active.swap(next);
   }
+  vecs.clear();
   for (int i = 0; i < B; ++i)
-    if (info[i] == 0 &&
-        hipMemcpyAsync(x[i], b.plans[i].t.x, sizeof(double) * b.plans[i].t.n, hipMemcpyDeviceToDevice, ctx.stream) != hipSuccess)
-      return fail(INLA_ERR_HIP);
+    if (info[i] == 0) vecs.push_back({x[i], b.plans[i].t.x, b.plans[i].t.n, b.plans[i].t.n});
+  if ((rc = copy_vectors(ctx, vecs))) return fail(rc);
   if (hipStreamSynchronize(ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
   ctx.harvest();
   teardown(b);
@@ -1618,8 +1656,8 @@ int inla_logdet(inla_handle *h, int32_t B, const int32_t *n, double *const *Q, c
       p.bytes = off;
       offs[i] = total; total += off;
     }
-    const size_t info_off = total;
-    total += align256(sizeof(int) * 4 * Bc);
+    const size_t res_off = total;
+    total += align256(results_bytes(Bc));
     if (!ctx.reserve(total)) return INLA_ERR_NOMEM;
     b.bases.resize(Bc);
     for (int i = 0; i < Bc; ++i) {
@@ -1631,13 +1669,10 @@ int inla_logdet(inla_handle *h, int32_t B, const int32_t *n, double *const *Q, c
       t.x = v; v += t.n_pad; t.r = v; v += t.n_pad; t.lam = v; v += 64; t.part = v; v += 2 * t.ldw; t.dres = v;
       t.Qp = nullptr; t.S = nullptr; t.P = nullptr;
     }
-    b.dinfo = (int *)(ctx.ws + info_off);
-    if (hipMemsetAsync(b.dinfo, 0, sizeof(int) * 4 * Bc, ctx.stream) != hipSuccess) return INLA_ERR_HIP;
-    if (hipHostMalloc(&b.pin, sizeof(double) * DRES_COUNT * Bc + sizeof(int) * 4 * Bc + 64) != hipSuccess)
-      return INLA_ERR_NOMEM;
     std::vector<int> ids2;
     for (int i = 0; i < Bc; ++i) if (b.plans[i].t.n > 0) ids2.push_back(i);
-    int rc = 0;
+    int rc = bind_results(b, ctx.ws + res_off, 0);
+    if (rc) return rc;
     if (!ids2.empty()) {
       ThetaDesc *d = upload_td(b, ids2);
       if (!d) { teardown(b); return INLA_ERR_NOMEM; }

@@ -41,6 +41,15 @@ struct Ctx {
   char *ring = nullptr;
   char *ring_host = nullptr;
   size_t ring_size = 0, ring_off = 0;
+  // the latest uploads since the ring last wrapped: the same bytes on the same
+  // stream again take the earlier copy (ring contents stay until the wrap)
+  struct Recent { size_t off, bytes; hipStream_t stream; };
+  std::vector<Recent> recent;
+  // pinned host staging of results, grow-only (slot 0: the main batch, 1: the
+  // concurrent prior pass)
+  void *pin[2] = {nullptr, nullptr};
+  size_t pin_size[2] = {0, 0};
+  void *pin_reserve(int slot, size_t bytes);
   // profiling
   bool prof = false;
   int prec_tag = INLA_PREC_FP64;  // precision of the pass being enqueued

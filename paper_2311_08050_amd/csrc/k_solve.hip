@@ -443,6 +443,13 @@ __global__ __launch_bounds__(256) void finish_kernel(const ThetaDesc *__restrict
   }
 }
 
+// Start vectors, modes and cleared vectors of a whole batch in one launch.
+__global__ __launch_bounds__(256) void copy_vectors_kernel(const VecCopy *__restrict__ v) {
+  const VecCopy c = v[blockIdx.y];
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < c.m) c.dst[i] = i < c.n && c.src ? c.src[i] : 0.0;
+}
+
 // Caller matrix (t.Quser, ld t.ldquser, order n) -> working matrix (storage T),
 // identity padded.
 template <typename T>
@@ -504,6 +511,18 @@ __global__ __launch_bounds__(256) void var_norms_kernel(const ThetaDesc *__restr
 }
 
 // ------------------------------------------------------------------ launchers
+int copy_vectors(Ctx &ctx, const std::vector<VecCopy> &v) {
+  if (v.empty()) return INLA_OK;
+  const VecCopy *d = (const VecCopy *)ctx.upload(v.data(), sizeof(VecCopy) * v.size());
+  if (!d) return INLA_ERR_NOMEM;
+  int m = 0;
+  for (const VecCopy &c : v) m = std::max(m, c.m);
+  if (m > 0)
+    ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
+      hipLaunchKernelGGL(copy_vectors_kernel, dim3((m + 255) / 256, v.size()), dim3(256), 0, ctx.stream, d);
+    });
+  return ctx.check();
+}
 #define INLA_DISPATCH_T(prec, KERNEL, ...)                                        \
   do {                                                                            \
     if ((prec) != INLA_PREC_FP64) hipLaunchKernelGGL(KERNEL<float>, __VA_ARGS__); \

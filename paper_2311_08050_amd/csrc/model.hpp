@@ -29,6 +29,14 @@ void launch_kriging_build(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max, int
 void launch_objective_terms(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, double bytes);
 void launch_kkt_residual(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int kp_max, double bytes);
 
+// dst[0, n) = src[0, n) (zeros where src is null), dst[n, m) = 0
+struct VecCopy {
+  double *dst;
+  const double *src;
+  int n, m;
+};
+int copy_vectors(Ctx &ctx, const std::vector<VecCopy> &v);
+
 // solves and reductions (k_solve.hip)
 void launch_kriging_solve(Ctx &ctx, const ThetaDesc *dtd, int B);
 void launch_rhs(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int from_z, int prec);
