@@ -1403,20 +1403,27 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
     std::vector<int> fin;
     for (int i : done) if (!failed[i]) fin.push_back(i);
     if (hipMemsetAsync(b.dinfo, 0, sizeof(int) * 4 * B, ctx.stream) != hipSuccess) return fail(INLA_ERR_HIP);
-    if (mixed) {
-      // The last Newton factorisation was taken at an iterate within the Newton
-      // tolerance (1e-11) of the mode; its log-dets differ from a refactorisation
-      // at the mode by far less than the FP32 factor's own error, so it is reused.
-      PrecScope tag(ctx, ref_prec);
-      ThetaDesc *d = upload_td(b, fin);
-      if (!fin.empty() && !d) return fail(INLA_ERR_NOMEM);
-      double by = 0;
-      for (int i : fin) by += 8.0 * 0.5 * b.plans[i].t.n * (b.plans[i].t.n + 1.0);
-      launch_objective_terms(ctx, d, (int)fin.size(), max_over(b, fin, &ThetaDesc::n_pad), by);
-      launch_finish(ctx, d, (int)fin.size(), ref_prec);
-    } else if ((rc = run_pass(b, fin, PASS_FINAL, prec))) {
-      return fail(rc);
+    // Thetas whose last Newton factorisation gives the log-dets: in mixed
+    // precision, where it was taken at an iterate within the Newton tolerance
+    // (1e-11) of the mode and its log-dets differ from a refactorisation at the
+    // mode by far less than the FP32 factor's own error; and with a Gaussian
+    // likelihood and A = I, whose W does not depend on the iterate, so that the
+    // final pass would factor the same matrix again.
+    std::vector<int> reuse, refactor;
+    for (int i : fin) {
+      const ThetaDesc &t = b.plans[i].t;
+      (mixed || (t.lik == LIK_GAUSSIAN && t.m == 0) ? reuse : refactor).push_back(i);
     }
+    if (!reuse.empty()) {
+      PrecScope tag(ctx, ref_prec);
+      ThetaDesc *d = upload_td(b, reuse);
+      if (!d) return fail(INLA_ERR_NOMEM);
+      double by = 0;
+      for (int i : reuse) by += 8.0 * 0.5 * b.plans[i].t.n * (b.plans[i].t.n + 1.0);
+      launch_objective_terms(ctx, d, (int)reuse.size(), max_over(b, reuse, &ThetaDesc::n_pad), by);
+      launch_finish(ctx, d, (int)reuse.size(), ref_prec);
+    }
+    if ((rc = run_pass(b, refactor, PASS_FINAL, prec))) return fail(rc);
     if ((rc = readback(b))) return fail(rc);
     for (int i : fin) {
       const int *inf = &b.hinfo[4 * i];
