@@ -85,23 +85,6 @@ __device__ __forceinline__ double xinv(const Potf2Lds &S, int a, int b) {
   return a == b ? S.rd[a] : S.M[b][a];
 }
 
-// sqrt(x) and 1 / sqrt(x) for x > 0 by Goldschmidt's coupled iteration
-// (g -> sqrt(x), h -> 1 / (2 sqrt(x)), each step squaring the relative error
-// r = 1/2 - g h) from the hardware reciprocal square root estimate; two steps
-// take the estimate's error below the FP64 rounding level.
-__device__ __forceinline__ void sqrt_rsqrt(double x, double &sq, double &rs) {
-  const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double r = fma(-g, h, 0.5);
-    g = fma(g, r, g);
-    h = fma(h, r, h);
-  }
-  sq = g;
-  rs = 2.0 * h;
-}
-
 // Elimination of the diagonal block d[] (column q in lane q of each 16-lane
 // group), applied to the columns b[] as well; dv receives pivot c in lane c of
 // each group.  With u = -column / pivot, row r is updated by (row r of column c) u.

@@ -7,11 +7,11 @@
 //
 // Jacobi: a block method.  The indices form blocks of 32; the block pairs of a
 // round follow the round-robin (circle) schedule, so their rotations are
-// disjoint.  Per round, each pair's 64 x 64 principal submatrix is diagonalised
-// in LDS by cyclic Jacobi (rotations accumulated from the identity), then every
-// pair's columns of A and V are multiplied by its 64 x 64 rotation and its rows
-// of A by the transpose (two passes of 64-wide tile products).  A sweep thus
-// passes over A and V n/32 times instead of n times.
+// disjoint.  Per round, each pair's 64 x 64 principal submatrix is reduced by one
+// sweep of cyclic Jacobi (rotations accumulated from the identity), then every
+// 64 x 64 block of A is multiplied by its row pair's rotation from the left and its
+// column pair's from the right, and V from the right (one pass of tile products).
+// A sweep thus passes over A and V n/32 times instead of n times.
 //
 // Woodbury Newton: with W the likelihood curvature (Q_l = diag(W)) and
 // S = diag(sqrt(W)), the symmetric form of Eq. (woodeqn) is
@@ -103,206 +103,350 @@ __global__ __launch_bounds__(256) void jacobi_init_kernel(const JacDesc *__restr
   J.V[(size_t)c * J.ne + i] = i == c ? 1.0 : 0.0;
 }
 
+// 1 / sqrt(x), x > 0 in the normal range: the hardware estimate y (relative error
+// 2^-20 or less) with e = 1 - x y^2 removed to e^3.
+__device__ __forceinline__ double rsqrt_fast(double x) {
+  const double y = __builtin_amdgcn_rsq(x), e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// The same rotation (also with t = s / c) by half angles, two reciprocal square
+// roots in a row and nothing else that takes time: with d = aqq - app, b = 2 apq and
+// y = 1 / sqrt(d^2 + b^2), c^2 = (1 + |d| y) / 2 and s = sgn(d b) |b| y / (2 c).
+// Entries whose squares leave the normal range take the scaled form above.
+__device__ __forceinline__ void jac_rot_fast(double app, double aqq, double apq, double &c, double &s, double &t) {
+  const double d = aqq - app, b = 2.0 * apq, big = fmax(fabs(d), fabs(b));
+  const double y = rsqrt_fast(fma(d, d, b * b));
+  const double c2 = fma(0.5 * fabs(d), y, 0.5), rc = rsqrt_fast(c2);
+  c = c2 * rc;
+  s = fabs(apq) * (y * rc);
+  if (d * b < 0.0) s = -s;
+  t = s * rc;
+  if (apq == 0.0) {
+    c = 1.0;
+    s = t = 0.0;
+  } else if (!(big > 0x1p-400 && big < 0x1p400)) {
+    jac_rot(app, aqq, apq, c, s);
+    t = s / c;
+  }
+}
+
 // Inner eigenproblem of one block pair: the JP x JP principal submatrix S of A
 // on the pair's indices is reduced in LDS by cyclic Jacobi (round-robin over
 // its JP indices, rotations accumulated from the identity, so R stays close to
 // I, which the outer iteration's convergence needs): JAC_INNER_SWEEPS sweeps,
 // none once its off-diagonal part is at the rounding level.  Writes R
 // (column-major).  Grid (nbk / 2 pairs, B).
-__global__ __launch_bounds__(256) void jacobi_pair_eig_kernel(const JacDesc *__restrict__ jd, int r) {
+//
+// A chain of 63 rounds with one barrier each: wave 0 updates the 32 blocks of S that
+// hold the next round's pivots and forms the next rotations from them, while waves
+// 1 .. 8 update the other 464 (S as its lower triangle in LDS, both sides of the
+// rotations applied to whole 2 x 2 blocks (t, u), t < u, of index pairs in one pass)
+// and waves 9 .. 12 rotate R in registers, where only the columns that change waves
+// with the schedule pass through LDS (8 KB a round and not 64).  The
+// player in slot s of the next round is in slot s + 1 (slot 0: in slot 0), so the
+// next pivot of pair s is the element of slots s + 1 and 64 - s: (q, p) of the
+// block (s - 1, s + 1), at the ends (p, p) of (0, 1) and (q, q) of (30, 31).
+// 16 pairs at n = 1000: 43.5 us per launch; 136 us with library square roots and
+// divisions, two full passes over S and one over R between three barriers a round;
+// 75 us with S as a triangle and the rotations formed between the rounds.
+constexpr int JEIG_R = 9;   // first of the four waves that hold R
+constexpr int JEIG_THREADS = 64 * (JEIG_R + 4);
+__global__ __launch_bounds__(JEIG_THREADS) void jacobi_pair_eig_kernel(const JacDesc *__restrict__ jd, int r) {
   const JacDesc J = jd[blockIdx.y];
   const int j = blockIdx.x;
   if (j >= J.nbk / 2) return;
   const int rb = r % (J.nbk - 1);
   const int I = rr_pos(j, rb, J.nbk), K = rr_pos(J.nbk - 1 - j, rb, J.nbk);
-  __shared__ double S[JP][JP + 1];    // S[row][col]
-  __shared__ double Rt[JP][JP + 1];   // Rt[col][row] = R(row, col)
-  __shared__ double cs[JP / 2], sn[JP / 2];
-  __shared__ int pp[JP / 2], qq[JP / 2];
-  __shared__ double sh[4];
-  const int tid = threadIdx.x;
+  __shared__ double S[JP][JP + 1];    // S[row][col], row >= col
+  __shared__ __attribute__((aligned(16))) d2 rot[2][JP / 2];   // (c, s) of a round's pairs
+  __shared__ double xch[2][4][2][64];   // columns of R that change waves (by round parity)
+  constexpr int NW = JEIG_THREADS / 64;
+  __shared__ double sh[2][NW];
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const auto *A = gptr((const double *)J.A);
-  for (int e = tid; e < JP * JP; e += 256) {
+  double off = 0.0, dia = 0.0;
+  for (int e = tid; e < JP * JP; e += JEIG_THREADS) {
     const int l = e % JP, m = e / JP;
-    S[l][m] = A[(size_t)pair_idx(m, I, K) * J.ne + pair_idx(l, I, K)];
-    Rt[m][l] = l == m ? 1.0 : 0.0;
+    if (l >= m) {
+      const double v = A[(size_t)pair_idx(m, I, K) * J.ne + pair_idx(l, I, K)];
+      S[l][m] = v;
+      if (l == m) dia += v * v;
+      else off += v * v;
+    }
   }
+  off = wave_sum(off);
+  dia = wave_sum(dia);
+  if (lane == 0) { sh[0][w] = off; sh[1][w] = dia; }
   __syncthreads();
+  off = dia = 0.0;
+  for (int q = 0; q < NW; ++q) { off += 2.0 * sh[0][q]; dia += sh[1][q]; }
   const double eps = 2.220446049250313e-16;
-  for (int sw = 0; sw < JAC_INNER_SWEEPS; ++sw) {
-    double off = 0.0, fro = 0.0;
-    for (int e = tid; e < JP * JP; e += 256) {
-      const int l = e % JP, m = e / JP;
-      const double v = S[l][m];
-      fro += v * v;
-      if (l != m) off += v * v;
+  static_assert(JAC_INNER_SWEEPS == 1, "one inner sweep");
+  auto pos = [](int slot, int ri) {   // rr_pos(slot, ri, JP) for ri < JP
+    const int v = slot + ri;
+    return slot == 0 ? 0 : (v > JP - 1 ? v - (JP - 1) : v);
+  };
+  auto at = [&](int a, int b) { return &S[max(a, b)][min(a, b)]; };
+  // positions of the four slots of this thread's block (t, u), one round further
+  // with each advance (slot 0 stays)
+  struct Block {
+    int p1, q1, p2, q2, fixed;
+    __device__ __forceinline__ void set(int t, int u) {
+      p1 = t; q1 = JP - 1 - t; p2 = u; q2 = JP - 1 - u;
+      fixed = t == 0;
     }
-    off = block_sum256(off, sh);
-    fro = block_sum256(fro, sh);
-    // already diagonal to the rounding level: no rotation
-    if (off <= 16.0 * eps * eps * fro) break;
+    __device__ __forceinline__ void advance() {
+      auto next = [](int v) { return v == JP - 1 ? 1 : v + 1; };
+      p1 = fixed ? 0 : next(p1);
+      q1 = next(q1); p2 = next(p2); q2 = next(q2);
+    }
+  } blk;
+  // its elements (p1,p2) (p1,q2) (q1,p2) (q1,q2) and their values
+  auto block_load = [&](double *(&e)[4], double (&v)[4]) {
+    e[0] = at(blk.p1, blk.p2);
+    e[1] = at(blk.p1, blk.q2);
+    e[2] = at(blk.q1, blk.p2);
+    e[3] = at(blk.q1, blk.q2);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) v[x] = *e[x];
+  };
+  auto block_rotate = [&](int t, int u, int ri, double (&v)[4]) {
+    const d2 r1 = rot[ri & 1][t], r2 = rot[ri & 1][u];
+    const double c1 = r1[0], s1 = r1[1], c2 = r2[0], s2 = r2[1];
+    const double pp = c2 * v[0] - s2 * v[1], pq = s2 * v[0] + c2 * v[1];
+    const double qp = c2 * v[2] - s2 * v[3], qq = s2 * v[2] + c2 * v[3];
+    v[0] = c1 * pp - s1 * qp;
+    v[1] = c1 * pq - s1 * qq;
+    v[2] = s1 * pp + c1 * qp;
+    v[3] = s1 * pq + c1 * qq;
+  };
+  // rotation of pair `lane` in round ri with pivot apq (written as the zero it becomes)
+  auto rotation = [&](int ri, double apq) {
+    const int p = pos(lane, ri), q = pos(JP - 1 - lane, ri);
+    const double app = S[p][p], aqq = S[q][q];
+    double c, s, t;
+    jac_rot_fast(app, aqq, apq, c, s, t);
+    rot[ri & 1][lane] = d2{c, s};
+    S[p][p] = fma(-t, apq, app);
+    S[q][q] = fma(t, apq, aqq);
+  };
+  // already diagonal to the rounding level: no rotation (the same value in every wave)
+  const bool work = off > 16.0 * eps * eps * (off + dia);
+  // The three roles run loops of their own (their registers are not kept together),
+  // each with one barrier before and one after every round.
+  if (w == 0) {
+    if (!work) return;
+    const int bt = lane == 0 ? 0 : lane - 1, bu = lane == 0 ? 1 : min(lane + 1, JP / 2 - 1);
+    blk.set(min(bt, JP / 2 - 2), bu);
+    const bool on = lane < JP / 2;
+    if (on) {
+      double *e = at(pos(lane, 0), pos(JP - 1 - lane, 0));
+      rotation(0, *e);
+      *e = 0.0;
+    }
+    __syncthreads();
     for (int ri = 0; ri < JP - 1; ++ri) {
-      if (tid < JP / 2) {
-        const int p = rr_pos(tid, ri, JP), q = rr_pos(JP - 1 - tid, ri, JP);
-        double c, s;
-        jac_rot(S[p][p], S[q][q], S[q][p], c, s);
-        pp[tid] = p; qq[tid] = q; cs[tid] = c; sn[tid] = s;
-      }
-      __syncthreads();
-      // Each thread owns row i of the pairs t = tid / JP + 4 u (u < 8): all its
-      // loads are issued before any of its stores (the pairs' columns are
-      // disjoint, so no thread reads what another writes in the same pass).
-      constexpr int NU = (JP / 2) * JP / 256;
-      {
-        const int i = tid % JP, t0 = tid / JP;
-        double a[NU], b[NU], ra[NU], rb2[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {   // columns p, q of S and of R
-          const int t = t0 + 4 * u, p = pp[t], q = qq[t];
-          a[u] = S[i][p]; b[u] = S[i][q]; ra[u] = Rt[p][i]; rb2[u] = Rt[q][i];
-        }
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-          const int t = t0 + 4 * u, p = pp[t], q = qq[t];
-          const double c = cs[t], s = sn[t];
-          S[i][p] = c * a[u] - s * b[u];
-          S[i][q] = s * a[u] + c * b[u];
-          Rt[p][i] = c * ra[u] - s * rb2[u];
-          Rt[q][i] = s * ra[u] + c * rb2[u];
-        }
-      }
-      __syncthreads();
-      {
-        const int i = tid % JP, t0 = tid / JP;
-        double a[NU], b[NU];
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {   // rows p, q of S; the pair's entry is annihilated
-          const int t = t0 + 4 * u;
-          a[u] = S[pp[t]][i]; b[u] = S[qq[t]][i];
-        }
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-          const int t = t0 + 4 * u, p = pp[t], q = qq[t];
-          const double c = cs[t], s = sn[t];
-          S[p][i] = i == q ? 0.0 : c * a[u] - s * b[u];
-          S[q][i] = i == p ? 0.0 : s * a[u] + c * b[u];
-        }
+      if (on) {
+        double *e[4], v[4];
+        block_load(e, v);
+        block_rotate(bt, bu, ri, v);
+        const bool more = ri + 1 < JP - 1;
+        const double apq = lane == 0 ? v[0] : lane == JP / 2 - 1 ? v[3] : v[2];
+        *e[0] = more && lane == 0 ? 0.0 : v[0];
+        *e[1] = v[1];
+        *e[2] = more && lane > 0 && lane < JP / 2 - 1 ? 0.0 : v[2];
+        *e[3] = more && lane == JP / 2 - 1 ? 0.0 : v[3];
+        if (more) rotation(ri + 1, apq);
+        blk.advance();
       }
       __syncthreads();
     }
+  } else if (w < JEIG_R) {
+    if (!work) return;
+    // the other blocks in order of u, then t: row u holds u - 1 of them (u > 2; one
+    // less at u = 31, where two blocks hold pivots), and (1, 2)
+    int x = tid - 64, bu = 3;
+    for (; bu < JP / 2; ++bu) {
+      const int row = bu - (bu == JP / 2 - 1 ? 2 : 1);
+      if (x < row) break;
+      x -= row;
+    }
+    int bt = x < bu - 2 ? x : bu - 1;   // t = u - 2 is a pivot block
+    if (tid == 64 * JEIG_R - 1) { bt = 1; bu = 2; }
+    const bool on = bu < JP / 2;
+    blk.set(min(bt, JP / 2 - 2), min(bu, JP / 2 - 1));
+    __syncthreads();
+    for (int ri = 0; ri < JP - 1; ++ri) {
+      if (on) {
+        double *e[4], v[4];
+        block_load(e, v);
+        block_rotate(bt, bu, ri, v);
+#pragma unroll
+        for (int x4 = 0; x4 < 4; ++x4) *e[x4] = v[x4];
+        blk.advance();
+      }
+      __syncthreads();
+    }
+  } else {
+    // R in registers: lane = row, wave k the columns in slots 8 k + i (lo) and
+    // 63 - 8 k - i (hi), i < 8, which are the pairs 8 k + i
+    const int k = w - JEIG_R, k8 = 8 * k;
+    double lo[8], hi[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      lo[i] = lane == k8 + i ? 1.0 : 0.0;
+      hi[i] = lane == JP - 1 - k8 - i ? 1.0 : 0.0;
+    }
+    // the columns that changed waves after round ri
+    auto receive = [&](int ri) {
+      if (k < 3) lo[7] = xch[ri & 1][k + 1][0][lane];
+      if (k > 0) hi[0] = xch[ri & 1][k - 1][1][lane];
+    };
+    if (work) {
+      __syncthreads();
+      for (int ri = 0; ri < JP - 1; ++ri) {
+        if (ri > 0) receive(ri - 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const d2 rt = rot[ri & 1][k8 + i];
+          const double a = lo[i], b = hi[i];
+          lo[i] = rt[0] * a - rt[1] * b;
+          hi[i] = rt[1] * a + rt[0] * b;
+        }
+        // next round: slot s takes slot s + 1's column, slot 63 slot 1's, slot 0 its own
+        if (k > 0) xch[ri & 1][k][0][lane] = lo[0];
+        if (k < 3) xch[ri & 1][k][1][lane] = hi[7];
+        const double slot0 = lo[0], slot1 = lo[1], slot32 = hi[7];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) lo[i] = lo[i + 1];
+#pragma unroll
+        for (int i = 7; i > 0; --i) hi[i] = hi[i - 1];
+        if (k == 0) {
+          lo[0] = slot0;
+          hi[0] = slot1;
+        }
+        if (k == 3) lo[7] = slot32;
+        __syncthreads();
+      }
+      receive(JP - 2);
+    }
+    // after 63 rounds (or none) every column is back in the slot of its number
+    auto *Rg = gptr(J.R) + (size_t)j * JP * JP + lane;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      Rg[(k8 + i) * JP] = lo[i];
+      Rg[(JP - 1 - k8 - i) * JP] = hi[i];
+    }
   }
-  double *Rg = J.R + (size_t)j * JP * JP;
-  for (int e = tid; e < JP * JP; e += 256) Rg[e] = Rt[e / JP][e % JP];
 }
 
-// Columns of every pair: X[:, pair] <- X[:, pair] R for X = A (z even) and
-// X = V (z odd), one 64-row tile per workgroup.  Grid (ne / 64, nbk / 2, 2 B).
-__global__ __launch_bounds__(256) void jacobi_pair_cols_kernel(const JacDesc *__restrict__ jd, int r) {
-  const JacDesc J = jd[blockIdx.z >> 1];
-  double *X = (blockIdx.z & 1) ? J.V : J.A;
-  const int j = blockIdx.y, i0 = blockIdx.x * 64;
-  if (j >= J.nbk / 2 || i0 >= J.ne) return;
-  const int rb = r % (J.nbk - 1);
-  const int I = rr_pos(j, rb, J.nbk), K = rr_pos(J.nbk - 1 - j, rb, J.nbk);
-  __shared__ double Xt[64][JP + 1];   // Xt[row][l]
+// A <- G^T A G and V <- V G for the round's block rotation G = diag(R_j), one
+// launch: workgroups x < nA take the 64 x 64 blocks (j1, j2), j2 <= j1, of A on the
+// index pairs, x >= nA the 64-row tiles of V.  A block is read once, multiplied on
+// both sides in registers and written with its mirror image (a pair's own block
+// keeps the computed R^T S R: the inner iteration's rounding-level residual stays
+// in A for later rounds; writing diag(lambda) there instead discards it, which a
+// CPU model measured as about 20 times less accurate).  FP64 MFMA: wave w owns 16
+// columns of X R_2, whose accumulator layout (row g + 4 v, column li) is the operand
+// layout of R_1^T (X R_2), so nothing passes through LDS between the two products.
+// In place of a column pass over A and V and a row pass over A: 28 n^2 bytes per
+// round and not 48 n^2, and one launch less (n = 1000: 15.0 us, 19.6 + 14.8 before).
+__global__ __launch_bounds__(256) void jacobi_pair_apply_kernel(const JacDesc *__restrict__ jd, int r, int nA) {
+  const JacDesc J = jd[blockIdx.y];
+  const int np = J.nbk / 2, rb = r % (J.nbk - 1);
+  __shared__ double Xs[64][JP + 1];   // Xs[row][l]
   __shared__ double Rs[JP][JP + 1];   // Rs[l][m] = R(l, m)
-  const int tid = threadIdx.x;
-  const double *Rg = J.R + (size_t)j * JP * JP;
-  auto *Xg = gptr(X);
-  for (int e = tid; e < 64 * JP; e += 256) {
-    const int row = e % 64, l = e / 64;
-    Xt[row][l] = Xg[(size_t)pair_idx(l, I, K) * J.ne + i0 + row];
-    Rs[e % JP][e / JP] = Rg[e];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, li = lane & 15, g = lane >> 4;
+  auto first = [&](int j) { return rr_pos(j, rb, J.nbk); };
+  auto second = [&](int j) { return rr_pos(J.nbk - 1 - j, rb, J.nbk); };
+  if ((int)blockIdx.x < nA) {
+    // block x = j1 (j1 + 1) / 2 + j2
+    const int x = blockIdx.x;
+    int j1 = (int)((sqrtf(8.0f * x + 1.0f) - 1.0f) * 0.5f);
+    while ((j1 + 1) * (j1 + 2) / 2 <= x) ++j1;
+    while (j1 * (j1 + 1) / 2 > x) --j1;
+    const int j2 = x - j1 * (j1 + 1) / 2;
+    if (j1 >= np) return;
+    const int I1 = first(j1), K1 = second(j1), I2 = first(j2), K2 = second(j2);
+    auto *Ag = gptr(J.A);
+    const auto *R1 = gptr((const double *)J.R) + (size_t)j1 * JP * JP;
+    const auto *R2 = gptr((const double *)J.R) + (size_t)j2 * JP * JP;
+    double r2[16];   // R_2(4 s + g, 16 w + li)
+#pragma unroll
+    for (int s = 0; s < 16; ++s) r2[s] = R2[(16 * w + li) * JP + 4 * s + g];
+#pragma unroll
+    for (int q = 0; q < JP * JP / 256; ++q) {
+      const int e = tid + 256 * q, l = e % JP, m = e / JP;
+      Xs[l][m] = Ag[(size_t)pair_idx(m, I2, K2) * J.ne + pair_idx(l, I1, K1)];
+      Rs[l][m] = R1[e];
+    }
+    __syncthreads();
+    d4 y[4], z[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) y[b] = z[b] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        y[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[16 * b + li][4 * s + g], r2[s], y[b], 0, 0, 0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+          z[a] = __builtin_amdgcn_mfma_f64_16x16x4f64(Rs[16 * b + g + 4 * v][16 * a + li], y[b][v], z[a], 0, 0, 0);
+    // z[a][v]: row 16 a + g + 4 v, column 16 w + li of the new block; first its
+    // mirror image (128-byte segments), then, through LDS, the block itself
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        Ag[(size_t)pair_idx(16 * a + g + 4 * v, I1, K1) * J.ne + pair_idx(16 * w + li, I2, K2)] = z[a][v];
+    if (j1 == j2) return;
+    __syncthreads();   // every wave has read Xs
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Xs[16 * a + g + 4 * v][16 * w + li] = z[a][v];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < JP * JP / 256; ++q) {
+      const int e = tid + 256 * q, l = e % JP, m = e / JP;
+      Ag[(size_t)pair_idx(m, I2, K2) * J.ne + pair_idx(l, I1, K1)] = Xs[l][m];
+    }
+    return;
+  }
+  // V tile: rows i0 .. i0 + 63 times R_j (operands swapped, so that each store
+  // covers 128-byte column segments)
+  const int tiles = J.ne / 64, x = blockIdx.x - nA, j = x / tiles, i0 = (x % tiles) * 64;
+  if (j >= np) return;
+  const int I = first(j), K = second(j);
+  auto *Vg = gptr(J.V);
+  const auto *Rg = gptr((const double *)J.R) + (size_t)j * JP * JP;
+#pragma unroll
+  for (int q = 0; q < JP * JP / 256; ++q) {
+    const int e = tid + 256 * q, l = e % JP, m = e / JP;
+    Xs[l][m] = Vg[(size_t)pair_idx(m, I, K) * J.ne + i0 + l];
+    Rs[l][m] = Rg[e];
   }
   __syncthreads();
-  // 64 x 64 x 64 product on FP64 MFMA: wave w owns the 32 x 32 quadrant
-  // (rows wr.., columns wc..) as 2 x 2 blocks of 16 x 16.  Operands are
-  // swapped as in the factorisation's trailing update, so lane l's four
-  // results are output row li of columns g + 4v and each store covers whole
-  // 128-byte column segments.
-  const int lane = tid & 63, w = tid >> 6, li = lane & 15, g = lane >> 4;
-  const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-  d4 acc[2][2];
+  d4 y[4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int b = 0; b < 4; ++b) y[b] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll 4
-  for (int k0 = 0; k0 < JP; k0 += 4) {
-    const int k = k0 + g;
-    double x[2], q[2];
+  for (int s = 0; s < 16; ++s) {
+    const double xr = Xs[16 * w + li][4 * s + g];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) x[a] = Xt[wr + 16 * a + li][k];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) q[b] = Rs[k][wc + 16 * b + li];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(q[b], x[a], acc[a][b], 0, 0, 0);
+    for (int b = 0; b < 4; ++b)
+      y[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(Rs[4 * s + g][16 * b + li], xr, y[b], 0, 0, 0);
   }
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const size_t col = (size_t)pair_idx(wc + 16 * b + g + 4 * v, I, K) * J.ne + i0;
-#pragma unroll
-      for (int a = 0; a < 2; ++a) Xg[col + wr + 16 * a + li] = acc[a][b][v];
-    }
-}
-
-// Rows of every pair: A[pair, :] <- R^T A[pair, :], one 64-column tile per
-// workgroup.  The pair's own block keeps the computed R^T S R: the inner
-// iteration's rounding-level residual stays in A for later rounds (writing
-// diag(lambda) there instead discards it, which a CPU model measured as about
-// 20 times less accurate).  Grid (ne / 64, nbk / 2, B).
-__global__ __launch_bounds__(256) void jacobi_pair_rows_kernel(const JacDesc *__restrict__ jd, int r) {
-  const JacDesc J = jd[blockIdx.z];
-  const int j = blockIdx.y, c0 = blockIdx.x * 64;
-  if (j >= J.nbk / 2 || c0 >= J.ne) return;
-  const int rb = r % (J.nbk - 1);
-  const int I = rr_pos(j, rb, J.nbk), K = rr_pos(J.nbk - 1 - j, rb, J.nbk);
-  __shared__ double At[JP][64 + 1];   // At[l][col]
-  __shared__ double Rs[JP][JP + 1];   // Rs[l][m] = R(l, m)
-  const int tid = threadIdx.x;
-  const double *Rg = J.R + (size_t)j * JP * JP;
-  auto *Ag = gptr(J.A);
-  for (int e = tid; e < JP * 64; e += 256) {
-    const int l = e % JP, col = e / JP;
-    At[l][col] = Ag[(size_t)(c0 + col) * J.ne + pair_idx(l, I, K)];
-    Rs[e % JP][e / JP] = Rg[e];
-  }
-  __syncthreads();
-  // R^T At on FP64 MFMA, laid out as in the column pass: lane l's four
-  // results are pair row wr + 16 a + li of columns g + 4v (16 consecutive pair
-  // rows lie in one 32-row block, so each store covers 128-byte segments).
-  const int lane = tid & 63, w = tid >> 6, li = lane & 15, g = lane >> 4;
-  const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-  d4 acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-  for (int k0 = 0; k0 < JP; k0 += 4) {
-    const int k = k0 + g;
-    double p[2], q[2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) p[a] = Rs[k][wr + 16 * a + li];
-#pragma unroll
-    for (int b = 0; b < 2; ++b) q[b] = At[k][wc + 16 * b + li];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(q[b], p[a], acc[a][b], 0, 0, 0);
-  }
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const size_t col = (size_t)(c0 + wc + 16 * b + g + 4 * v) * J.ne;
-#pragma unroll
-      for (int a = 0; a < 2; ++a) Ag[col + pair_idx(wr + 16 * a + li, I, K)] = acc[a][b][v];
-    }
+    for (int v = 0; v < 4; ++v)
+      Vg[(size_t)pair_idx(16 * b + g + 4 * v, I, K) * J.ne + i0 + 16 * w + li] = y[b][v];
 }
 
 // Sums of squares of the off-diagonal and of all entries: workgroup g sums
@@ -475,20 +619,19 @@ static int pinv_batch(Ctx &ctx, int B, const int *n, const double *const *Q, con
     const JacDesc *da = (const JacDesc *)ctx.upload(ha.data(), sizeof(JacDesc) * ha.size());
     if (!da) return INLA_ERR_NOMEM;
     const int nb = (int)ha.size(), nbk = ne_act / JB, tiles = ne_act / 64;
-    // per round: columns of A and V (2 JP flops and 16 bytes per element each),
-    // then rows of A
-    const double round_flops = 6.0 * JP * (double)ne_act * ne_act * nb;
-    const double round_bytes = 48.0 * (double)ne_act * ne_act * nb;
+    // per round: both sides of the lower half of A, columns of V (2 JP flops per
+    // element and side); each element of both read and written once
+    const double round_flops = 4.0 * JP * (double)ne_act * ne_act * nb;
+    const double round_bytes = 28.0 * (double)ne_act * ne_act * nb;
+    const int nA = (nbk / 2) * (nbk / 2 + 1) / 2;
     for (int k = 0; k < nbk - 1; ++k, ++r) {
       const int rr = r;
       ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-        hipLaunchKernelGGL(jacobi_pair_eig_kernel, dim3(nbk / 2, nb), dim3(256), 0, ctx.stream, da, rr);
+        hipLaunchKernelGGL(jacobi_pair_eig_kernel, dim3(nbk / 2, nb), dim3(JEIG_THREADS), 0, ctx.stream, da, rr);
       });
-      ctx.launch(INLA_K_SOLVE, round_flops * 2.0 / 3.0, round_bytes * 2.0 / 3.0, [&] {
-        hipLaunchKernelGGL(jacobi_pair_cols_kernel, dim3(tiles, nbk / 2, 2 * nb), dim3(256), 0, ctx.stream, da, rr);
-      });
-      ctx.launch(INLA_K_SOLVE, round_flops / 3.0, round_bytes / 3.0, [&] {
-        hipLaunchKernelGGL(jacobi_pair_rows_kernel, dim3(tiles, nbk / 2, nb), dim3(256), 0, ctx.stream, da, rr);
+      ctx.launch(INLA_K_SOLVE, round_flops, round_bytes, [&] {
+        hipLaunchKernelGGL(jacobi_pair_apply_kernel, dim3(nA + tiles * (nbk / 2), nb), dim3(256), 0, ctx.stream, da,
+                           rr, nA);
       });
     }
     ctx.launch(INLA_K_SOLVE, 0.0, 8.0 * ne_act * ne_act * nb, [&] {
