@@ -102,172 +102,286 @@ __device__ __forceinline__ void block64_load(const T *__restrict__ Mg, T (&e)[16
   for (int q = 0; q < 16; ++q) e[q] = g[(16 * w + q) * 64 + m];
 }
 
-// Sums a[0..15] over the 64 lanes of a wave: lane l returns the total of
-// a[l >> 2].  A butterfly that halves the values it carries at each of the
-// first four exchanges (lane bits 5, 4, 3, 2 pick the half kept), then adds
-// across lane bits 1 and 0: 17 exchanges in place of 16 full reductions.
-// a is overwritten.
-template <int HALF>
-__device__ __forceinline__ void fold_half(double (&a)[16], int l) {
-  const bool up = (l & (4 * HALF)) != 0;
+// The lanes of a double moved by a DPP control (within rows of 16 lanes).
+template <int CTRL> __device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Sum over each row of 16 lanes, in all of them (rotations by 8, 4, 2 and 1).
+__device__ __forceinline__ double row_sum16(double v) {
+  v += dpp64<0x128>(v);
+  v += dpp64<0x124>(v);
+  v += dpp64<0x122>(v);
+  v += dpp64<0x121>(v);
+  return v;
+}
+// Sums of a and b over lanes l and l ^ 32 (H = 32) or l ^ 16: a's in the rows of 16
+// lanes whose bit H is clear, b's in the others.
+template <int H> __device__ __forceinline__ double fold2(double a, double b) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 lo, hi;
+  if (H == 32) {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false));
+  } else {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false));
+  }
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sums of a[0..3] over the 64 lanes: lane l returns the total of a[l >> 4].
+__device__ __forceinline__ double wave_sum4(const double *a) {
+  return row_sum16(fold2<16>(fold2<32>(a[0], a[2]), fold2<32>(a[1], a[3])));
+}
+// v of lane l (a constant).
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// --------------------------------------------------------------------------
+// Triangular solves with the big factor in steps of 256 rows, one launch per step
+// over every theta: a workgroup of 1024 threads updates 256 rows (forward) or
+// columns (backward) by the step's solved block, and the one that holds the next
+// block's also solves that block, by its 64 x 64 sub-blocks with the stored
+// inverses of the diagonal ones.  A chain of n / 256 dependent launches, bound by
+// latency but for large batches, where the factor's bytes bound it: steps of 256
+// in place of 64 because a launch (start, loads of L and of the solved block, the
+// next block's solve) takes little longer for four times the rows.
+//
+// In the solve of a block the 16 waves share every product by its summed index
+// (forward) or its result (backward), four each, so that a sub-block costs two
+// barriers, and between them one LDS read per lane and sums over lanes by DPP and
+// permlane swaps; operands that all lanes need come by readlane, not by LDS reads
+// that each would occupy the LDS for a whole wave.  A wave's share of the products
+// with the rows (columns) still to be solved stays in its registers until their
+// turn comes.  A step of 256 in FP32: 13.3 us forward, 11.9 us backward at order
+// 16384, 10.4 and 8.9 us at 1024 with six matrices (steps of 64: 4.2 us each and
+// 1.5 us between launches); FP64 backward, nine of 3000: 19.5 us (6.1 us and the gap).
+// --------------------------------------------------------------------------
+constexpr int TSB = 256;
+constexpr int TSP = TSB + 2;   // a wave's partial sums: padded against bank conflicts
+
+// Four consecutive values from a 16-byte aligned address.
+template <typename T, typename P> __device__ __forceinline__ void load4(T (&v)[4], P p) {
+  constexpr int VEC = 16 / sizeof(T);
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  typedef __attribute__((address_space(1))) const vec_t gcvec;
 #pragma unroll
-  for (int h = 0; h < HALF; ++h) {
-    const double keep = up ? a[h + HALF] : a[h], send = up ? a[h] : a[h + HALF];
-    a[h] = keep + __shfl_xor(send, 4 * HALF, 64);
+  for (int q = 0; q < 4; q += VEC) {
+    const vec_t x = *(gcvec *)(p + q);
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) v[q + k] = x[k];
   }
 }
-__device__ __forceinline__ double wave_sum16(double (&a)[16]) {
-  const int l = threadIdx.x & 63;
-  fold_half<8>(a, l);
-  fold_half<4>(a, l);
-  fold_half<2>(a, l);
-  fold_half<1>(a, l);
-  double s = a[0];
-  s += __shfl_xor(s, 2, 64);
-  s += __shfl_xor(s, 1, 64);
-  return s;
-}
 
-// y = M v for the block whose elements block64_load read into e: each wave
-// sums its 16 columns, the four partial sums meet in `part` (4 x 64 doubles of
-// LDS).  v and y live in LDS.  All 256 threads take part; returns after a
-// barrier.
-template <typename T>
-__device__ __forceinline__ void block64_mv(const T (&e)[16], const double *v, double *y, double (*part)[64]) {
-  const int tid = threadIdx.x, m = tid & 63, w = tid >> 6;
-  double s = 0.0;
+// Forward solve of the diagonal block at row i0 (nsub sub-blocks of 64): z to the
+// global vector.  acc holds the wave's sums over earlier columns for the block's rows
+// 4 l .. 4 l + 3.  Loads run AHEAD sub-blocks ahead and have no conditions: sub-blocks
+// and rows are clamped to the block, and values above the diagonal are not used.
+template <typename T, typename P>
+__device__ __forceinline__ void solve_block_fwd(const ThetaDesc &t, int i0, int nsub, P r, double (&acc)[4], P z,
+                                                double *part) {
+  constexpr int AHEAD = sizeof(T) == 4 ? 3 : 1;
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q4 = l >> 4;
+  const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 4 * w) * t.ldw + i0;
+  const unsigned lr = min(4 * l, 64 * nsub - 4);
+  const auto *X = gptr((const T *)t.linv) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
+  double *p1 = part, *p2 = part + 16 * TSP;
+  double rv[4];
+  T e[4][4], lo[4][4][4];   // inverses: columns 4 w .. of row l; rows 4 l .. of the sub-block's columns 4 w ..
+  auto load = [&](int b) {
+    const int bc = min(b, nsub - 1);
+    rv[b] = r[i0 + 64 * bc + 4 * w + q4];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) s += (double)e[q] * v[16 * w + q];
-  part[w][m] = s;
-  __syncthreads();
-  if (tid < 64) y[tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
-  __syncthreads();
-}
-
-// y = M^T v for the block in e: y[16w + q] = sum over the rows m (the lanes)
-// of M[m][16w + q] v[m], formed whole by wave w.  v and y live in LDS; returns
-// after a barrier.
-template <typename T>
-__device__ __forceinline__ void block64_mtv(const T (&e)[16], const double *v, double *y) {
-  const int m = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const double vm = v[m];
-  double a[16];
+    for (int q = 0; q < 4; ++q) e[b][q] = X[bc * 4096 + q * 64 + (unsigned)l];
+    if (b < 3) {
 #pragma unroll
-  for (int q = 0; q < 16; ++q) a[q] = (double)e[q] * vm;
-  const double s = wave_sum16(a);
-  if ((m & 3) == 0) y[16 * w + (m >> 2)] = s;
-  __syncthreads();
+      for (int q = 0; q < 4; ++q) load4(lo[b][q], L + (size_t)(64 * bc + q) * t.ldw + lr);
+    }
+  };
+#pragma unroll
+  for (int b = 0; b < AHEAD; ++b) load(b);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (b >= nsub) break;
+    if (b + AHEAD < 4) load(b + AHEAD);
+    if (q4 == b) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) p1[w * TSP + 4 * l + q] = acc[q];
+    }
+    __syncthreads();
+    const double rb = rv[b] - row_sum16(p1[(l & 15) * TSP + 64 * b + 4 * w + q4]);
+    double s = (double)e[b][0] * lane_value(rb, 0) + (double)e[b][1] * lane_value(rb, 16);
+    s += (double)e[b][2] * lane_value(rb, 32) + (double)e[b][3] * lane_value(rb, 48);
+    p2[w * TSP + 64 * b + l] = s;
+    __syncthreads();
+    const double zv = row_sum16(p2[(l & 15) * TSP + 64 * b + 4 * w + q4]);
+    if ((l & 15) == 0) z[i0 + 64 * b + 4 * w + q4] = zv;
+    if (b < 3) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double zq = lane_value(zv, 16 * q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += (double)lo[b][q][k] * zq;
+      }
+    }
+  }
 }
 
-// One 64-row block step of the forward solve L z = r for every theta (a launch
-// per block, blocks from the top).  On entry z_b = L_bb^{-1} r_b is already in
-// z (written by the previous step; the first step forms it from the stored
-// inverse of the diagonal block).  The rows below are updated,
-// r_j -= sum_c L[j][i0 + c] z_b[c], 256 rows per workgroup (one thread per row,
-// each column read contiguous across the threads).  The workgroup holding the
-// next block's rows finalises them and forms z_{b+1} for the next launch.
+// Back solve x = L_bb^{-T} r of the same block: acc[s][q] holds this lane's part of
+// the sum over later rows for column 64 s + 4 w + q.
+template <typename T, typename P>
+__device__ __forceinline__ void solve_block_bwd(const ThetaDesc &t, int i0, int nsub, P r, double (&acc)[4][4], P x,
+                                                double *part) {
+  constexpr int AHEAD = sizeof(T) == 4 ? 3 : 1;
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q4 = l >> 4;
+  const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 4 * w) * t.ldw + i0;
+  const auto *X = gptr((const T *)t.linv) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
+  double *sr = part, *sz = part + TSB;
+  double rv[4];
+  T e[4][4], lo[4][3][4];   // inverses: row l of columns 4 w ..; row l of columns 64 s + 4 w .. of the block row
+  auto load = [&](int b) {
+    const int bc = min(b, nsub - 1);
+    rv[b] = r[i0 + 64 * bc + 4 * w + q4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) e[b][q] = X[bc * 4096 + q * 64 + (unsigned)l];
+#pragma unroll
+    for (int s = 0; s < b; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) lo[b][s][q] = (L + (size_t)(64 * min(s, bc) + q) * t.ldw + 64 * bc)[(unsigned)l];
+  };
+#pragma unroll
+  for (int b = 3; b > 3 - AHEAD; --b) load(b);
+#pragma unroll
+  for (int b = 3; b >= 0; --b) {
+    if (b - AHEAD >= 0) load(b - AHEAD);
+    if (b >= nsub) continue;
+    const double rb = rv[b] - wave_sum4(acc[b]);
+    if ((l & 15) == 0) sr[64 * b + 4 * w + q4] = rb;
+    __syncthreads();
+    const double rl = sr[64 * b + l];
+    double zs[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) zs[q] = (double)e[b][q] * rl;
+    const double xv = wave_sum4(zs);
+    if ((l & 15) == 0) {
+      sz[64 * b + 4 * w + q4] = xv;
+      x[i0 + 64 * b + 4 * w + q4] = xv;
+    }
+    if (b > 0) {
+      __syncthreads();
+      const double zl = sz[64 * b + l];
+#pragma unroll
+      for (int s = 0; s < b; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[s][q] += (double)lo[b][s][q] * zl;
+    }
+  }
+}
+
+// One step of the forward solve L z = r (blocks from the top); i0 < 0: only the first
+// block's solve.  On entry the block's solution is in z.  The rows below are updated,
+// r_j -= sum_c L[j][i0 + c] z_c: wave w takes the columns 16 w .., its lanes four rows
+// each in 16-byte loads.
 template <typename T>
-__global__ __launch_bounds__(256) void trsv_fwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
+__global__ __launch_bounds__(1024) void trsv_fwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
   const ThetaDesc t = td[blockIdx.y];
-  const int np = t.n_pad;
-  if (i0 >= np) return;
-  const int tid = threadIdx.x;
-  const auto *L = gptr((const T *)t.W);
-  const T *linv = (const T *)t.linv;
+  const int np = t.n_pad, j0 = i0 + TSB + blockIdx.x * TSB;
+  if (j0 >= np) return;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nn = min(TSB, np - j0);
+  __shared__ __align__(16) double part[(16 + 16) * TSP];
   auto *r = gptr(vsel(t, src));
   auto *z = gptr(vsel(t, dst));
-  __shared__ double part[4][64];
-  __shared__ double zb[64], rb[64], zn[64];
-  const bool next = blockIdx.x == 0 && i0 + 64 < np;   // this workgroup forms z_{b+1}
-  T e[16];
-  if (i0 == 0) {
-    block64_load(linv, e);
-    if (tid < 64) rb[tid] = r[tid];
-    __syncthreads();
-    block64_mv(e, rb, zb, part);
-    if (blockIdx.x == 0 && tid < 64) z[tid] = zb[tid];
-  } else {
-    if (tid < 64) zb[tid] = z[i0 + tid];
-    __syncthreads();
-  }
-  // the next diagonal block's inverse is read while the rows are updated
-  if (next) block64_load(linv + (size_t)(i0 / 64 + 1) * 4096, e);
-  const int j = i0 + 64 + blockIdx.x * 256 + tid;
-  double nv = 0.0;
-  if (j < np) {
-    T lv[64];   // all 64 loads in flight before the first product
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  if (i0 >= 0) {
+    constexpr int U = sizeof(T) == 4 ? 16 : 8;   // loads in flight before the first product
+    const double zv = z[i0 + 16 * w + (l & 15)];
+    const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 16 * w) * t.ldw + j0;
+    const unsigned lr = min(4 * l, nn - 4);
 #pragma unroll
-    for (int c = 0; c < 64; ++c) lv[c] = L[(size_t)(i0 + c) * t.ldw + j];
-    double s = 0.0;
+    for (int c0 = 0; c0 < 16; c0 += U) {
+      T lv[U][4];
 #pragma unroll
-    for (int c = 0; c < 64; ++c) s += (double)lv[c] * zb[c];
-    nv = r[j] - s;
-    r[j] = nv;
+      for (int c = 0; c < U; ++c) load4(lv[c], L + (size_t)(c0 + c) * t.ldw + lr);
+#pragma unroll
+      for (int c = 0; c < U; ++c) {
+        const double zc = lane_value(zv, c0 + c);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += (double)lv[c][k] * zc;
+      }
+    }
   }
-  if (next) {
-    if (tid < 64) rb[tid] = nv;
-    __syncthreads();
-    block64_mv(e, rb, zn, part);
-    if (tid < 64) z[i0 + 64 + tid] = zn[tid];
+  if (blockIdx.x == 0) {   // the next block
+    solve_block_fwd<T>(t, j0, nn / 64, r, acc, z, part);
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) part[w * TSP + 4 * l + k] = acc[k];
+  __syncthreads();
+  if (tid < nn) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s[k & 3] += part[k * TSP + tid];
+    r[j0 + tid] -= (s[0] + s[1]) + (s[2] + s[3]);
   }
 }
 
-// One 64-row block step of the back solve L^T x = r (blocks from the bottom).
-// On entry x_b = L_bb^{-T} r_b is already in x (the bottom block of a theta
-// forms it from the stored inverse).  The columns above are updated,
-// r_j -= sum_m L[i0 + m][j] x_b[m]: a workgroup takes 64 columns, a wave 16 of
-// them with its lanes on the 64 contiguous rows of each, and the wave's 16 x 64
-// products are summed per column across its lanes (wave_sum16).  The workgroup
-// holding the columns just above the block finalises them and forms x_{b-1}
-// for the next launch.
+// One step of the back solve L^T x = r (blocks from the bottom; block starts are
+// multiples of 256).  i0 is the step's block; the columns above are updated,
+// r_j -= sum_m L[i0 + m][j] x_m: wave w takes columns 64 s + 4 w + q of a workgroup's
+// 256 with its lanes on four contiguous rows each.  A matrix whose last block is the
+// one above (i0 >= n_pad) starts with that block's solve.
 template <typename T>
-__global__ __launch_bounds__(256) void trsv_bwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
+__global__ __launch_bounds__(1024) void trsv_bwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
   const ThetaDesc t = td[blockIdx.y];
-  const int np = t.n_pad;
-  if (i0 >= np) return;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const auto *L = gptr((const T *)t.W);
-  const T *linv = (const T *)t.linv;
+  const int np = t.n_pad, j0 = i0 - TSB - (int)blockIdx.x * TSB;
+  if (j0 < 0 || j0 >= np || (i0 >= np && blockIdx.x != 0)) return;
+  const int tid = threadIdx.x, l = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nb = min(TSB, np - i0), nn = min(TSB, np - j0);
+  __shared__ double part[2 * TSB];
   auto *r = gptr(vsel(t, src));
   auto *x = gptr(vsel(t, dst));
-  __shared__ double xb[64], rb[64], xn[64];
-  T e[16];
-  if (i0 + 64 == np) {
-    block64_load(linv + (size_t)(i0 / 64) * 4096, e);
-    if (tid < 64) rb[tid] = r[i0 + tid];
-    __syncthreads();
-    block64_mtv(e, rb, xb);
-    if (blockIdx.x == 0 && tid < 64) x[i0 + tid] = xb[tid];
-  } else {
-    if (tid < 64) xb[tid] = x[i0 + tid];
-    __syncthreads();
-  }
-  const int g = blockIdx.x;
-  if (64 * g >= i0) return;
-  // the workgroup holding the columns just above the block forms x_{b-1}:
-  // its diagonal block's inverse is read while the columns are updated
-  const bool prev = 64 * g + 64 == i0;
-  if (prev) block64_load(linv + (size_t)(i0 / 64 - 1) * 4096, e);
-  const double xm = xb[lane];
-  const int j0 = 64 * g + 16 * w;
-  T v[16];
+  double acc[4][4];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) v[q] = L[(size_t)(j0 + q) * t.ldw + i0 + lane];
-  double a[16];
+  for (int s = 0; s < 4; ++s)
 #pragma unroll
-  for (int q = 0; q < 16; ++q) a[q] = (double)v[q] * xm;
-  const double s = wave_sum16(a);
-  const int jc = j0 + (lane >> 2);
-  double nv = 0.0;
-  if ((lane & 3) == 0) {
-    nv = r[jc] - s;
-    r[jc] = nv;
+    for (int q = 0; q < 4; ++q) acc[s][q] = 0.0;
+  if (nb > 0) {
+    constexpr int U = sizeof(T) == 4 ? 4 : 2;   // groups of four columns in flight
+    const unsigned m = min(4 * l, nb - 4);
+    double xv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) xv[k] = 4 * l < nb ? x[i0 + m + k] : 0.0;
+    const auto *L = gptr((const T *)t.W) + (size_t)(j0 + 4 * w) * t.ldw + i0;
+#pragma unroll
+    for (int s0 = 0; s0 < 4; s0 += U) {
+      T lv[U][4][4];
+#pragma unroll
+      for (int s = 0; s < U; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load4(lv[s][q], L + (size_t)(64 * (s0 + s) + q) * t.ldw + m);
+#pragma unroll
+      for (int s = 0; s < U; ++s)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[s0 + s][q] = ((double)lv[s][q][0] * xv[0] + (double)lv[s][q][1] * xv[1]) +
+                           ((double)lv[s][q][2] * xv[2] + (double)lv[s][q][3] * xv[3]);
+      __builtin_amdgcn_sched_barrier(0);   // the next group's loads stay behind: registers
+    }
   }
-  if (prev) {
-    if ((lane & 3) == 0) rb[16 * w + (lane >> 2)] = nv;
-    __syncthreads();
-    block64_mtv(e, rb, xn);
-    if (tid < 64) x[i0 - 64 + tid] = xn[tid];
+  if (blockIdx.x == 0) {   // the block above
+    solve_block_bwd<T>(t, j0, nn / 64, r, acc, x, part);
+    return;
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const double v = wave_sum4(acc[s]);
+    if ((l & 15) == s) {
+      const int j = j0 + 64 * s + 4 * w + (l >> 4);
+      r[j] -= v;
+    }
   }
 }
 
@@ -547,10 +661,10 @@ void launch_trsv_fwd(Ctx &ctx, const std::vector<ThetaDesc> &htd, int np_max, in
                                     (int64_t)std::llround(bytes)};
   (void)ctx.sequence(INLA_K_SOLVE, key, htd.data(), sizeof(ThetaDesc) * B, [&](const void *dv) {
     const ThetaDesc *dtd = (const ThetaDesc *)dv;
-    for (int i0 = 0; i0 < np_max; i0 += 64) {
-      const int gx = std::max(1, (np_max - i0 - 64 + 255) / 256);
-      ctx.launch(INLA_K_SOLVE, 0.0, bytes * (double)(np_max - i0) / np_max * 2.0 / np_max, [&] {
-        INLA_DISPATCH_T(prec, trsv_fwd_step_kernel, dim3(gx, B), dim3(256), 0, ctx.stream, dtd, i0, src, dst);
+    for (int i0 = -TSB; i0 + TSB < np_max; i0 += TSB) {
+      const int gx = i0 < 0 ? 1 : (np_max - i0 - 1) / TSB;
+      ctx.launch(INLA_K_SOLVE, 0.0, bytes * (double)(np_max - i0) / np_max * 2.0 * TSB / np_max, [&] {
+        INLA_DISPATCH_T(prec, trsv_fwd_step_kernel, dim3(gx, B), dim3(1024), 0, ctx.stream, dtd, i0, src, dst);
       });
     }
   });
@@ -563,10 +677,11 @@ void launch_trsv_bwd(Ctx &ctx, const std::vector<ThetaDesc> &htd, int np_max, in
                                     (int64_t)std::llround(bytes)};
   (void)ctx.sequence(INLA_K_SOLVE, key, htd.data(), sizeof(ThetaDesc) * B, [&](const void *dv) {
     const ThetaDesc *dtd = (const ThetaDesc *)dv;
-    for (int i0 = np_max - 64; i0 >= 0; i0 -= 64) {
-      const int gx = std::max(1, (i0 + 63) / 64);
-      ctx.launch(INLA_K_SOLVE, 0.0, bytes * (double)(i0 + 64) / np_max * 2.0 / np_max, [&] {
-        INLA_DISPATCH_T(prec, trsv_bwd_step_kernel, dim3(gx, B), dim3(256), 0, ctx.stream, dtd, i0, src, dst);
+    const int top = (np_max + TSB - 1) / TSB * TSB;
+    for (int i0 = top; i0 > 0; i0 -= TSB) {
+      const int gx = i0 == top ? 1 : i0 / TSB;
+      ctx.launch(INLA_K_SOLVE, 0.0, bytes * (double)std::min(i0, np_max) / np_max * 2.0 * TSB / np_max, [&] {
+        INLA_DISPATCH_T(prec, trsv_bwd_step_kernel, dim3(gx, B), dim3(1024), 0, ctx.stream, dtd, i0, src, dst);
       });
     }
   });
