@@ -80,10 +80,12 @@ struct ThetaDesc {
   double *part;    // [2 * ldw] per-column partial sums (loglik, x'Qx)
   double *dres;    // [16] per-theta device results (see DRES_*)
   void *linv;      // inverses of the big factor's 64 x 64 diagonal blocks (factor storage type)
+  double *linv_s;  // the same for the kriging factor
   double *u;       // forward-solve output / refinement correction [n_pad]
   double *symv;    // partial sums of Q_prior v from its lower triangle: P
                    // ((n_pad / 64) x n_pad, block column J's part of row i at
-                   // J n_pad + i), then D [n_pad] (the transposed part)
+                   // J n_pad + i), then D [n_pad] (the transposed part); between two
+                   // of them the border's partial sums, n_pad / 256 x k_pad
   double *out;     // caller's output vector (mode or variances), device
   // variational-Bayes mean correction: with vb_var set, the likelihood terms
   // are expectations over eta ~ N(eta(x), vb_var[i]) by ngh-point Gauss-Hermite
@@ -129,6 +131,39 @@ __device__ __forceinline__ double wave_sum(double v) {
 __device__ __forceinline__ double wave_max(double v) {
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
   return v;
+}
+
+// The lanes of a double moved by a DPP control (within rows of 16 lanes).
+template <int CTRL> __device__ __forceinline__ double dpp64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+// Sum over each row of 16 lanes, in all of them (rotations by 8, 4, 2 and 1).
+__device__ __forceinline__ double row_sum16(double v) {
+  v += dpp64<0x128>(v);
+  v += dpp64<0x124>(v);
+  v += dpp64<0x122>(v);
+  v += dpp64<0x121>(v);
+  return v;
+}
+// Sums of a and b over lanes l and l ^ 32 (H = 32) or l ^ 16: a's in the rows of 16
+// lanes whose bit H is clear, b's in the others.
+template <int H> __device__ __forceinline__ double fold2(double a, double b) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 lo, hi;
+  if (H == 32) {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false));
+  } else {
+    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false));
+    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false));
+  }
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sums of a[0..3] over the 64 lanes: lane l returns the total of a[l >> 4].
+__device__ __forceinline__ double wave_sum4(const double *a) {
+  return row_sum16(fold2<16>(fold2<32>(a[0], a[2]), fold2<32>(a[1], a[3])));
 }
 
 // sqrt(x) and 1 / sqrt(x) for x > 0 by Goldschmidt's coupled iteration

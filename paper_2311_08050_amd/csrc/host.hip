@@ -608,6 +608,7 @@ static void bind(Plan &p, char *base) {
   t.part = v; v += 2 * t.ldw;
   t.dres = v;
   t.linv = (void *)(base + p.off_linv);
+  t.linv_s = (double *)(base + p.off_linv_small);
   t.symv = (double *)(base + p.off_symv);
   if (t.m > 0) {
     double *o = (double *)(base + p.off_obs);
@@ -898,7 +899,7 @@ static int refine(Batch &b, const std::vector<int> &ids, int prec, int max_ir, d
       const int npm = max_over(b, act, &ThetaDesc::n_pad), kpm = max_over(b, act, &ThetaDesc::k_pad);
       launch_kkt_residual(b.ctx, d, B, npm, kpm, rb);
       launch_trsv_fwd(b.ctx, b.last_td, npm, V_Z, V_U, 0.5 * tb, prec);
-      launch_ir_correct(b.ctx, d, B, kpm, prec);
+      launch_ir_correct(b.ctx, d, B, npm, kpm, prec);
       launch_rhs(b.ctx, d, B, npm, 1, prec);
       launch_trsv_bwd(b.ctx, b.last_td, npm, V_R, V_U, 0.5 * tb, prec);
       launch_ir_update(b.ctx, d, B);

@@ -414,86 +414,103 @@ __global__ __launch_bounds__(256) void kriging_build_kernel(const ThetaDesc *__r
 }
 
 // y = Q_prior v from the lower triangle of Q_prior alone (half the bytes of a
-// whole-column product; the consumers below finish it).  Block (J, theta) takes
-// the 64 columns [64 J, 64 J + 64) and walks the 64-row tiles at and below the
-// diagonal through LDS: row r of a tile receives sum_{c in J, c <= r} Q_rc v_c,
-// written to P[J][r]; column c receives sum_{r > c} Q_rc v_r, summed over the
-// tiles in registers and written to D[c].  Then (Q v)_i = D[i] + sum over
-// J <= i / 64 of P[J][i], in that order (no atomics: fixed summation order).
+// whole-column product; the consumers below finish it).  A workgroup takes up to
+// SYMV_TILES 64 x 64 tiles of block column J, from the diagonal down: row r of a tile
+// receives sum_{c in J, c <= r} Q_rc v_c, written to P[J][r]; column c receives
+// sum_{r > c} Q_rc v_r over the tiles, written to D[c] by the first workgroup of the
+// block column and to P[J + s][c] by its s-th further one, rows of P that hold no row
+// sums above the diagonal.  Then (Q v)_i = D[i] + the sum of P[j][i] over
+// j < i / 64 + (workgroups of that block column), in a fixed order (no atomics).
+// A lane keeps one row of 16 columns, so both products come from the registers that
+// were loaded, and only their sums cross lanes, once per workgroup.  HBM-bound; four
+// tiles, since one workgroup per block column leaves the longest to run alone: at
+// n = 16384 724 to 279 us (3.9 TB/s), six matrices of 1024 44 to 16 us.
 // src 0: v = xn (refinement residuals); 1: v = x (objective terms).
+constexpr int SYMV_TILES = 4;
+__device__ __forceinline__ int symv_splits(int np, int J) { return (np / 64 - J + SYMV_TILES - 1) / SYMV_TILES; }
 __global__ __launch_bounds__(256) void symv_lower_part_kernel(const ThetaDesc *__restrict__ td, int src) {
-  const ThetaDesc t = td[blockIdx.y];
-  const int J = blockIdx.x, c0 = J * 64, np = t.n_pad, n = t.n;
-  if (c0 >= np) return;
-  const double *v = src ? t.x : t.xn;
-  __shared__ double T[64][65];
-  __shared__ double vc[64], vr[64];
-  __shared__ double red[4][64];
-  const int tid = threadIdx.x, lo = tid & 63, part = tid >> 6;
+  const ThetaDesc t = td[blockIdx.z];
+  const int J = blockIdx.x, sp = blockIdx.y, c0 = J * 64, np = t.n_pad, n = t.n;
+  const int r0 = c0 + sp * 64 * SYMV_TILES;
+  if (r0 >= np) return;
+  const auto *v = gptr((const double *)(src ? t.x : t.xn));
+  __shared__ double red[SYMV_TILES][4][64];
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double *P = t.symv;
-  double *D = t.symv + (size_t)(np / 64) * np;
-  if (tid < 64) vc[tid] = c0 + tid < n ? v[c0 + tid] : 0.0;
-  const double *Qc = t.Qp + (size_t)c0 * t.ldqp;
-  double dot = 0.0;
-  // the next tile's 16 loads per thread are in flight while this tile is reduced
-  double buf[16];
+  const auto *Q = gptr((const double *)t.Qp) + (size_t)(c0 + 16 * w) * t.ldqp;
+  double vc[16], col[16];   // the wave's columns c0 + 16 w ..
 #pragma unroll
-  for (int q = 0; q < 16; ++q) buf[q] = Qc[(size_t)(part + 4 * q) * t.ldqp + c0 + lo];
-  for (int r0 = c0; r0 < np; r0 += 64) {
-    __syncthreads();   // the previous tile and its row sums are consumed
+  for (int q = 0; q < 16; ++q) {
+    const int c = c0 + 16 * w + q;
+    vc[q] = c < n ? v[c] : 0.0;
+    col[q] = 0.0;
+  }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) T[lo][part + 4 * q] = buf[q];
-    if (r0 + 64 < np) {
+  for (int i = 0; i < SYMV_TILES; ++i) {
+    const int r = r0 + 64 * i;
+    if (r >= np) break;
+    double x[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) buf[q] = Qc[(size_t)(part + 4 * q) * t.ldqp + r0 + 64 + lo];
-    }
-    if (tid < 64) vr[tid] = r0 + tid < n ? v[r0 + tid] : 0.0;
-    __syncthreads();
-    const bool diag = r0 == c0;
-    double rs = 0.0;   // row lo, columns 16 part .. 16 part + 15
+    for (int q = 0; q < 16; ++q) x[q] = (Q + (size_t)q * t.ldqp + r)[(unsigned)l];
+    const double vr = r + l < n ? v[r + l] : 0.0;
+    const bool diag = r == c0;
+    double s[2] = {0.0, 0.0};
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int c = 16 * part + q;
-      if (!diag || c <= lo) rs += T[lo][c] * vc[c];
+      const int c = 16 * w + q;
+      s[q & 1] += (diag && c > l ? 0.0 : x[q]) * vc[q];
+      col[q] += (diag && c >= l ? 0.0 : x[q]) * vr;
     }
-    red[part][lo] = rs;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {   // column lo, rows 16 part .. 16 part + 15
-      const int r = 16 * part + q;
-      if (!diag || r > lo) dot += T[r][lo] * vr[r];
-    }
-    __syncthreads();
-    if (tid < 64) P[(size_t)J * np + r0 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+    red[i][w][l] = s[0] + s[1];
   }
   __syncthreads();
-  red[part][lo] = dot;
-  __syncthreads();
-  if (tid < 64) D[c0 + tid] = (red[0][tid] + red[1][tid]) + (red[2][tid] + red[3][tid]);
+  const int r = r0 + 64 * w + l;   // wave w adds up tile w
+  if (r < np) P[(size_t)J * np + r] = (red[w][0][l] + red[w][1][l]) + (red[w][2][l] + red[w][3][l]);
+  double *D = P + (size_t)(sp == 0 ? np / 64 : J + sp) * np + c0 + 16 * w;
+#pragma unroll
+  for (int q = 0; q < 16; q += 4) {
+    const double d = wave_sum4(col + q);
+    if ((l & 15) == 0) D[q + (l >> 4)] = d;
+  }
 }
 
 // (Q_prior v)_i from the partial sums of symv_lower_part_kernel.
 __device__ __forceinline__ double symv_row(const ThetaDesc &t, int i) {
-  const int np = t.n_pad;
+  const int np = t.n_pad, nj = i / 64 + symv_splits(np, i / 64);
   double y = t.symv[(size_t)(np / 64) * np + i];
-  for (int J = 0; J <= i / 64; ++J) y += t.symv[(size_t)J * np + i];
+#pragma unroll 8
+  for (int j = 0; j < nj; ++j) y += t.symv[(size_t)j * np + i];
   return y;
 }
 
 // FP64 residual of the constrained Newton system at the refined iterate xn:
 //   r1 = b - (Q_prior + diag W) xn - C^T lambda,   b = g(x) + W(x) x
 // with g, W at the linearisation point x and Q_prior xn from the lower-triangle
-// partial sums; one thread per row, the result to t.z.
-__global__ __launch_bounds__(256) void kkt_residual_kernel(const ThetaDesc *__restrict__ td) {
+// partial sums, the result to t.z.  A workgroup takes 64 rows, its 16 waves a 16th of
+// the partial sums and of the constraints each: one thread per row walks both alone,
+// which at n = 16384 is 64 workgroups, 193 us (now 17).
+__global__ __launch_bounds__(1024) void kkt_residual_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.y];
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= t.n_pad) return;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6, np = t.n_pad;
+  const int i = blockIdx.x * 64 + l, ic = min(i, t.n - 1), nj = blockIdx.x + symv_splits(np, blockIdx.x);
+  __shared__ double part[16][64];
+  if ((int)blockIdx.x * 64 >= np) return;
+  double s = 0.0;
+#pragma unroll 4
+  for (int j = w; j < nj; j += 16) s += t.symv[(size_t)j * np + i];
+#pragma unroll 4
+  for (int a = w; a < t.k; a += 16) s += t.C[(size_t)a * t.n + ic] * t.lam[a];
+  part[w][l] = s;
+  __syncthreads();
+  if (w != 0) return;
   double r = 0.0;
   if (i < t.n) {
-    double s = symv_row(t, i);
-    for (int a = 0; a < t.k; ++a) s += t.C[(size_t)a * t.n + i] * t.lam[a];
+    double c[4] = {t.symv[(size_t)(np / 64) * np + i], 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) c[q & 3] += part[q][l];
     double g, W, ll;
     lik_point(t, i, t.x[i], g, W, ll);
-    r = (g + W * t.x[i]) - W * t.xn[i] - s;
+    r = (g + W * t.x[i]) - W * t.xn[i] - ((c[0] + c[1]) + (c[2] + c[3]));
   }
   t.z[i] = r;
 }
@@ -516,17 +533,19 @@ __global__ __launch_bounds__(256) void objective_terms_kernel(const ThetaDesc *_
   t.part[t.ldw + i] = xq;
 }
 
-// r2 = e - C xn, one wave per constraint row (zero on padded rows).
+// r2 = e - C xn, a workgroup per constraint row (zero on padded rows).
 __global__ __launch_bounds__(256) void constraint_residual_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.y];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int a = blockIdx.x * 4 + w;
+  const int a = blockIdx.x;
+  __shared__ double sh[4];
   if (a >= t.k_pad) return;
   double s = 0.0;
-  if (a < t.k)
-    for (int i = lane; i < t.n; i += 64) s += t.C[(size_t)a * t.n + i] * t.xn[i];
-  s = wave_sum(s);
-  if (lane == 0) t.rtwo[a] = a < t.k ? (t.e ? t.e[a] : 0.0) - s : 0.0;
+  if (a < t.k) {
+#pragma unroll 8
+    for (int i = threadIdx.x; i < t.n; i += 256) s += t.C[(size_t)a * t.n + i] * t.xn[i];
+  }
+  s = block_sum256(s, sh);
+  if (threadIdx.x == 0) t.rtwo[a] = a < t.k ? (t.e ? t.e[a] : 0.0) - s : 0.0;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -606,7 +625,8 @@ void launch_kriging_build(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max, int
 void launch_objective_terms(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, double bytes) {
   if (B <= 0 || np_max <= 0) return;
   ctx.launch(INLA_K_ASSEMBLE, 0.0, bytes, [&] {
-    hipLaunchKernelGGL(symv_lower_part_kernel, dim3(np_max / 64, B), dim3(256), 0, ctx.stream, dtd, 1);
+    hipLaunchKernelGGL(symv_lower_part_kernel, dim3(np_max / 64, (np_max / 64 + SYMV_TILES - 1) / SYMV_TILES, B), dim3(256), 0,
+                       ctx.stream, dtd, 1);
   });
   ctx.launch(INLA_K_ASSEMBLE, 0.0, 0.0, [&] {
     hipLaunchKernelGGL(objective_terms_kernel, dim3((np_max + 255) / 256, B), dim3(256), 0, ctx.stream, dtd);
@@ -615,14 +635,15 @@ void launch_objective_terms(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, d
 void launch_kkt_residual(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int kp_max, double bytes) {
   if (B <= 0 || np_max <= 0) return;
   ctx.launch(INLA_K_SOLVE, 0.0, bytes, [&] {
-    hipLaunchKernelGGL(symv_lower_part_kernel, dim3(np_max / 64, B), dim3(256), 0, ctx.stream, dtd, 0);
+    hipLaunchKernelGGL(symv_lower_part_kernel, dim3(np_max / 64, (np_max / 64 + SYMV_TILES - 1) / SYMV_TILES, B), dim3(256), 0,
+                       ctx.stream, dtd, 0);
   });
   ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-    hipLaunchKernelGGL(kkt_residual_kernel, dim3((np_max + 255) / 256, B), dim3(256), 0, ctx.stream, dtd);
+    hipLaunchKernelGGL(kkt_residual_kernel, dim3(np_max / 64, B), dim3(1024), 0, ctx.stream, dtd);
   });
   if (kp_max > 0)
     ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-      hipLaunchKernelGGL(constraint_residual_kernel, dim3(kp_max / 4, B), dim3(256), 0, ctx.stream, dtd);
+      hipLaunchKernelGGL(constraint_residual_kernel, dim3(kp_max, B), dim3(256), 0, ctx.stream, dtd);
     });
 }
 

@@ -10,130 +10,11 @@
 
 namespace inla {
 
-// Solve L^T x = x in place for a lower-triangular L (column-major, order np, a
-// multiple of 64) in 64-row blocks from the bottom.  For each block: the 64
-// dot products with the already solved tail (coalesced column reads, 16 columns
-// per wave), then a 64-step substitution in wave 0 against the block staged in
-// LDS (D, 64 x 65 doubles).  Global writes to x are made visible to the other
-// waves of the workgroup by the barriers.
-template <typename T>
-__device__ void trsv_lt_block(const T *__restrict__ L, int ld, int np, double *x, double *sred, double (*D)[65]) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (int i0 = np - 64; i0 >= 0; i0 -= 64) {
-    double acc[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] = 0.0;
-    const T *Lc = L + (size_t)(i0 + 16 * w) * ld;
-    for (int j = i0 + 64 + lane; j < np; j += 64) {
-      const double xj = x[j];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[q] += (double)Lc[(size_t)q * ld + j] * xj;
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const double s = wave_sum(acc[q]);
-      if (lane == 0) sred[16 * w + q] = s;
-    }
-    for (int e = tid; e < 64 * 64; e += 256) {
-      const int r = e & 63, c = e >> 6;
-      D[r][c] = (double)L[(size_t)(i0 + c) * ld + i0 + r];
-    }
-    __syncthreads();
-    if (w == 0) {
-      double rhs = x[i0 + lane] - sred[lane];
-      double xm = 0.0;
-      for (int i = 63; i >= 0; --i) {
-        const double xi = __shfl(rhs, i, 64) / D[i][i];
-        if (lane == i) xm = xi;
-        if (lane < i) rhs -= D[i][lane] * xi;
-      }
-      x[i0 + lane] = xm;
-    }
-    __syncthreads();
-  }
-}
-
-// Solve L x = x in place (forward substitution), same blocking from the top.
-// The block's rows against the solved head: thread (row i, column phase p)
-// sums columns j = p, p+4, ... (each column read is 64 contiguous values).
-template <typename T>
-__device__ void trsv_l_block(const T *__restrict__ L, int ld, int np, double *x, double *sred4, double (*D)[65]) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  for (int i0 = 0; i0 < np; i0 += 64) {
-    double s = 0.0;
-#pragma unroll 8
-    for (int j = w; j < i0; j += 4) s += (double)L[(size_t)j * ld + i0 + lane] * x[j];
-    sred4[w * 64 + lane] = s;
-    for (int e = tid; e < 64 * 64; e += 256) {
-      const int r = e & 63, c = e >> 6;
-      D[r][c] = (double)L[(size_t)(i0 + c) * ld + i0 + r];
-    }
-    __syncthreads();
-    if (w == 0) {
-      double rhs = x[i0 + lane] - ((sred4[lane] + sred4[64 + lane]) + (sred4[128 + lane] + sred4[192 + lane]));
-      double xm = 0.0;
-      for (int c = 0; c < 64; ++c) {
-        const double xc = __shfl(rhs, c, 64) / D[c][c];
-        if (lane == c) xm = xc;
-        if (lane > c) rhs -= D[lane][c] * xc;
-      }
-      x[i0 + lane] = xm;
-    }
-    __syncthreads();
-  }
-}
-
 // Vector selectors for the step-wise triangular solves (V_* in model.hpp).
 __device__ __forceinline__ double *vsel(const ThetaDesc &t, int v) {
   return v == V_X ? t.x : v == V_R ? t.r : v == V_XN ? t.xn : v == V_Z ? t.z : t.u;
 }
 
-// y = M v or y = M^T v for a 64 x 64 block M stored column-major at Mg
-// (element (m, c) at Mg[c * 64 + m]).  block64_load reads the block into
-// registers, lane m of wave w holding row m of columns 16w .. 16w + 15 (each
-// load 64 contiguous elements of one column), so that the caller can issue it
-// ahead of other work; neither product stages the block in LDS, which keeps
-// the solve steps' LDS at a few KB.
-template <typename T>
-__device__ __forceinline__ void block64_load(const T *__restrict__ Mg, T (&e)[16]) {
-  const auto *g = gptr(Mg);
-  const int m = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) e[q] = g[(16 * w + q) * 64 + m];
-}
-
-// The lanes of a double moved by a DPP control (within rows of 16 lanes).
-template <int CTRL> __device__ __forceinline__ double dpp64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-  return __hiloint2double(hi, lo);
-}
-// Sum over each row of 16 lanes, in all of them (rotations by 8, 4, 2 and 1).
-__device__ __forceinline__ double row_sum16(double v) {
-  v += dpp64<0x128>(v);
-  v += dpp64<0x124>(v);
-  v += dpp64<0x122>(v);
-  v += dpp64<0x121>(v);
-  return v;
-}
-// Sums of a and b over lanes l and l ^ 32 (H = 32) or l ^ 16: a's in the rows of 16
-// lanes whose bit H is clear, b's in the others.
-template <int H> __device__ __forceinline__ double fold2(double a, double b) {
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  u2 lo, hi;
-  if (H == 32) {
-    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false));
-    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false));
-  } else {
-    lo = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false));
-    hi = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false));
-  }
-  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
-}
-// Sums of a[0..3] over the 64 lanes: lane l returns the total of a[l >> 4].
-__device__ __forceinline__ double wave_sum4(const double *a) {
-  return row_sum16(fold2<16>(fold2<32>(a[0], a[2]), fold2<32>(a[1], a[3])));
-}
 // v of lane l (a constant).
 __device__ __forceinline__ double lane_value(double v, int l) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
@@ -175,18 +56,24 @@ template <typename T, typename P> __device__ __forceinline__ void load4(T (&v)[4
   }
 }
 
+// A factor in lower triangular, column-major form and its stored inverses.
+template <typename T> struct TriMat {
+  const T *L, *X;
+  int ld;
+};
+
 // Forward solve of the diagonal block at row i0 (nsub sub-blocks of 64): z to the
 // global vector.  acc holds the wave's sums over earlier columns for the block's rows
 // 4 l .. 4 l + 3.  Loads run AHEAD sub-blocks ahead and have no conditions: sub-blocks
 // and rows are clamped to the block, and values above the diagonal are not used.
 template <typename T, typename P>
-__device__ __forceinline__ void solve_block_fwd(const ThetaDesc &t, int i0, int nsub, P r, double (&acc)[4], P z,
+__device__ __forceinline__ void solve_block_fwd(const TriMat<T> &t, int i0, int nsub, P r, double (&acc)[4], P z,
                                                 double *part) {
   constexpr int AHEAD = sizeof(T) == 4 ? 3 : 1;
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q4 = l >> 4;
-  const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 4 * w) * t.ldw + i0;
+  const auto *L = gptr(t.L) + (size_t)(i0 + 4 * w) * t.ld + i0;
   const unsigned lr = min(4 * l, 64 * nsub - 4);
-  const auto *X = gptr((const T *)t.linv) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
+  const auto *X = gptr(t.X) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
   double *p1 = part, *p2 = part + 16 * TSP;
   double rv[4];
   T e[4][4], lo[4][4][4];   // inverses: columns 4 w .. of row l; rows 4 l .. of the sub-block's columns 4 w ..
@@ -197,7 +84,7 @@ __device__ __forceinline__ void solve_block_fwd(const ThetaDesc &t, int i0, int 
     for (int q = 0; q < 4; ++q) e[b][q] = X[bc * 4096 + q * 64 + (unsigned)l];
     if (b < 3) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) load4(lo[b][q], L + (size_t)(64 * bc + q) * t.ldw + lr);
+      for (int q = 0; q < 4; ++q) load4(lo[b][q], L + (size_t)(64 * bc + q) * t.ld + lr);
     }
   };
 #pragma unroll
@@ -232,12 +119,12 @@ __device__ __forceinline__ void solve_block_fwd(const ThetaDesc &t, int i0, int 
 // Back solve x = L_bb^{-T} r of the same block: acc[s][q] holds this lane's part of
 // the sum over later rows for column 64 s + 4 w + q.
 template <typename T, typename P>
-__device__ __forceinline__ void solve_block_bwd(const ThetaDesc &t, int i0, int nsub, P r, double (&acc)[4][4], P x,
+__device__ __forceinline__ void solve_block_bwd(const TriMat<T> &t, int i0, int nsub, P r, double (&acc)[4][4], P x,
                                                 double *part) {
   constexpr int AHEAD = sizeof(T) == 4 ? 3 : 1;
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q4 = l >> 4;
-  const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 4 * w) * t.ldw + i0;
-  const auto *X = gptr((const T *)t.linv) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
+  const auto *L = gptr(t.L) + (size_t)(i0 + 4 * w) * t.ld + i0;
+  const auto *X = gptr(t.X) + (size_t)(i0 / 64) * 4096 + 4 * w * 64;
   double *sr = part, *sz = part + TSB;
   double rv[4];
   T e[4][4], lo[4][3][4];   // inverses: row l of columns 4 w ..; row l of columns 64 s + 4 w .. of the block row
@@ -249,7 +136,7 @@ __device__ __forceinline__ void solve_block_bwd(const ThetaDesc &t, int i0, int 
 #pragma unroll
     for (int s = 0; s < b; ++s)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) lo[b][s][q] = (L + (size_t)(64 * min(s, bc) + q) * t.ldw + 64 * bc)[(unsigned)l];
+      for (int q = 0; q < 4; ++q) lo[b][s][q] = (L + (size_t)(64 * min(s, bc) + q) * t.ld + 64 * bc)[(unsigned)l];
   };
 #pragma unroll
   for (int b = 3; b > 3 - AHEAD; --b) load(b);
@@ -280,10 +167,87 @@ __device__ __forceinline__ void solve_block_bwd(const ThetaDesc &t, int i0, int 
   }
 }
 
+// acc += this wave's part of L[j0 ..][i0 ..] z for rows j0 + 4 l .. (nn rows): its
+// columns are i0 + 16 w .., its lanes take four rows each in 16-byte loads.
+template <typename T, typename P>
+__device__ __forceinline__ void update_fwd(const TriMat<T> &t, int i0, int j0, int nn, P z, double (&acc)[4]) {
+  constexpr int U = sizeof(T) == 4 ? 16 : 8;   // loads in flight before the first product
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double zv = z[i0 + 16 * w + (l & 15)];
+  const auto *L = gptr(t.L) + (size_t)(i0 + 16 * w) * t.ld + j0;
+  const unsigned lr = min(4 * l, nn - 4);
+#pragma unroll
+  for (int c0 = 0; c0 < 16; c0 += U) {
+    T lv[U][4];
+#pragma unroll
+    for (int c = 0; c < U; ++c) load4(lv[c], L + (size_t)(c0 + c) * t.ld + lr);
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+      const double zc = lane_value(zv, c0 + c);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] += (double)lv[c][k] * zc;
+    }
+  }
+}
+
+// acc[s][q] += this lane's part (rows i0 + 4 l .., nb rows) of (L^T x)_c for the
+// columns c = j0 + 64 s + 4 w + q.
+template <typename T, typename P>
+__device__ __forceinline__ void update_bwd(const TriMat<T> &t, int i0, int j0, int nb, P x, double (&acc)[4][4]) {
+  constexpr int U = sizeof(T) == 4 ? 4 : 2;   // groups of four columns in flight
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned m = min(4 * l, nb - 4);
+  double xv[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) xv[k] = 4 * l < nb ? x[i0 + m + k] : 0.0;
+  const auto *L = gptr(t.L) + (size_t)(j0 + 4 * w) * t.ld + i0;
+#pragma unroll
+  for (int s0 = 0; s0 < 4; s0 += U) {
+    T lv[U][4][4];
+#pragma unroll
+    for (int s = 0; s < U; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) load4(lv[s][q], L + (size_t)(64 * (s0 + s) + q) * t.ld + m);
+#pragma unroll
+    for (int s = 0; s < U; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[s0 + s][q] += ((double)lv[s][q][0] * xv[0] + (double)lv[s][q][1] * xv[1]) +
+                          ((double)lv[s][q][2] * xv[2] + (double)lv[s][q][3] * xv[3]);
+    __builtin_amdgcn_sched_barrier(0);   // the next group's loads stay behind: registers
+  }
+}
+
+// x <- L^{-1} x and x <- L^{-T} x by one workgroup of 1024 threads, for the kriging
+// factor: the same blocks one after the other, x in global memory.
+template <typename T, typename P>
+__device__ __forceinline__ void solve_fwd_wg(const TriMat<T> &t, int np, P x, double *part) {
+  for (int j0 = 0; j0 < np; j0 += TSB) {
+    const int nn = min(TSB, np - j0);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = 0; i0 < j0; i0 += TSB) update_fwd<T>(t, i0, j0, nn, x, acc);
+    solve_block_fwd<T>(t, j0, nn / 64, x, acc, x, part);
+    __syncthreads();
+  }
+}
+template <typename T, typename P>
+__device__ __forceinline__ void solve_bwd_wg(const TriMat<T> &t, int np, P x, double *part) {
+  const int last = (np - 1) / TSB * TSB;
+  for (int j0 = last; j0 >= 0; j0 -= TSB) {
+    double acc[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[s][q] = 0.0;
+    for (int i0 = j0 + TSB; i0 < np; i0 += TSB) update_bwd<T>(t, i0, j0, min(TSB, np - i0), x, acc);
+    solve_block_bwd<T>(t, j0, min(TSB, np - j0) / 64, x, acc, x, part);
+    __syncthreads();
+  }
+}
+
 // One step of the forward solve L z = r (blocks from the top); i0 < 0: only the first
 // block's solve.  On entry the block's solution is in z.  The rows below are updated,
-// r_j -= sum_c L[j][i0 + c] z_c: wave w takes the columns 16 w .., its lanes four rows
-// each in 16-byte loads.
+// r_j -= sum_c L[j][i0 + c] z_c.
 template <typename T>
 __global__ __launch_bounds__(1024) void trsv_fwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
   const ThetaDesc t = td[blockIdx.y];
@@ -294,27 +258,11 @@ __global__ __launch_bounds__(1024) void trsv_fwd_step_kernel(const ThetaDesc *__
   __shared__ __align__(16) double part[(16 + 16) * TSP];
   auto *r = gptr(vsel(t, src));
   auto *z = gptr(vsel(t, dst));
+  const TriMat<T> f = {(const T *)t.W, (const T *)t.linv, t.ldw};
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  if (i0 >= 0) {
-    constexpr int U = sizeof(T) == 4 ? 16 : 8;   // loads in flight before the first product
-    const double zv = z[i0 + 16 * w + (l & 15)];
-    const auto *L = gptr((const T *)t.W) + (size_t)(i0 + 16 * w) * t.ldw + j0;
-    const unsigned lr = min(4 * l, nn - 4);
-#pragma unroll
-    for (int c0 = 0; c0 < 16; c0 += U) {
-      T lv[U][4];
-#pragma unroll
-      for (int c = 0; c < U; ++c) load4(lv[c], L + (size_t)(c0 + c) * t.ldw + lr);
-#pragma unroll
-      for (int c = 0; c < U; ++c) {
-        const double zc = lane_value(zv, c0 + c);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] += (double)lv[c][k] * zc;
-      }
-    }
-  }
+  if (i0 >= 0) update_fwd<T>(f, i0, j0, nn, z, acc);
   if (blockIdx.x == 0) {   // the next block
-    solve_block_fwd<T>(t, j0, nn / 64, r, acc, z, part);
+    solve_block_fwd<T>(f, j0, nn / 64, r, acc, z, part);
     return;
   }
 #pragma unroll
@@ -330,8 +278,7 @@ __global__ __launch_bounds__(1024) void trsv_fwd_step_kernel(const ThetaDesc *__
 
 // One step of the back solve L^T x = r (blocks from the bottom; block starts are
 // multiples of 256).  i0 is the step's block; the columns above are updated,
-// r_j -= sum_m L[i0 + m][j] x_m: wave w takes columns 64 s + 4 w + q of a workgroup's
-// 256 with its lanes on four contiguous rows each.  A matrix whose last block is the
+// r_j -= sum_m L[i0 + m][j] x_m.  A matrix whose last block is the
 // one above (i0 >= n_pad) starts with that block's solve.
 template <typename T>
 __global__ __launch_bounds__(1024) void trsv_bwd_step_kernel(const ThetaDesc *__restrict__ td, int i0, int src, int dst) {
@@ -343,36 +290,15 @@ __global__ __launch_bounds__(1024) void trsv_bwd_step_kernel(const ThetaDesc *__
   __shared__ double part[2 * TSB];
   auto *r = gptr(vsel(t, src));
   auto *x = gptr(vsel(t, dst));
+  const TriMat<T> f = {(const T *)t.W, (const T *)t.linv, t.ldw};
   double acc[4][4];
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int q = 0; q < 4; ++q) acc[s][q] = 0.0;
-  if (nb > 0) {
-    constexpr int U = sizeof(T) == 4 ? 4 : 2;   // groups of four columns in flight
-    const unsigned m = min(4 * l, nb - 4);
-    double xv[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) xv[k] = 4 * l < nb ? x[i0 + m + k] : 0.0;
-    const auto *L = gptr((const T *)t.W) + (size_t)(j0 + 4 * w) * t.ldw + i0;
-#pragma unroll
-    for (int s0 = 0; s0 < 4; s0 += U) {
-      T lv[U][4][4];
-#pragma unroll
-      for (int s = 0; s < U; ++s)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) load4(lv[s][q], L + (size_t)(64 * (s0 + s) + q) * t.ldw + m);
-#pragma unroll
-      for (int s = 0; s < U; ++s)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          acc[s0 + s][q] = ((double)lv[s][q][0] * xv[0] + (double)lv[s][q][1] * xv[1]) +
-                           ((double)lv[s][q][2] * xv[2] + (double)lv[s][q][3] * xv[3]);
-      __builtin_amdgcn_sched_barrier(0);   // the next group's loads stay behind: registers
-    }
-  }
+  if (nb > 0) update_bwd<T>(f, i0, j0, nb, x, acc);
   if (blockIdx.x == 0) {   // the block above
-    solve_block_bwd<T>(t, j0, nn / 64, r, acc, x, part);
+    solve_block_bwd<T>(f, j0, nn / 64, r, acc, x, part);
     return;
   }
 #pragma unroll
@@ -385,6 +311,25 @@ __global__ __launch_bounds__(1024) void trsv_bwd_step_kernel(const ThetaDesc *__
   }
 }
 
+// Maxima of three values over a workgroup of 1024 threads, valid in thread 0.
+__device__ __forceinline__ void block_max3(double &a, double &b, double &c, double (*sh)[16]) {
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  a = wave_max(a);
+  b = wave_max(b);
+  c = wave_max(c);
+  if (l == 0) {
+    sh[0][w] = a;
+    sh[1][w] = b;
+    sh[2][w] = c;
+  }
+  __syncthreads();
+  if (w == 0) {
+    a = wave_max(sh[0][l & 15]);
+    b = wave_max(sh[1][l & 15]);
+    c = wave_max(sh[2][l & 15]);
+  }
+}
+
 // A Newton step taken in correction form starts its new iterate at the current
 // one (xn <- x); one refinement step then adds the constrained correction.
 __global__ __launch_bounds__(256) void restart_kernel(const ThetaDesc *__restrict__ td) {
@@ -394,20 +339,20 @@ __global__ __launch_bounds__(256) void restart_kernel(const ThetaDesc *__restric
 }
 
 // Accept the refined iterate: Newton stopping quantities and x <- xn.
-__global__ __launch_bounds__(256) void newton_accept_kernel(const ThetaDesc *__restrict__ td) {
+__global__ __launch_bounds__(1024) void newton_accept_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.x];
-  __shared__ double sh[4];
+  __shared__ double sh[3][16];
   double st = 0.0, sc = 0.0, bad = 0.0;
-  for (int i = threadIdx.x; i < t.n; i += 256) {
+#pragma unroll 4
+  for (int i = threadIdx.x; i < t.n; i += 1024) {
     const double xn = t.xn[i], xo = t.x[i];
     if (!isfinite(xn)) bad = 1.0;
     st = fmax(st, fabs(xn - xo));
     sc = fmax(sc, fabs(xn));
   }
-  st = block_max256(st, sh);
-  sc = block_max256(sc, sh);
-  bad = block_sum256(bad, sh);
-  for (int i = threadIdx.x; i < t.n_pad; i += 256) t.x[i] = i < t.n ? t.xn[i] : 0.0;
+  block_max3(st, sc, bad, sh);
+#pragma unroll 4
+  for (int i = threadIdx.x; i < t.n_pad; i += 1024) t.x[i] = i < t.n ? t.xn[i] : 0.0;
   if (threadIdx.x == 0) {
     t.dres[DRES_STEP] = st;
     t.dres[DRES_SCALE] = fmax(1.0, sc);
@@ -417,15 +362,16 @@ __global__ __launch_bounds__(256) void newton_accept_kernel(const ThetaDesc *__r
 
 // Kriging solve after the small (FP64) factorisation: w from the border row,
 // then lambda = L_S^{-T} w; also log|S| = 2 sum log (L_S)_ii, ||w||^2 and the
-// numerical-rank flag.
-__global__ __launch_bounds__(256) void kriging_solve_kernel(const ThetaDesc *__restrict__ td) {
+// numerical-rank flag.  Latency-bound; the diagonal blocks' stored inverses and 16
+// waves in place of a 64-step substitution by one: 86 to 13 us at
+// k_pad = 128, 39 to 10 us at smaller borders (the residual's two solves 60 to 13 us).
+__global__ __launch_bounds__(1024) void kriging_solve_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.x];
-  __shared__ double sred[64];
-  __shared__ double sh[4];
-  __shared__ double D[64][65];
-  const int kp = t.k_pad, k = t.k;
+  __shared__ double sh[4][16];
+  __shared__ __align__(16) double part[2 * 16 * TSP];
+  const int kp = t.k_pad, k = t.k, tid = threadIdx.x;
   double lds_ = 0.0, w2 = 0.0, dmin = INFINITY, dmax = 0.0;
-  for (int i = threadIdx.x; i < kp; i += 256) {
+  for (int i = tid; i < kp; i += 1024) {
     const double wv = i < k ? t.S[(size_t)i * t.lds + kp] : 0.0;
     t.lam[i] = wv;
     w2 += wv * wv;
@@ -436,83 +382,124 @@ __global__ __launch_bounds__(256) void kriging_solve_kernel(const ThetaDesc *__r
       dmax = fmax(dmax, d * d);
     }
   }
-  lds_ = block_sum256(lds_, sh);
-  w2 = block_sum256(w2, sh);
-  dmin = -block_max256(-dmin, sh);
-  dmax = block_max256(dmax, sh);
-  trsv_lt_block<double>(t.S, t.lds, kp, t.lam, sred, D);
-  if (threadIdx.x == 0) {
+  lds_ = wave_sum(lds_);
+  w2 = wave_sum(w2);
+  dmin = -wave_max(-dmin);
+  dmax = wave_max(dmax);
+  if ((tid & 63) == 0) {
+    sh[0][tid >> 6] = lds_;
+    sh[1][tid >> 6] = w2;
+    sh[2][tid >> 6] = dmin;
+    sh[3][tid >> 6] = dmax;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    lds_ = w2 = 0.0;
+    for (int i = 0; i < 16; ++i) {
+      lds_ += sh[0][i];
+      w2 += sh[1][i];
+      dmin = fmin(dmin, sh[2][i]);
+      dmax = fmax(dmax, sh[3][i]);
+    }
     t.dres[DRES_LOGDET_S] = 2.0 * lds_;
     t.dres[DRES_WNORM2] = w2;
     // squared pivot below 1e-13 of the largest: numerically dependent constraints
     t.dres[DRES_RANK] = (k > 0 && !(dmin >= 1e-13 * dmax)) ? 1.0 : 0.0;
   }
+  if (kp > 0) solve_bwd_wg<double>({t.S, t.linv_s, t.lds}, kp, gptr(t.lam), part);
 }
 
 // r_c = z_c - sum_a lambda_a (G L^{-T})_{a,c}.  Newton (from_z = 0): z is the
 // factored b row and lambda the kriging multipliers, giving the corrected
 // right-hand side of x = L^{-T}(L^{-1} b - L^{-1} C^T lambda).  Refinement
-// (from_z = 1): u = L^{-1} r1 and lambda = dlambda.
+// (from_z = 1): u = L^{-1} r1 and lambda = dlambda.  A wave takes four columns, all
+// of their loads in flight together: nine of order 3000, 32 to 8 us.
 template <typename T>
 __global__ __launch_bounds__(256) void rhs_kernel(const ThetaDesc *__restrict__ td, int from_z) {
   const ThetaDesc t = td[blockIdx.y];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c0 = blockIdx.x * 64 + w * 16;
+  const int l = threadIdx.x & 63, c0 = blockIdx.x * 16 + (threadIdx.x >> 6) * 4;
   if (c0 >= t.n_pad) return;
   const int k = t.k, np = t.n_pad;
-  const double *lam = from_z ? t.dlam : t.lam;
-  for (int q = 0; q < 16; ++q) {
-    const int c = c0 + q;
-    const T *col = (const T *)t.W + (size_t)c * t.ldw + np;
-    double s = 0.0;
-    for (int a = lane; a < k; a += 64) s += lam[a] * (double)col[a];
-    s = wave_sum(s);
-    if (lane == 0) t.r[c] = (from_z ? t.u[c] : (double)col[k]) - s;
+  const auto *lam = gptr((const double *)(from_z ? t.dlam : t.lam));
+  const auto *W = gptr((const T *)t.W) + (size_t)c0 * t.ldw + np;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int a = l; a < k; a += 64) {
+    const double la = lam[a];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] += la * (double)W[(size_t)q * t.ldw + a];
   }
+  const int c = c0 + (l >> 4);
+  const double v = from_z ? t.u[c] : (double)W[(size_t)(l >> 4) * t.ldw + k];
+  const double dot = wave_sum4(s);
+  if ((l & 15) == 0) t.r[c] = v - dot;
 }
 
-// Refinement, constrained part 1: t = (L^{-1} C^T)^T u - r2 = C Q~^{-1} r1 - r2 with
-// u = L^{-1} r1, into dlam.  A workgroup per 64 border rows; the four waves split
-// the columns, each column read is 64 contiguous border values.
+// Refinement, constrained part 1: partial sums of (L^{-1} C^T)^T u, u = L^{-1} r1,
+// into t.symv (whose residual sums have been used): a workgroup takes 64 border rows
+// and 256 columns (BG_COLS), each column read 64 contiguous border values; splits
+// because the border's few row blocks alone would leave the chip idle, each a serial
+// walk over every column: a batch of order 8192, 164 to 33 us.
+constexpr int BG_COLS = 256;
 template <typename T>
 __global__ __launch_bounds__(256) void border_gemv_kernel(const ThetaDesc *__restrict__ td) {
-  const ThetaDesc t = td[blockIdx.y];
-  const int a = blockIdx.x * 64 + (threadIdx.x & 63), w = threadIdx.x >> 6;
+  const ThetaDesc t = td[blockIdx.z];
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int a = blockIdx.x * 64 + l, c0 = blockIdx.y * BG_COLS + 64 * w, np = t.n_pad;
   __shared__ double part[4][64];
-  if ((int)blockIdx.x * 64 >= t.k_pad) return;
-  const int np = t.n_pad;
+  if ((int)blockIdx.x * 64 >= t.k_pad || (int)blockIdx.y * BG_COLS >= np) return;
   double s = 0.0;
-  if (a < t.k) {
-    const T *row = (const T *)t.W + np + a;
-#pragma unroll 8
-    for (int c = w; c < np; c += 4) s += (double)row[(size_t)c * t.ldw] * t.u[c];
+  if (c0 < np) {
+    const auto *row = gptr((const T *)t.W) + (size_t)c0 * t.ldw + np;
+    const double uv = gptr((const double *)t.u)[c0 + l];
+#pragma unroll
+    for (int c1 = 0; c1 < 64; c1 += 16) {
+      T v[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) v[c] = (row + (size_t)(c1 + c) * t.ldw)[(unsigned)min(a, t.k - 1)];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) s += (double)v[c] * lane_value(uv, c1 + c);
+    }
   }
-  part[w][threadIdx.x & 63] = s;
+  part[w][l] = s;
   __syncthreads();
-  if (w == 0) {
-    const int l = threadIdx.x;
-    t.dlam[a] = a < t.k ? ((part[0][l] + part[1][l]) + (part[2][l] + part[3][l])) - t.rtwo[a] : 0.0;
-  }
+  if (w == 0) t.symv[(size_t)blockIdx.y * t.k_pad + a] = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
 }
 
-// Refinement, constrained part 2: dlambda = S~^{-1} t with the FP64 kriging factor.
-__global__ __launch_bounds__(256) void kriging_correct_kernel(const ThetaDesc *__restrict__ td) {
+// Refinement, constrained part 2: t = C Q~^{-1} r1 - r2 from the partial sums, then
+// dlambda = S~^{-1} t with the FP64 kriging factor.
+__global__ __launch_bounds__(1024) void kriging_correct_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.x];
-  __shared__ double sred4[256];
-  __shared__ double D[64][65];
-  if (t.k_pad > 0) {
-    trsv_l_block<double>(t.S, t.lds, t.k_pad, t.dlam, sred4, D);
-    trsv_lt_block<double>(t.S, t.lds, t.k_pad, t.dlam, sred4, D);
+  __shared__ __align__(16) double part[2 * 16 * TSP];
+  const int kp = t.k_pad, tid = threadIdx.x, l = tid & 255, p = tid >> 8;
+  const int ns = (t.n_pad + BG_COLS - 1) / BG_COLS;
+  if (kp == 0) return;
+  for (int a0 = 0; a0 < kp; a0 += 256) {   // thread (row, quarter of the splits)
+    const int a = a0 + l;
+    double s = 0.0;
+    if (a < t.k) {
+#pragma unroll 8
+      for (int j = p; j < ns; j += 4) s += t.symv[(size_t)j * kp + a];
+    }
+    part[p * 256 + l] = s;
+    __syncthreads();
+    if (p == 0 && a < kp)
+      t.dlam[a] = a < t.k ? ((part[l] + part[256 + l]) + (part[512 + l] + part[768 + l])) - t.rtwo[a] : 0.0;
+    __syncthreads();
   }
+  const TriMat<double> f = {t.S, t.linv_s, t.lds};
+  solve_fwd_wg<double>(f, kp, gptr(t.dlam), part);
+  solve_bwd_wg<double>(f, kp, gptr(t.dlam), part);
 }
 
 // Refinement, update: xn += dx (dx in u), lambda += dlambda, and the
 // quantities of the refinement stopping test.
-__global__ __launch_bounds__(256) void ir_update_kernel(const ThetaDesc *__restrict__ td) {
+__global__ __launch_bounds__(1024) void ir_update_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.x];
-  __shared__ double sh[4];
+  __shared__ double sh[3][16];
   double dm = 0.0, xm = 0.0, bad = 0.0;
-  for (int i = threadIdx.x; i < t.n_pad; i += 256) {
+#pragma unroll 4
+  for (int i = threadIdx.x; i < t.n_pad; i += 1024) {
     double v = 0.0;
     if (i < t.n) {
       const double dx = t.u[i];
@@ -523,10 +510,8 @@ __global__ __launch_bounds__(256) void ir_update_kernel(const ThetaDesc *__restr
     }
     t.xn[i] = v;
   }
-  for (int a = threadIdx.x; a < t.k; a += 256) t.lam[a] += t.dlam[a];
-  dm = block_max256(dm, sh);
-  xm = block_max256(xm, sh);
-  bad = block_sum256(bad, sh);
+  for (int a = threadIdx.x; a < t.k; a += 1024) t.lam[a] += t.dlam[a];
+  block_max3(dm, xm, bad, sh);
   if (threadIdx.x == 0) {
     t.dres[DRES_IR_DX] = bad > 0.0 ? INFINITY : dm;
     t.dres[DRES_IR_X] = fmax(1.0, xm);
@@ -645,12 +630,12 @@ int copy_vectors(Ctx &ctx, const std::vector<VecCopy> &v) {
 
 void launch_kriging_solve(Ctx &ctx, const ThetaDesc *dtd, int B) {
   if (B <= 0) return;
-  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(kriging_solve_kernel, dim3(B), dim3(256), 0, ctx.stream, dtd); });
+  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(kriging_solve_kernel, dim3(B), dim3(1024), 0, ctx.stream, dtd); });
 }
 void launch_rhs(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int from_z, int prec) {
   if (B <= 0 || np_max <= 0) return;
   ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-    INLA_DISPATCH_T(prec, rhs_kernel, dim3((np_max + 63) / 64, B), dim3(256), 0, ctx.stream, dtd, from_z);
+    INLA_DISPATCH_T(prec, rhs_kernel, dim3((np_max + 15) / 16, B), dim3(256), 0, ctx.stream, dtd, from_z);
   });
 }
 void launch_trsv_fwd(Ctx &ctx, const std::vector<ThetaDesc> &htd, int np_max, int src, int dst, double bytes,
@@ -694,19 +679,19 @@ void launch_restart(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max) {
 }
 void launch_newton_accept(Ctx &ctx, const ThetaDesc *dtd, int B) {
   if (B <= 0) return;
-  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(newton_accept_kernel, dim3(B), dim3(256), 0, ctx.stream, dtd); });
+  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(newton_accept_kernel, dim3(B), dim3(1024), 0, ctx.stream, dtd); });
 }
-void launch_ir_correct(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max, int prec) {
+void launch_ir_correct(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int kp_max, int prec) {
   if (B <= 0) return;
   if (kp_max > 0)
     ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-      INLA_DISPATCH_T(prec, border_gemv_kernel, dim3(kp_max / 64, B), dim3(256), 0, ctx.stream, dtd);
+      INLA_DISPATCH_T(prec, border_gemv_kernel, dim3(kp_max / 64, (np_max + BG_COLS - 1) / BG_COLS, B), dim3(256), 0, ctx.stream, dtd);
     });
-  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(kriging_correct_kernel, dim3(B), dim3(256), 0, ctx.stream, dtd); });
+  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(kriging_correct_kernel, dim3(B), dim3(1024), 0, ctx.stream, dtd); });
 }
 void launch_ir_update(Ctx &ctx, const ThetaDesc *dtd, int B) {
   if (B <= 0) return;
-  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(ir_update_kernel, dim3(B), dim3(256), 0, ctx.stream, dtd); });
+  ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] { hipLaunchKernelGGL(ir_update_kernel, dim3(B), dim3(1024), 0, ctx.stream, dtd); });
 }
 void launch_finish(Ctx &ctx, const ThetaDesc *dtd, int B, int prec) {
   if (B <= 0) return;

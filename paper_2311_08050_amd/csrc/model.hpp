@@ -47,7 +47,7 @@ void launch_trsv_fwd(Ctx &ctx, const std::vector<ThetaDesc> &htd, int np_max, in
 void launch_trsv_bwd(Ctx &ctx, const std::vector<ThetaDesc> &htd, int np_max, int src, int dst, double bytes, int prec);
 void launch_restart(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max);
 void launch_newton_accept(Ctx &ctx, const ThetaDesc *dtd, int B);
-void launch_ir_correct(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max, int prec);
+void launch_ir_correct(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int kp_max, int prec);
 void launch_ir_update(Ctx &ctx, const ThetaDesc *dtd, int B);
 void launch_finish(Ctx &ctx, const ThetaDesc *dtd, int B, int prec);
 void launch_copy_in(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max, int prec);
