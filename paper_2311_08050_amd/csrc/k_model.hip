@@ -300,92 +300,126 @@ __global__ __launch_bounds__(256) void obs_kernel(const ThetaDesc *__restrict__ 
 // Schur-block columns start at zero.  `with_lik` = 0 gives the prior pass
 // (W = 0, b = 0).  Per-column partial sums of log pi(y|eta) and x^T Q_prior x go
 // to t.part for a fixed-order reduction.
+//
+// HBM-bound.  A workgroup takes ASM_C columns, a thread two rows of them in 16-byte
+// loads: with one column per workgroup most of its life went to the descriptor and
+// the likelihood.  Nine of order 3000: 178 to 146 us, the 25 of order 1024 in FP32 52
+// to 26, with an identity border 940 to 260 us; at order 8192 and above one column
+// is as good (980 to 967 us for eight in FP64, two of 16384 in FP32 464 to 500).
+// Two and eight columns: 147 and 160 us at 3000.
+constexpr int ASM_C = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void assemble_kernel(const ThetaDesc *__restrict__ td, int with_lik, int want_xqx,
                                                        int border) {
   const ThetaDesc t = td[blockIdx.y];
-  const int c = blockIdx.x;
-  const int N = t.Nw;
-  if (c >= t.Ncw) return;
-  T *col = (T *)t.W + (size_t)c * t.ldw;
+  const int c0 = blockIdx.x * ASM_C, N = t.Nw, tid = threadIdx.x;
+  if (c0 >= t.Ncw) return;
+  auto *col = gptr((T *)t.W) + (size_t)c0 * t.ldw;
   const int np = t.n_pad, n = t.n, k = t.k;
-  __shared__ double sh[4];
-  if (c >= np) {
-    for (int r = c + threadIdx.x; r < N; r += 256) col[r] = (T)0;
+  if (c0 >= np) {
+    for (int r = c0 + tid; r < N; r += 256)
+#pragma unroll
+      for (int q = 0; q < ASM_C; ++q)
+        if (r >= c0 + q) col[(size_t)q * t.ldw + r] = (T)0;
     return;
   }
-  double g = 0.0, W = 0.0, ll = 0.0, xc = 0.0, bc = 0.0;
-  if (c < n) {
-    xc = t.x[c];
-    if (with_lik && t.m == 0) lik_point(t, c, xc, g, W, ll);
-  }
-  if (with_lik && t.m == 0) {
-    bc = g + W * xc;
-  } else if (with_lik && c < n) {
-    // b_c = (A^T (g + W A x))_c over the CSC column, fixed-order block sum
-    double s = 0.0;
-    for (int p = t.cscp[c] + threadIdx.x; p < t.cscp[c + 1]; p += 256) {
-      const int i = t.csci[p];
-      s += t.cscv[p] * (t.obs_g[i] + t.obs_W[i] * t.obs_ax[i]);
+  __shared__ double sh[4], sW[ASM_C], sb[ASM_C], sx[4][ASM_C];
+  if (tid < ASM_C) {
+    const int c = c0 + tid;
+    double g = 0.0, W = 0.0, ll = 0.0, xc = 0.0;
+    if (c < n) {
+      xc = t.x[c];
+      if (with_lik && t.m == 0) lik_point(t, c, xc, g, W, ll);
     }
-    bc = block_sum256(s, sh);
+    sW[tid] = W;
+    sb[tid] = with_lik && t.m == 0 ? g + W * xc : 0.0;
+    t.part[c] = ll;
   }
-  const double *q = t.Qp + (size_t)c * t.ldqp;
-  const int kc_pad = round_up_dev(k, PADN);
-  double xq = 0.0;
-  // Four rows per thread and pass, their loads issued before any store (the
-  // stores to the working matrix may alias the prior for the compiler, which
-  // would otherwise keep one load in flight per thread).  Each thread still
-  // visits its rows in increasing order, so the x^T Q x partial sums keep
-  // their order.
-  constexpr int U = 4;
-  for (int rb = c + threadIdx.x; rb < N; rb += 256 * U) {
-    double qv[U], xr[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = rb + 256 * u;
-      qv[u] = r < np ? q[r] : 0.0;
-      xr[u] = (want_xqx && r < n) ? t.x[r] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = rb + 256 * u;
-      if (r >= N) break;
-      double v;
-      if (r < np) {
-        v = qv[u] + (r == c ? W : 0.0);
-        if (want_xqx && r < n) xq += (r == c ? 1.0 : 2.0) * qv[u] * xr[u];
-      } else {
-        const int a = r - np;
-        if (a < k) v = (c < n) ? t.C[(size_t)a * n + c] : 0.0;
-        else if (border == BORDER_CB) v = (a == k) ? bc : 0.0;
-        else v = (a - kc_pad == c) ? 1.0 : 0.0;
+  if (with_lik && t.m > 0) {
+    // b_c = (A^T (g + W A x))_c over the CSC columns, fixed-order block sums
+    for (int q = 0; q < ASM_C && c0 + q < n; ++q) {
+      double s = 0.0;
+      for (int p = t.cscp[c0 + q] + tid; p < t.cscp[c0 + q + 1]; p += 256) {
+        const int i = t.csci[p];
+        s += t.cscv[p] * (t.obs_g[i] + t.obs_W[i] * t.obs_ax[i]);
       }
-      col[r] = (T)v;
+      s = block_sum256(s, sh);
+      if (tid == 0) sb[q] = s;
     }
+  }
+  __syncthreads();
+  const auto *Q = gptr((const double *)t.Qp) + (size_t)c0 * t.ldqp;
+  const auto *C = gptr(t.C) + c0;
+  const int kc_pad = round_up_dev(k, PADN);
+  double xq[ASM_C];
+#pragma unroll
+  for (int q = 0; q < ASM_C; ++q) xq[q] = 0.0;
+  typedef T t2 __attribute__((ext_vector_type(2)));
+  typedef __attribute__((address_space(1))) t2 gt2;
+#pragma unroll 2
+  for (int r = c0 + 2 * tid; r < np; r += 512) {
+    d2 v[ASM_C];
+#pragma unroll
+    for (int q = 0; q < ASM_C; ++q) v[q] = *(gcd2 *)(Q + (size_t)q * t.ldqp + r);
+    if (want_xqx) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (r + h >= n) break;
+        const double xr = t.x[r + h];
+#pragma unroll
+        for (int q = 0; q < ASM_C; ++q)
+          if (r + h >= c0 + q) xq[q] += (r + h == c0 + q ? 1.0 : 2.0) * v[q][h] * xr;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < ASM_C; ++q) {
+      auto *p = col + (size_t)q * t.ldw + r;
+      if (r == c0 + q) v[q][0] += sW[q];
+      if (r + 1 == c0 + q) v[q][1] += sW[q];
+      if (r >= c0 + q) *(gt2 *)p = t2{(T)v[q][0], (T)v[q][1]};
+      else if (r + 1 == c0 + q) p[1] = (T)v[q][1];
+    }
+  }
+  for (int r = np + tid; r < N; r += 256) {
+    const int a = r - np;
+    double v[ASM_C];
+#pragma unroll
+    for (int q = 0; q < ASM_C; ++q) {
+      if (a < k) v[q] = c0 + q < n ? C[(size_t)a * n + q] : 0.0;
+      else if (border == BORDER_CB) v[q] = a == k ? sb[q] : 0.0;
+      else v[q] = a - kc_pad == c0 + q ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < ASM_C; ++q) col[(size_t)q * t.ldw + r] = (T)v[q];
   }
   if (want_xqx) {
-    xq = block_sum256(xq, sh);
-    if (threadIdx.x == 0) t.part[t.ldw + c] = xq * xc;
+#pragma unroll
+    for (int q = 0; q < ASM_C; ++q) {
+      const double d = wave_sum(xq[q]);
+      if ((tid & 63) == 0) sx[tid >> 6][q] = d;
+    }
+    __syncthreads();
+    if (tid < ASM_C) {
+      const int c = c0 + tid;
+      t.part[t.ldw + c] = c < n ? ((sx[0][tid] + sx[1][tid]) + (sx[2][tid] + sx[3][tid])) * t.x[c] : 0.0;
+    }
   }
-  if (with_lik && t.m > 0 && c < n) {
-    // + (A^T W A)_{r c} for the lower pattern entries of column c (distinct rows)
+  if (with_lik && t.m > 0) {
+    // + (A^T W A)_{r c} for the lower pattern entries of the columns (distinct rows)
     __syncthreads();
     double bad = 0.0;
-    for (int e = t.patp[c] + threadIdx.x; e < t.patp[c + 1]; e += 256) {
-      double v = 0.0;
-      for (int q = t.patt[e]; q < t.patt[e + 1]; ++q) v += t.tcoef[q] * t.obs_W[t.tobs[q]];
-      if (!isfinite(v)) bad = 1.0;
-      const int r = t.patr[e];
-      col[r] = (T)((double)col[r] + v);
-    }
+    for (int q = 0; q < ASM_C && c0 + q < n; ++q)
+      for (int e = t.patp[c0 + q] + tid; e < t.patp[c0 + q + 1]; e += 256) {
+        double v = 0.0;
+        for (int p = t.patt[e]; p < t.patt[e + 1]; ++p) v += t.tcoef[p] * t.obs_W[t.tobs[p]];
+        if (!isfinite(v)) bad = 1.0;
+        auto *m = col + (size_t)q * t.ldw + t.patr[e];
+        *m = (T)((double)*m + v);
+      }
     bad = block_sum256(bad, sh);
-    if (threadIdx.x == 0 && bad > 0.0) t.dres[DRES_NONFINITE] = 1.0;
+    if (tid == 0 && bad > 0.0) t.dres[DRES_NONFINITE] = 1.0;
   }
-  if (threadIdx.x == 0) {
-    t.part[c] = ll;
-    if (!isfinite(W) || !isfinite(bc)) t.dres[DRES_NONFINITE] = 1.0;
-  }
+  if (tid < ASM_C && (!isfinite(sW[tid]) || !isfinite(sb[tid]))) t.dres[DRES_NONFINITE] = 1.0;
 }
 
 // Kriging system from the Schur block -[[S, C x_u], [., b^T x_u]] of the big
@@ -424,7 +458,7 @@ __global__ __launch_bounds__(256) void kriging_build_kernel(const ThetaDesc *__r
 // A lane keeps one row of 16 columns, so both products come from the registers that
 // were loaded, and only their sums cross lanes, once per workgroup.  HBM-bound; four
 // tiles, since one workgroup per block column leaves the longest to run alone: at
-// n = 16384 724 to 279 us (3.9 TB/s), six matrices of 1024 44 to 16 us.
+// order 16384, two, 724 to 279 us (7.7 TB/s); 25 of 1024 44 to 16 us.
 // src 0: v = xn (refinement residuals); 1: v = x (objective terms).
 constexpr int SYMV_TILES = 4;
 __device__ __forceinline__ int symv_splits(int np, int J) { return (np / 64 - J + SYMV_TILES - 1) / SYMV_TILES; }
@@ -488,7 +522,7 @@ __device__ __forceinline__ double symv_row(const ThetaDesc &t, int i) {
 // with g, W at the linearisation point x and Q_prior xn from the lower-triangle
 // partial sums, the result to t.z.  A workgroup takes 64 rows, its 16 waves a 16th of
 // the partial sums and of the constraints each: one thread per row walks both alone,
-// which at n = 16384 is 64 workgroups, 193 us (now 17).
+// which for two of n = 16384 is 128 workgroups and 193 us (now 17).
 __global__ __launch_bounds__(1024) void kkt_residual_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.y];
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6, np = t.n_pad;
@@ -606,10 +640,10 @@ void launch_assemble(Ctx &ctx, const ThetaDesc *dtd, int B, int N_max, int with_
     });
   ctx.launch(INLA_K_ASSEMBLE, 0.0, bytes, [&] {
     if (prec != INLA_PREC_FP64)
-      hipLaunchKernelGGL(assemble_kernel<float>, dim3(N_max, B), dim3(256), 0, ctx.stream, dtd, with_lik, want_xqx,
+      hipLaunchKernelGGL(assemble_kernel<float>, dim3(N_max / ASM_C, B), dim3(256), 0, ctx.stream, dtd, with_lik, want_xqx,
                          border);
     else
-      hipLaunchKernelGGL(assemble_kernel<double>, dim3(N_max, B), dim3(256), 0, ctx.stream, dtd, with_lik, want_xqx,
+      hipLaunchKernelGGL(assemble_kernel<double>, dim3(N_max / ASM_C, B), dim3(256), 0, ctx.stream, dtd, with_lik, want_xqx,
                          border);
   });
 }

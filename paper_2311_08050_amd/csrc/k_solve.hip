@@ -37,7 +37,7 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // that each would occupy the LDS for a whole wave.  A wave's share of the products
 // with the rows (columns) still to be solved stays in its registers until their
 // turn comes.  A step of 256 in FP32: 13.3 us forward, 11.9 us backward at order
-// 16384, 10.4 and 8.9 us at 1024 with six matrices (steps of 64: 4.2 us each and
+// 16384, 10.4 and 8.9 us at 1024 with 25 matrices (steps of 64: 4.2 us each and
 // 1.5 us between launches); FP64 backward, nine of 3000: 19.5 us (6.1 us and the gap).
 // --------------------------------------------------------------------------
 constexpr int TSB = 256;
@@ -593,20 +593,33 @@ __global__ __launch_bounds__(256) void var_small_build_kernel(const ThetaDesc *_
 }
 
 // var_i = ||row i of L^{-T}||^2 - ||row i of V L_S^{-T}||^2 (i < n), written to t.out.
-__global__ __launch_bounds__(256) void var_norms_kernel(const ThetaDesc *__restrict__ td) {
+// A workgroup takes 64 rows, coalesced, its 16 waves share the columns; L^{-T} is
+// upper triangular, so its rows start at their own 64-wide block column.  One thread
+// per row over all columns was a serial walk by n / 256 workgroups: nine of
+// order 3000, 1265 to 89 us.
+__global__ __launch_bounds__(1024) void var_norms_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.y];
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= t.n) return;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6, i0 = blockIdx.x * 64, i = i0 + l;
+  __shared__ double part[2][16][64];
+  if (i0 >= t.n) return;
   const int np = t.n_pad, kp = t.k_pad;
-  const double *row = (const double *)t.W + np + kp + i;
-  double s = 0.0;
-  for (int c = 0; c < np; ++c) { const double v = row[(size_t)c * t.ldw]; s += v * v; }
-  double s2 = 0.0;
+  const auto *row = gptr((const double *)t.W) + np + kp + i;
+  double s = 0.0, s2 = 0.0;
+#pragma unroll 8
+  for (int c = i0 + w; c < np; c += 16) { const double v = row[(size_t)c * t.ldw]; s += v * v; }
   if (t.k > 0) {
-    const double *row2 = t.S + kp + i;
-    for (int c = 0; c < t.k; ++c) { const double v = row2[(size_t)c * t.lds]; s2 += v * v; }
+    const auto *row2 = gptr((const double *)t.S) + kp + i;
+#pragma unroll 4
+    for (int c = w; c < t.k; c += 16) { const double v = row2[(size_t)c * t.lds]; s2 += v * v; }
   }
-  t.out[i] = s - s2;
+  part[0][w][l] = s;
+  part[1][w][l] = s2;
+  __syncthreads();
+  if (w != 0 || i >= t.n) return;
+  double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 16; ++q) c[q & 1] += part[0][q][l], c[2 + (q & 1)] += part[1][q][l];
+  t.out[i] = (c[0] + c[1]) - (c[2] + c[3]);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -720,7 +733,7 @@ void launch_var_small_build(Ctx &ctx, const ThetaDesc *dtd, int B, int kp_max) {
 void launch_var_norms(Ctx &ctx, const ThetaDesc *dtd, int B, int np_max) {
   if (B <= 0 || np_max <= 0) return;
   ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-    hipLaunchKernelGGL(var_norms_kernel, dim3((np_max + 255) / 256, B), dim3(256), 0, ctx.stream, dtd);
+    hipLaunchKernelGGL(var_norms_kernel, dim3((np_max + 63) / 64, B), dim3(1024), 0, ctx.stream, dtd);
   });
 }
 

@@ -794,21 +794,35 @@ __global__ __launch_bounds__(256) void wb_lik_kernel(const WbDesc *__restrict__ 
 }
 
 // Partial products of Pq v over WB_CH column chunks (v = src, or sw * src).
-// Grid (n_pad / 256, WB_CH, B); the row reads of each column are coalesced.
+// Grid (n_pad / 256, WB_CH, B); the row reads of each column are coalesced, 16
+// columns in flight: the vector comes from LDS, so that its loads don't stand
+// between the matrix's: nine of order 3000 150 to 104 us (6.2 TB/s, one shared Pq).
 __global__ __launch_bounds__(256) void wb_symv_part_kernel(const WbDesc *__restrict__ wd, int src, int scaled) {
   const WbDesc D = wd[blockIdx.z];
   const int i = blockIdx.x * 256 + threadIdx.x;
   if ((int)blockIdx.x * 256 >= D.n_pad) return;
+  __shared__ double vs[256];
   const int cs = (D.n + WB_CH - 1) / WB_CH;
   const int j0 = blockIdx.y * cs, j1 = min(D.n, j0 + cs);
-  const double *v = wb_vec(D, src);
-  double acc = 0.0;
-  if (i < D.n) {
-    const auto *col = gptr(D.Pq) + i;
-#pragma unroll 8
-    for (int j = j0; j < j1; ++j) acc = fma(col[(size_t)j * D.ldq], scaled ? D.sw[j] * v[j] : v[j], acc);
+  const auto *v = gptr((const double *)wb_vec(D, src)), *sw = gptr((const double *)D.sw);
+  const auto *row = gptr(D.Pq) + min(i, D.n - 1);
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int jb = j0; jb < j1; jb += 256) {
+    const int m = min(256, j1 - jb), j = jb + min((int)threadIdx.x, m - 1);
+    __syncthreads();
+    vs[threadIdx.x] = (int)threadIdx.x < m ? (scaled ? sw[j] * v[j] : v[j]) : 0.0;
+    __syncthreads();
+    for (int q0 = 0; q0 < m; q0 += 16) {
+      double x[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) x[q] = row[(size_t)(jb + min(q0 + q, m - 1)) * D.ldq];
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+        if (q0 + q < m) acc[q & 3] = fma(x[q], vs[q0 + q], acc[q & 3]);
+    }
   }
-  if (i < D.n_pad) D.part[(size_t)blockIdx.y * D.n_pad + i] = acc;
+  if (i < D.n_pad)
+    D.part[(size_t)blockIdx.y * D.n_pad + i] = i < D.n ? (acc[0] + acc[1]) + (acc[2] + acc[3]) : 0.0;
 }
 
 // dst = sum of the partials in chunk order; with `border` also the border row
@@ -827,39 +841,62 @@ __global__ __launch_bounds__(256) void wb_symv_reduce_kernel(const WbDesc *__res
 // Border rows (i >= n_pad): Newton (var = 0): zero below row n_pad, whose r is
 // written by the reduction; variances (var = 1): row n_pad + a holds
 // (Q^+ A^T S)_{a, j} = HT_{a j} sw_j (A = I: Q^+_{a j} sw_j) for a < n_lat,
-// zero beyond.  Grid (ldm / 256, n_pad, B).
+// zero beyond.  Grid (ldm / 256, n_pad / WB_AC, B): a thread takes one row of WB_AC
+// columns with their loads in flight together (one column per workgroup was bound
+// by the launch of workgroups: nine of order 3000 196 to 131 us, 5 TB/s).
+constexpr int WB_AC = 16;
 __global__ __launch_bounds__(256) void wb_assemble_kernel(const WbDesc *__restrict__ wd, int var) {
   const WbDesc D = wd[blockIdx.z];
-  const int j = blockIdx.y;
-  if (j >= D.n_pad) return;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= D.ldm || i < j || (!var && i == D.n_pad)) return;
-  double v = 0.0;
-  if (i < D.n_pad) {
-    v = i == j ? 1.0 : 0.0;
-    if (i < D.n && j < D.n) v += D.sw[i] * D.Pq[(size_t)j * D.ldq + i] * D.sw[j];
-  } else if (var) {
-    const int a = i - D.n_pad;
-    if (a < D.n_lat && j < D.n)
-      v = (D.general ? D.HT[(size_t)j * D.ldh + a] : D.Pq[(size_t)j * D.ldq + a]) * D.sw[j];
+  const int j0 = blockIdx.y * WB_AC, i0 = blockIdx.x * 256, i = i0 + threadIdx.x;
+  if (j0 >= D.n_pad || i0 + 255 < j0 || i >= D.ldm) return;
+  auto *M = gptr(D.M) + (size_t)j0 * D.ldm + i;
+  const auto *sw = gptr((const double *)D.sw);
+  // the matrix that the rows are taken from, the row in it and how many it has
+  const bool body = i < D.n_pad;
+  const int a = body ? i : i - D.n_pad, na = body ? D.n : var ? D.n_lat : 0;
+  const auto *A = gptr((const double *)(!body && D.general ? D.HT : D.Pq));
+  const int lda = !body && D.general ? D.ldh : D.ldq;
+  double x[WB_AC];
+#pragma unroll
+  for (int q = 0; q < WB_AC; ++q) x[q] = 0.0;
+  if (a < na) {
+#pragma unroll
+    for (int q = 0; q < WB_AC; ++q) x[q] = A[(size_t)min(j0 + q, D.n - 1) * lda + a];
   }
-  D.M[(size_t)j * D.ldm + i] = v;
+  const double si = body && i < D.n ? sw[i] : 1.0;
+#pragma unroll
+  for (int q = 0; q < WB_AC; ++q) {
+    const int j = j0 + q;
+    if (i < j || (!var && i == D.n_pad)) continue;
+    double v = i == j ? 1.0 : 0.0;
+    if (a < na && j < D.n) v += si * x[q] * sw[j];
+    M[(size_t)q * D.ldm] = v;
+  }
 }
 
 // var_a = Q^+_aa - ||row a of the factored border||^2 = diag(Sigma*)_a, written
-// to the caller's vector.  Grid (n_lat_pad / 256, B); the column reads of the
-// border are coalesced across the rows.
-__global__ __launch_bounds__(256) void wb_var_kernel(const WbDesc *__restrict__ wd) {
+// to the caller's vector.  Grid (n_lat_pad / 64, B): 64 rows, coalesced, and the
+// columns shared by 16 waves (one thread per row over all columns: nine of order
+// 3000 1280 to 121 us, 5.4 TB/s).
+__global__ __launch_bounds__(1024) void wb_var_kernel(const WbDesc *__restrict__ wd) {
   const WbDesc D = wd[blockIdx.y];
-  const int a = blockIdx.x * 256 + threadIdx.x;
-  if (a >= D.n_lat) return;
-  const auto *G = gptr((const double *)D.M) + D.n_pad + a;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6, a = blockIdx.x * 64 + l;
+  __shared__ double part[16][64];
+  if ((int)blockIdx.x * 64 >= D.n_lat) return;
+  const auto *G = gptr((const double *)D.M) + D.n_pad + min(a, D.n_lat - 1);
   double s = 0.0;
-  for (int j = 0; j < D.n; ++j) {
+#pragma unroll 8
+  for (int j = w; j < D.n; j += 16) {
     const double g = G[(size_t)j * D.ldm];
     s = fma(g, g, s);
   }
-  D.vext[a] = D.Plat[(size_t)a * D.ldlat + a] - s;
+  part[w][l] = s;
+  __syncthreads();
+  if (w != 0 || a >= D.n_lat) return;
+  double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < 16; ++q) c[q & 3] += part[q][l];
+  D.vext[a] = D.Plat[(size_t)a * D.ldlat + a] - ((c[0] + c[1]) + (c[2] + c[3]));
 }
 
 // s = L^{-1} r from the factored border row.  Grid (n_pad / 256, B).
@@ -1175,7 +1212,7 @@ static int woodbury_eval(Ctx &ctx, int B, const inla_model *models, const double
       hipLaunchKernelGGL(wb_symv_reduce_kernel, gv, dim3(256), 0, ctx.stream, da, WV_U, 1);
     });
     ctx.launch(INLA_K_ASSEMBLE, 0.0, qbytes, [&] {
-      hipLaunchKernelGGL(wb_assemble_kernel, dim3((ldm + 255) / 256, np, na), dim3(256), 0, ctx.stream, da, 0);
+      hipLaunchKernelGGL(wb_assemble_kernel, dim3((ldm + 255) / 256, (np + WB_AC - 1) / WB_AC, na), dim3(256), 0, ctx.stream, da, 0);
     });
     int rc = factor_batch(ctx, fs, INLA_PREC_FP64);
     if (rc) return rc;
@@ -1280,13 +1317,13 @@ static int woodbury_var(Ctx &ctx, int B, const inla_model *models, const double 
     hipLaunchKernelGGL(wb_lik_kernel, dim3((L.np_max + 255) / 256, B), dim3(256), 0, ctx.stream, dd);
   });
   ctx.launch(INLA_K_ASSEMBLE, 0.0, 0.0, [&] {
-    hipLaunchKernelGGL(wb_assemble_kernel, dim3((L.ldm_max + 255) / 256, L.np_max, B), dim3(256), 0, ctx.stream,
+    hipLaunchKernelGGL(wb_assemble_kernel, dim3((L.ldm_max + 255) / 256, (L.np_max + WB_AC - 1) / WB_AC, B), dim3(256), 0, ctx.stream,
                        dd, 1);
   });
   int rc = factor_batch(ctx, fs, INLA_PREC_FP64);
   if (rc) return rc;
   ctx.launch(INLA_K_SOLVE, 0.0, 0.0, [&] {
-    hipLaunchKernelGGL(wb_var_kernel, dim3((L.nlp_max + 255) / 256, B), dim3(256), 0, ctx.stream, dd);
+    hipLaunchKernelGGL(wb_var_kernel, dim3((L.nlp_max + 63) / 64, B), dim3(1024), 0, ctx.stream, dd);
   });
   std::vector<int> hinfo(B);
   if (hipMemcpyAsync(hinfo.data(), dinfo, sizeof(int) * B, hipMemcpyDeviceToHost, ctx.stream) != hipSuccess)
