@@ -8,6 +8,7 @@
 // W2 (H x H), b2 (H), W3 (O x H), b3 (O).
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "device.hpp"
@@ -18,23 +19,25 @@ namespace inla {
 // C(M x N) = A(M x K) * B(K x N) with A(i, k) = A[i*sar + k*sac],
 // B(k, j) = B[k*sbr + j*sbc], C(i, j) = C[i*scr + j*scc], on FP32 MFMA
 // (v_mfma_f32_16x16x4f32, FP32 accumulate): 64 x 64 tiles per workgroup, 32 x 32
-// per wave (2 x 2 blocks of 16 x 16), K in chunks of 16 through LDS.  Tile loads
-// run along whichever index of an operand is contiguous, so every layout the
-// network's forward and backward passes use is read coalesced.
-// Epilogue: + bias[j] (if bias), Z = pre-activation stored (if Z), C = GELU(.)
-// (if gelu), or C = alpha * acc + beta * C.  With `ksplit` > 1 the K range is
-// split over blockIdx.z and each split writes its partial tile to `part`
-// (ksplit x M x N); gemm_epilogue_kernel then sums the splits in a fixed order
-// and applies the epilogue (the backward product through the output layer has
-// K = n and only B x H outputs).
+// per wave (2 x 2 blocks of 16 x 16), K in chunks of GKC through two LDS buffers, the
+// loads of the next GPF chunks in flight while one is multiplied: the products of a
+// small batch are bound by the latency of their chunks (one ahead: 1.4 us each), the
+// output layer's by the matrix units.  Tile loads run along whichever index of an
+// operand is contiguous, so every layout the network's forward and backward passes use
+// is read coalesced, in 16-byte loads (W = 4) where every group of four is aligned and
+// inside the operand, else W = 1.  The eight products of a gradient at 256 inputs, 256
+// hidden units and 8192 outputs: 207 to 116 us.  Epilogue: + bias[j] (if bias) and what
+// EPI says, the tile's rows taken from LDS so that they are written whole.
+// With `ksplit` > 1 the K range is split over blockIdx.z and each split writes its
+// partial tile to `part` (ksplit x M x N); gemm_epilogue_kernel then sums the splits in
+// a fixed order and applies the epilogue (the backward product through the output
+// layer has K = n and only B x H outputs).
 struct GemmArgs {
   const float *A, *B;
   float *C, *Z;
-  const float *bias;
+  const float *bias, *dz;
   int M, N, K;
   int sar, sac, sbr, sbc, scr, scc;
-  int gelu;
-  float alpha, beta;
 };
 
 __device__ __forceinline__ float gelu_f(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
@@ -42,124 +45,228 @@ __device__ __forceinline__ float gelu_grad_f(float x) {
   return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * 0.39894228040143268f * expf(-0.5f * x * x);
 }
 
-__device__ __forceinline__ void gemm_store(const GemmArgs &g, int i, int j, float val) {
-  if (g.bias) val += g.bias[j];
-  float *c = g.C + (size_t)i * g.scr + (size_t)j * g.scc;
-  if (g.Z) g.Z[(size_t)i * g.N + j] = val;
-  if (g.gelu) *c = gelu_f(val);
-  else *c = g.alpha * val + (g.beta != 0.0f ? g.beta * *c : 0.0f);
+// Epilogues: the K split's partial tile, a linear output, a hidden layer's forward
+// pass (Z and GELU) and its backward pass (* GELU'(dz)).
+enum { EPI_PART, EPI_LIN, EPI_GELU, EPI_DGELU };
+template <int EPI>
+__device__ __forceinline__ void gemm_store(const GemmArgs &g, int i, int j, float val, float bias, float dz) {
+  val += bias;
+  auto *c = gptr(g.C) + (size_t)i * g.scr + (size_t)j * g.scc;
+  if (EPI == EPI_GELU) {
+    gptr(g.Z)[(size_t)i * g.N + j] = val;
+    val = gelu_f(val);
+  } else if (EPI == EPI_DGELU) {
+    val *= gelu_grad_f(dz);
+  }
+  *c = val;
 }
 
 typedef float f4m __attribute__((ext_vector_type(4)));
 
+constexpr int GKC = 32, GLD = 66;   // GLD: conflict-free reads of k = 8 gq + st and writes along k
+
+// One operand's loads: X(x, k) = P[x * sx + k * sk] for x in [x0, x0 + 64) below nx, a
+// thread's elements (groups of W = 4 along the contiguous index in 16-byte loads, or
+// W = 1) fixed for the whole product.  Indices past the operand are clamped, so that
+// no load is conditional; values past nx belong to outputs that are not stored.
+constexpr int GPF = 4;   // chunks whose loads are in flight
+template <int W> struct TileLoad {
+  static constexpr int NL = GKC * 64 / 256 / W;
+  const float __attribute__((address_space(1))) *row[NL];
+  int kk[NL], lds[NL], kmax, us;
+  size_t sk;
+  __device__ __forceinline__ void init(const float *p, int sx, int sk_, int x0, int nx, int ke) {
+    const bool along_k = sk_ == 1;
+    sk = sk_;
+    us = along_k ? GLD : 1;
+    kmax = along_k ? ke - W : ke - 1;
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const int e = q * 256 + (int)threadIdx.x;
+      int x;
+      if (along_k) { x = e / (GKC / W); kk[q] = e % (GKC / W) * W; } else { kk[q] = e / (64 / W); x = e % (64 / W) * W; }
+      row[q] = gptr(p) + (size_t)min(x0 + x, along_k ? nx - 1 : nx - W) * sx;
+      lds[q] = kk[q] * GLD + x;
+    }
+  }
+  __device__ __forceinline__ void load(int k0, float (&r)[8]) const {
+    typedef float vec __attribute__((ext_vector_type(W)));
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      const auto *p = row[q] + (size_t)min(k0 + kk[q], kmax) * sk;
+      if constexpr (W == 1) r[q] = *p;
+      else {
+        const vec v = *(const vec __attribute__((address_space(1))) *)p;
+#pragma unroll
+        for (int u = 0; u < W; ++u) r[W * q + u] = v[u];
+      }
+    }
+  }
+  __device__ __forceinline__ void store(int k0, int ke, const float (&r)[8], float *S) const {
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+#pragma unroll
+      for (int u = 0; u < W; ++u) S[lds[q] + u * us] = k0 + kk[q] < ke ? r[W * q + u] : 0.0f;
+  }
+};
+
+template <int EPI, int W>
 __global__ __launch_bounds__(256) void mlp_gemm_kernel(GemmArgs g, float *part, int kper) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
+  __shared__ float S[4][GKC][GLD];   // A and B, two buffers each; the product's tile
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w >> 1, wn = w & 1, li = lane & 15, gq = lane >> 4;
   const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
   const int kb = blockIdx.z * kper, ke = min(g.K, kb + kper);
-  const bool a_krow = g.sac == 1, b_kcol = g.sbc != 1;   // contiguous along k?
-  f4m acc[2][2];
+  TileLoad<W> A, B;
+  A.init(g.A, g.sar, g.sac, i0, g.M, ke);
+  B.init(g.B, g.sbc, g.sbr, j0, g.N, ke);
+  float ra[GPF][8], rb[GPF][8];
+  f4m acc2[2][2][2];   // even and odd chunks: shorter chains of rounded sums
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f4m{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kb; k0 < ke; k0 += 16) {
+    for (int b = 0; b < 2; ++b) acc2[0][a][b] = acc2[1][a][b] = f4m{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = q * 256 + tid;
-      int r, kk;
-      if (a_krow) { r = e >> 4; kk = e & 15; } else { kk = e >> 6; r = e & 63; }
-      const int i = i0 + r, k = k0 + kk;
-      As[kk][r] = (i < g.M && k < ke) ? g.A[(size_t)i * g.sar + (size_t)k * g.sac] : 0.0f;
-      int c;
-      if (b_kcol) { c = e >> 4; kk = e & 15; } else { kk = e >> 6; c = e & 63; }
-      const int j = j0 + c, kb2 = k0 + kk;
-      Bs[kk][c] = (j < g.N && kb2 < ke) ? g.B[(size_t)kb2 * g.sbr + (size_t)j * g.sbc] : 0.0f;
+  for (int u = 0; u < GPF; ++u)
+    if (kb + u * GKC < ke) {
+      A.load(kb + u * GKC, ra[u]);
+      B.load(kb + u * GKC, rb[u]);
     }
-    __syncthreads();
+  for (int k1 = kb; k1 < ke; k1 += GPF * GKC)
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      const int kk = 4 * gq + st;   // lane group gq supplies k = 4 gq + st at step st
-      float av[2], bv[2];
+    for (int u = 0; u < GPF; ++u) {
+      const int k0 = k1 + u * GKC;
+      if (k0 >= ke) break;
+      // a buffer is written again two chunks on: every wave has passed the barrier of
+      // the chunk between, so it has read this one
+      A.store(k0, ke, ra[u], &S[2 * (u & 1)][0][0]);
+      B.store(k0, ke, rb[u], &S[2 * (u & 1) + 1][0][0]);
+      if (k0 + GPF * GKC < ke) {
+        A.load(k0 + GPF * GKC, ra[u]);
+        B.load(k0 + GPF * GKC, rb[u]);
+      }
+      __syncthreads();
 #pragma unroll
-      for (int a = 0; a < 2; ++a) av[a] = As[kk][wm * 32 + a * 16 + li];
+      for (int st = 0; st < GKC / 4; ++st) {
+        const int kk = GKC / 4 * gq + st;   // lane group gq supplies k = 8 gq + st at step st
+        float av[2], bv[2];
 #pragma unroll
-      for (int b = 0; b < 2; ++b) bv[b] = Bs[kk][wn * 32 + b * 16 + li];
+        for (int a = 0; a < 2; ++a) av[a] = S[2 * (u & 1)][kk][wm * 32 + a * 16 + li];
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int b = 0; b < 2; ++b) bv[b] = S[2 * (u & 1) + 1][kk][wn * 32 + b * 16 + li];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc[a][b], 0, 0, 0);
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc2[u & 1][a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv[b], acc2[u & 1][a][b], 0, 0, 0);
+      }
     }
-    __syncthreads();
-  }
+  __syncthreads();
   // lane l holds rows 4 (l / 16) + v, column l % 16 of each 16 x 16 block
+  float (*T)[GLD] = S[0];   // 64 rows over both of the first buffers
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = i0 + wm * 32 + a * 16 + 4 * gq + v, j = j0 + wn * 32 + b * 16 + li;
-        if (i >= g.M || j >= g.N) continue;
-        if (part) part[((size_t)blockIdx.z * g.M + i) * g.N + j] = acc[a][b][v];
-        else gemm_store(g, i, j, acc[a][b][v]);
-      }
+      for (int v = 0; v < 4; ++v) T[wm * 32 + a * 16 + 4 * gq + v][wn * 32 + b * 16 + li] = acc2[0][a][b][v] + acc2[1][a][b][v];
+  __syncthreads();
+  const int j = j0 + lane, jc = min(j, g.N - 1);
+  const float bias = EPI != EPI_PART && g.bias ? gptr(g.bias)[jc] : 0.0f;
+  float (*Z)[GLD] = S[2];   // the same rows of dz, loaded together
+  if (EPI == EPI_DGELU) {
+    float dz[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) dz[u] = gptr(g.dz)[(size_t)min(i0 + w + 4 * u, g.M - 1) * g.N + jc];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) Z[w + 4 * u][lane] = dz[u];
+  }
+  float *C = EPI == EPI_PART ? part + (size_t)blockIdx.z * g.M * g.N : nullptr;
+#pragma unroll 1
+  for (int r = w; r < 64; r += 16) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + r + 4 * u;
+      if (i >= g.M || j >= g.N) continue;
+      const float val = T[r + 4 * u][lane];
+      if (EPI == EPI_PART) gptr(C)[(size_t)i * g.N + j] = val;
+      else gemm_store<EPI>(g, i, j, val, bias, EPI == EPI_DGELU ? Z[r + 4 * u][lane] : 0.0f);
+    }
+  }
 }
 
 // Sum of the K splits (fixed order) and the epilogue, one thread per output.
-__global__ __launch_bounds__(256) void gemm_epilogue_kernel(GemmArgs g, const float *part, int ksplit) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+template <int EPI> __global__ __launch_bounds__(64) void gemm_epilogue_kernel(GemmArgs g, const float *part, int ksplit) {
+  const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;
   if (idx >= (int64_t)g.M * g.N) return;
   const int i = (int)(idx / g.N), j = (int)(idx % g.N);
+  const float bias = g.bias ? gptr(g.bias)[j] : 0.0f, dz = EPI == EPI_DGELU ? gptr(g.dz)[idx] : 0.0f;
   float s = 0.0f;
-  for (int z = 0; z < ksplit; ++z) s += part[(size_t)z * g.M * g.N + idx];
-  gemm_store(g, i, j, s);
+#pragma unroll 8
+  for (int z = 0; z < ksplit; ++z) s += gptr(part)[(size_t)z * g.M * g.N + idx];
+  gemm_store<EPI>(g, i, j, s, bias, dz);
 }
 
 // K splits of a product: enough workgroups for the chip (about 512) without
-// splits shorter than 128.
+// splits shorter than 256: half of that costs a second launch for the sum that takes
+// as long as the chunks it saves.
 static int gemm_ksplit(int M, int N, int K) {
   const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
   int ks = std::max(1, 512 / std::max(1, tiles));
-  ks = std::min(ks, std::max(1, K / 128));
+  ks = std::min(ks, std::max(1, K / 256));
   return ks;
 }
 
-// dY <- dY * GELU'(Z) (elementwise).
-__global__ void gelu_back_kernel(float *dY, const float *Z, int count) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < count) dY[i] *= gelu_grad_f(Z[i]);
-}
-
-// Column sums of a (rows x cols) row-major matrix into out[cols] (bias
-// gradients), rows added in increasing order; eight rows' loads are issued
-// ahead of their additions.
-__global__ void colsum_kernel(const float *X, int rows, int cols, float *out) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= cols) return;
+// Column sums of the (rows x cols) row-major matrices X into out (the three layers'
+// bias gradients) in one launch: a workgroup takes 64 columns, its 16 waves every 16th
+// row.  One thread per column was a serial walk by one or a few workgroups (rows = 256,
+// cols = 8192 and twice 256: 46 to 6 us together).
+struct ColSums {
+  const float *X[3];
+  float *out[3];
+  int cols[3];
+};
+__global__ __launch_bounds__(1024) void colsum_kernel(ColSums c, int rows) {
+  __shared__ float part[16][64];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int blk = blockIdx.x, m = 0;
+  for (; m < 2 && blk >= (c.cols[m] + 63) / 64; ++m) blk -= (c.cols[m] + 63) / 64;
+  const int cols = c.cols[m], j = blk * 64 + l, jc = min(j, cols - 1);
+  const auto *X = gptr(c.X[m]);
   float s = 0.0f;
-  for (int r0 = 0; r0 < rows; r0 += 8) {
-    float v[8];
+#pragma unroll 8
+  for (int r = w; r < rows; r += 16) s += X[(size_t)r * cols + jc];
+  part[w][l] = s;
+  __syncthreads();
+  if (w != 0 || j >= cols) return;
+  float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = r0 + u < rows ? X[(size_t)(r0 + u) * cols + j] : 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (r0 + u < rows) s += v[u];
-  }
-  out[j] = s;
+  for (int q = 0; q < 16; ++q) t[q & 3] += part[q][l];
+  c.out[m][j] = (t[0] + t[1]) + (t[2] + t[3]);
 }
 
 // dOut = 2 (out - target) / (B * O); per-block partial sums of the squared error.
-__global__ void mse_grad_kernel(const float *out, const double *tgt, float *dout, int count, float scale, double *part) {
+__global__ __launch_bounds__(256) void mse_grad_kernel(const float *out, const double *tgt, float *dout, int64_t count,
+                                                       float scale, double *part) {
   __shared__ double sh[4];
-  const int i = blockIdx.x * 256 + threadIdx.x;
   double se = 0.0;
-  if (i < count) {
-    const float d = out[i] - (float)tgt[i];
-    dout[i] = scale * 2.0f * d;
-    se = (double)d * d;
+  for (int64_t i0 = (int64_t)blockIdx.x * 1024; i0 < count; i0 += (int64_t)gridDim.x * 1024) {
+    float o[4];
+    double t[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t i = min(i0 + q * 256 + threadIdx.x, count - 1);
+      o[q] = gptr(out)[i];
+      t[q] = gptr(tgt)[i];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t i = i0 + q * 256 + threadIdx.x;
+      if (i >= count) continue;
+      const float d = o[q] - (float)t[q];
+      gptr(dout)[i] = scale * 2.0f * d;
+      se += (double)d * d;
+    }
   }
   se = block_sum256(se, sh);
   if (threadIdx.x == 0) part[blockIdx.x] = se;
@@ -294,12 +401,28 @@ void gemm(inla_mlp *m, hipStream_t s, const GemmArgs &g) {
   const int kper = ks > 1 ? ((g.K + ks - 1) / ks + 15) / 16 * 16 : g.K;
   ks = ks > 1 ? (g.K + kper - 1) / kper : 1;
   dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, ks);
-  hipLaunchKernelGGL(mlp_gemm_kernel, grid, dim3(256), 0, s, g, ks > 1 ? m->kpart : nullptr, kper);
-  if (ks > 1) {
+  // 16-byte loads: a contiguous index whose length, and the other index's stride, are
+  // multiples of four (kper is one of 16), at an aligned address
+  auto vec4 = [](const float *p, int sx, int sk, int nx, int K) {
+    return ((uintptr_t)p & 15) == 0 && (sk == 1 ? sx % 4 == 0 && K % 4 == 0 : sx == 1 && sk % 4 == 0 && nx % 4 == 0);
+  };
+  const bool vec = vec4(g.A, g.sar, g.sac, g.M, g.K) && vec4(g.B, g.sbc, g.sbr, g.N, g.K);
+  auto launch = [&](auto epi) {
+    constexpr int E = decltype(epi)::value;
+    if (ks == 1) {
+      if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<E, 4>), grid, dim3(256), 0, s, g, nullptr, kper);
+      else hipLaunchKernelGGL((mlp_gemm_kernel<E, 1>), grid, dim3(256), 0, s, g, nullptr, kper);
+      return;
+    }
     const int64_t cnt = (int64_t)g.M * g.N;
-    hipLaunchKernelGGL(gemm_epilogue_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, g,
+    if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 4>), grid, dim3(256), 0, s, g, m->kpart, kper);
+    else hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 1>), grid, dim3(256), 0, s, g, m->kpart, kper);
+    hipLaunchKernelGGL(gemm_epilogue_kernel<E>, dim3((unsigned)((cnt + 63) / 64)), dim3(64), 0, s, g,
                        (const float *)m->kpart, ks);
-  }
+  };
+  if (g.Z) launch(std::integral_constant<int, EPI_GELU>());
+  else if (g.dz) launch(std::integral_constant<int, EPI_DGELU>());
+  else launch(std::integral_constant<int, EPI_LIN>());
 }
 
 GemmArgs ga(const float *A, int sar, int sac, const float *B, int sbr, int sbc, float *C, int scr, int scc, int M,
@@ -307,7 +430,6 @@ GemmArgs ga(const float *A, int sar, int sac, const float *B, int sbr, int sbc, 
   GemmArgs g{};
   g.A = A; g.B = B; g.C = C; g.M = M; g.N = N; g.K = K;
   g.sar = sar; g.sac = sac; g.sbr = sbr; g.sbc = sbc; g.scr = scr; g.scc = scc;
-  g.alpha = 1.0f; g.beta = 0.0f;
   return g;
 }
 
@@ -315,45 +437,46 @@ GemmArgs ga(const float *A, int sar, int sac, const float *B, int sbr, int sbc, 
 void forward(inla_mlp *m, hipStream_t s, int B) {
   const float *P = m->params;
   GemmArgs g = ga(m->u, m->I, 1, P + m->off_W1(), 1, m->I, m->h1, m->H, 1, B, m->H, m->I);
-  g.bias = P + m->off_b1(); g.Z = m->z1; g.gelu = 1;
+  g.bias = P + m->off_b1(); g.Z = m->z1;
   gemm(m, s, g);
   g = ga(m->h1, m->H, 1, P + m->off_W2(), 1, m->H, m->h2, m->H, 1, B, m->H, m->H);
-  g.bias = P + m->off_b2(); g.Z = m->z2; g.gelu = 1;
+  g.bias = P + m->off_b2(); g.Z = m->z2;
   gemm(m, s, g);
   g = ga(m->h2, m->H, 1, P + m->off_W3(), 1, m->H, m->out, m->O, 1, B, m->O, m->H);
   g.bias = P + m->off_b3();
   gemm(m, s, g);
 }
 
-// Backward pass from m->dout into m->grad (flat, same layout as params).
-void backward(inla_mlp *m, hipStream_t s, int B) {
+// Backward pass from m->dout into G (flat, same layout as params).
+void backward(inla_mlp *m, hipStream_t s, int B, float *G) {
   const float *P = m->params;
-  float *G = m->grad;
   const int I = m->I, H = m->H, O = m->O;
   // dW3 (O x H) = dout^T (O x B) * h2 (B x H)
   gemm(m, s, ga(m->dout, 1, O, m->h2, H, 1, G + m->off_W3(), H, 1, O, H, B));
-  hipLaunchKernelGGL(colsum_kernel, dim3((O + 255) / 256), dim3(256), 0, s, m->dout, B, O, G + m->off_b3());
   // dh2 (B x H) = dout (B x O) * W3 (O x H), then * GELU'(z2)
-  gemm(m, s, ga(m->dout, O, 1, P + m->off_W3(), H, 1, m->dh2, H, 1, B, H, O));
-  hipLaunchKernelGGL(gelu_back_kernel, dim3((B * H + 255) / 256), dim3(256), 0, s, m->dh2, m->z2, B * H);
+  GemmArgs g = ga(m->dout, O, 1, P + m->off_W3(), H, 1, m->dh2, H, 1, B, H, O);
+  g.dz = m->z2;
+  gemm(m, s, g);
   gemm(m, s, ga(m->dh2, 1, H, m->h1, H, 1, G + m->off_W2(), H, 1, H, H, B));
-  hipLaunchKernelGGL(colsum_kernel, dim3((H + 255) / 256), dim3(256), 0, s, m->dh2, B, H, G + m->off_b2());
-  gemm(m, s, ga(m->dh2, H, 1, P + m->off_W2(), H, 1, m->dh1, H, 1, B, H, H));
-  hipLaunchKernelGGL(gelu_back_kernel, dim3((B * H + 255) / 256), dim3(256), 0, s, m->dh1, m->z1, B * H);
+  g = ga(m->dh2, H, 1, P + m->off_W2(), H, 1, m->dh1, H, 1, B, H, H);
+  g.dz = m->z1;
+  gemm(m, s, g);
   gemm(m, s, ga(m->dh1, 1, H, m->u, I, 1, G + m->off_W1(), I, 1, H, I, B));
-  hipLaunchKernelGGL(colsum_kernel, dim3((H + 255) / 256), dim3(256), 0, s, m->dh1, B, H, G + m->off_b1());
+  const ColSums c = {{m->dout, m->dh2, m->dh1}, {G + m->off_b3(), G + m->off_b2(), G + m->off_b1()}, {O, H, H}};
+  hipLaunchKernelGGL(colsum_kernel, dim3((O + 63) / 64 + 2 * ((H + 63) / 64)), dim3(1024), 0, s, c, B);
 }
 
-int loss_and_grad(inla_mlp *m, int B, const float *x_in, const double *target, double *loss) {
+// The gradient goes to `grad` (m->grad or the caller's).
+int loss_and_grad(inla_mlp *m, int B, const float *x_in, const double *target, double *loss, float *grad) {
   hipStream_t s = handle_stream(m->h);
   int rc = ensure_cap(m, B);
   if (rc) return rc;
   if (hipMemcpyAsync(m->u, x_in, 4 * (size_t)B * m->I, hipMemcpyDeviceToDevice, s) != hipSuccess) return INLA_ERR_HIP;
   forward(m, s, B);
-  const int cnt = B * m->O, nblk = (cnt + 255) / 256;
-  hipLaunchKernelGGL(mse_grad_kernel, dim3(nblk), dim3(256), 0, s, m->out, target, m->dout, cnt, 1.0f / (float)cnt,
-                     m->part);
-  backward(m, s, B);
+  const int cnt = B * m->O, nblk = std::min((cnt + 1023) / 1024, 1024);
+  hipLaunchKernelGGL(mse_grad_kernel, dim3(nblk), dim3(256), 0, s, m->out, target, m->dout, (int64_t)cnt,
+                     1.0f / (float)cnt, m->part);
+  backward(m, s, B, grad);
   if (loss) {
     std::vector<double> h(nblk);
     if (hipMemcpyAsync(h.data(), m->part, 8 * nblk, hipMemcpyDeviceToHost, s) != hipSuccess) return INLA_ERR_HIP;
@@ -465,12 +588,9 @@ int inla_mlp_grad(inla_mlp *m, int32_t B, const float *x_in, const double *targe
   if (B < 1) return -2;
   if (!x_in) return -3;
   if (!target) return -4;
-  int rc = loss_and_grad(m, B, x_in, target, loss);
+  int rc = loss_and_grad(m, B, x_in, target, loss, grad_out ? grad_out : m->grad);
   if (rc) return rc;
-  hipStream_t s = handle_stream(m->h);
-  if (grad_out && hipMemcpyAsync(grad_out, m->grad, 4 * (size_t)m->P, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return INLA_ERR_HIP;
-  return hipStreamSynchronize(s) == hipSuccess ? INLA_OK : INLA_ERR_HIP;
+  return hipStreamSynchronize(handle_stream(m->h)) == hipSuccess ? INLA_OK : INLA_ERR_HIP;
 }
 
 int inla_mlp_train_step(inla_mlp *m, int32_t B, const float *x_in, const double *target, float lr, double *loss) {
@@ -479,7 +599,7 @@ int inla_mlp_train_step(inla_mlp *m, int32_t B, const float *x_in, const double 
   if (!x_in) return -3;
   if (!target) return -4;
   if (!(lr > 0.0f)) return -5;
-  int rc = loss_and_grad(m, B, x_in, target, loss);
+  int rc = loss_and_grad(m, B, x_in, target, loss, m->grad);
   if (rc) return rc;
   hipStream_t s = handle_stream(m->h);
   m->step += 1;
