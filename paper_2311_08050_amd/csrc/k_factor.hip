@@ -613,7 +613,10 @@ __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDe
 // chain takes 45,000 cycles in FP64 and 40,000 in FP32 at every column, 23,000 of
 // them the factorisation (65,000 and 50,000 on average with the product over the
 // whole panel, and TRSM operands and results staged in 16-deep chunks before that):
-// one matrix of order 1000 463 us (622), 9 of order 3000 2.82 ms (3.36).
+// one matrix of order 1000 463 us (622), 9 of order 3000 2.82 ms (3.36).  The chunks'
+// loads through buffer resources, whose offsets leave registers for a second FP64
+// chunk: a step of 9 of order 3000 24.7 to 24.1 us, of two of order 16384 in FP32 20.9
+// to 20.1.
 template <typename T>
 struct PanelLds {
   static constexpr int LDC = NBI + 4;          // LDS row length (elements): conflict-free MFMA operand reads
@@ -637,6 +640,9 @@ template <typename T> struct TileBuf {
     if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, off, 0));
     else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_off, off, 0));
   }
+  template <typename V> __device__ __forceinline__ V load16(unsigned lane_off, unsigned off) const {
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
+  }
   __device__ __forceinline__ void store(T v, unsigned lane_off, unsigned off) const {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
     if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane_off, off, 0);
@@ -653,10 +659,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   constexpr int VEC = 16 / sizeof(T);
   constexpr int LDC = PanelLds<T>::LDC, PKC = PanelLds<T>::PKC, NB = NBI / 16;
   constexpr int LA = PKC * NBI / VEC / 256;           // 16-byte loads per thread per operand chunk
+  constexpr int DEPTH = F64 ? 2 : 1;                  // chunks in flight (two in FP32: no faster)
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   typedef __attribute__((address_space(1))) T gT;
   typedef __attribute__((address_space(1))) const T gcT;
-  typedef __attribute__((address_space(1))) const vec_t gcvec;
   typedef typename std::conditional<F64, d4, f4>::type acc_t;
   __shared__ __attribute__((aligned(16))) PanelLds<T> S;
 
@@ -698,7 +704,8 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
     else return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0);
   };
 
-  // 1. acc = A[I, ks:j] A[c0, ks:j]^T, double-buffered PKC-deep chunks.  The tile
+  // 1. acc = A[I, ks:j] A[c0, ks:j]^T, double-buffered PKC-deep chunks, in FP64 with
+  //    two in flight (a 448-deep tile 46,500 to 43,400 cycles).  The tile
   //    itself and the first KX column blocks of L_jj^{-1} (column-major: X[n][k] at
   //    k * 64 + n, zero above its diagonal) are read behind the first chunk.
   acc_t acc[NB];
@@ -727,47 +734,50 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
     for (int k = 0; k < KX; ++k) xload(k, xp[k]);
   };
   if (K > 0) {
-    gcT *Ag = gptr((const T *)d.A) + (size_t)ks * ld + r0;
-    gcT *Bg = gptr((const T *)d.A) + (size_t)ks * ld + c0;
-    vec_t ra[LA], rb[LA];
-    auto gload = [&](int kc) {
+    const T *Ap = (const T *)d.A + (size_t)ks * ld + r0, *Bp = (const T *)d.A + (size_t)ks * ld + c0;
+    constexpr int KS = 256 / (NBI / VEC);   // columns per load of the workgroup
+    const unsigned gl = (unsigned)((tid / (NBI / VEC) * ld + tid % (NBI / VEC) * VEC) * sizeof(T));
+    // chunk c's loads go to register set c % DEPTH, DEPTH chunks ahead (K is a multiple of 64)
+    vec_t ra[DEPTH][LA], rb[DEPTH][LA];
+    auto gload = [&](int u, int kc) {
+      const TileBuf<T> Ag(Ap + (size_t)kc * ld), Bg(Bp + (size_t)kc * ld);
+#pragma unroll
+      for (int it = 0; it < LA; ++it) {
+        ra[u][it] = Ag.template load16<vec_t>(gl, it * KS * lds);
+        rb[u][it] = Bg.template load16<vec_t>(gl, it * KS * lds);
+      }
+    };
+    auto lstore = [&](int u, int buf) {
 #pragma unroll
       for (int it = 0; it < LA; ++it) {
         const int lin = it * 256 + tid, kk = lin / (NBI / VEC), rp = lin % (NBI / VEC);
-        ra[it] = *reinterpret_cast<gcvec *>(Ag + (size_t)(kc + kk) * ld + VEC * rp);
-        rb[it] = *reinterpret_cast<gcvec *>(Bg + (size_t)(kc + kk) * ld + VEC * rp);
+        *reinterpret_cast<vec_t *>(&S.g.As[buf][kk][VEC * rp]) = ra[u][it];
+        *reinterpret_cast<vec_t *>(&S.g.Bs[buf][kk][VEC * rp]) = rb[u][it];
       }
     };
-    auto lstore = [&](int buf) {
 #pragma unroll
-      for (int it = 0; it < LA; ++it) {
-        const int lin = it * 256 + tid, kk = lin / (NBI / VEC), rp = lin % (NBI / VEC);
-        *reinterpret_cast<vec_t *>(&S.g.As[buf][kk][VEC * rp]) = ra[it];
-        *reinterpret_cast<vec_t *>(&S.g.Bs[buf][kk][VEC * rp]) = rb[it];
-      }
-    };
-    gload(0);
+    for (int u = 0; u < DEPTH; ++u) gload(u, u * PKC);
     tile_loads();
-    lstore(0);
+    lstore(0, 0);
     __syncthreads();
-    int buf = 0;
-    for (int kc = 0; kc < K; kc += PKC) {   // K is a multiple of 64
-      const bool more = kc + PKC < K;
-      if (more) gload(kc + PKC);
+    for (int kc0 = 0; kc0 < K; kc0 += 2 * PKC)
 #pragma unroll
-      for (int s = 0; s < PKC / 4; ++s) {
-        const int kk = 16 * (s >> 2) + 4 * g + (s & 3);
-        const T y = S.g.As[buf][kk][16 * w + li];
-        T x[NB];
+      for (int c = 0; c < 2; ++c) {
+        const int kc = kc0 + c * PKC;
+        if (kc + DEPTH * PKC < K) gload(c % DEPTH, kc + DEPTH * PKC);
 #pragma unroll
-        for (int b = 0; b < NB; ++b) x[b] = S.g.Bs[buf][kk][16 * b + li];
+        for (int s = 0; s < PKC / 4; ++s) {
+          const int kk = 16 * (s >> 2) + 4 * g + (s & 3);
+          const T y = S.g.As[c][kk][16 * w + li];
+          T x[NB];
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = mfma(x[b], y, acc[b]);
+          for (int b = 0; b < NB; ++b) x[b] = S.g.Bs[c][kk][16 * b + li];
+#pragma unroll
+          for (int b = 0; b < NB; ++b) acc[b] = mfma(x[b], y, acc[b]);
+        }
+        if (kc + PKC < K) lstore((c + 1) % DEPTH, c ^ 1);
+        __syncthreads();
       }
-      if (more) lstore(buf ^ 1);
-      __syncthreads();
-      buf ^= 1;
-    }
   } else {
     tile_loads();
   }
