@@ -425,6 +425,28 @@ __device__ __forceinline__ void subtract_tile(__attribute__((address_space(1))) 
 // sub-chunk.  LDS rows are padded by 4 elements so that each read is free of
 // bank conflicts.
 // --------------------------------------------------------------------------
+// Elements of a tile through a buffer resource: a uniform base, one 32-bit lane
+// offset for the whole tile and a scalar offset per access (both in bytes), where
+// 64-bit addresses would hold two registers per element over the kernel's length.
+// The resource spans 2 GB from the base (a 64-column tile ends well before that).
+template <typename T> struct TileBuf {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ explicit TileBuf(const void *base)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000)) {}
+  __device__ __forceinline__ T load(unsigned lane_off, unsigned off) const {
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, off, 0));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_off, off, 0));
+  }
+  template <typename V> __device__ __forceinline__ V load16(unsigned lane_off, unsigned off) const {
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
+  }
+  __device__ __forceinline__ void store(T v, unsigned lane_off, unsigned off) const {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane_off, off, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane_off, off, 0);
+  }
+};
+
 // SEL (row selection of update_tile) is a template parameter so that the
 // border-row launch beside a BF16 trailing update is a kernel of its own; the
 // trailing update of every row is trail_update_kernel (below), so that each
@@ -456,9 +478,8 @@ __device__ __forceinline__ void gemm_update_body(const FactorDesc *__restrict__ 
   int row0, col0, ks, ke;
   if (!update_tile(d, kind, p0, nb, TM, TN, SEL, bx, row0, col0, ks, ke)) return;
 
-  const int ld = d.ld, ldb = ld;
-  gcT *Ag = gptr((const T *)d.A) + (size_t)ks * ld + row0;
-  gcT *Bg = gptr((const T *)d.A) + (size_t)ks * ld + col0;
+  const int ld = d.ld;
+  const T *Ap = (const T *)d.A + (size_t)ks * ld + row0, *Bp = (const T *)d.A + (size_t)ks * ld + col0;
   gT *Cg = gptr((T *)d.A) + (size_t)col0 * ld + row0;
   const int K = ke - ks;
 
@@ -473,17 +494,16 @@ __device__ __forceinline__ void gemm_update_body(const FactorDesc *__restrict__ 
     for (int b = 0; b < BN; ++b) acc[a][b] = acc_t{0, 0, 0, 0};
 
   vec_t ra[LA], rb[LB];
+  constexpr int KA = 256 / (TM / VEC), KB = 256 / (TN / VEC);   // columns per load of the workgroup
+  const unsigned lds = ld * (unsigned)sizeof(T);
+  const unsigned al = (unsigned)((tid / (TM / VEC) * ld + tid % (TM / VEC) * VEC) * sizeof(T));
+  const unsigned bl = (unsigned)((tid / (TN / VEC) * ld + tid % (TN / VEC) * VEC) * sizeof(T));
   auto gload = [&](int kc) {
+    const TileBuf<T> Ag(Ap + (size_t)kc * ld), Bg(Bp + (size_t)kc * ld);
 #pragma unroll
-    for (int it = 0; it < LA; ++it) {
-      const int lin = it * 256 + tid, kk = lin / (TM / VEC), rp = lin % (TM / VEC);
-      ra[it] = *reinterpret_cast<gcvec *>(Ag + (size_t)(kc + kk) * ld + VEC * rp);
-    }
+    for (int it = 0; it < LA; ++it) ra[it] = Ag.template load16<vec_t>(al, it * KA * lds);
 #pragma unroll
-    for (int it = 0; it < LB; ++it) {
-      const int lin = it * 256 + tid, kk = lin / (TN / VEC), rp = lin % (TN / VEC);
-      rb[it] = *reinterpret_cast<gcvec *>(Bg + (size_t)(kc + kk) * ldb + VEC * rp);
-    }
+    for (int it = 0; it < LB; ++it) rb[it] = Bg.template load16<vec_t>(bl, it * KB * lds);
   };
   auto lstore = [&](int buf) {
 #pragma unroll
@@ -552,9 +572,13 @@ __global__ __launch_bounds__(256, 2) void gemm_update_kernel(const FactorDesc *_
 }
 
 // The trailing update of the blocked Cholesky (kinds TRAIL, TRAIL_A, TRAIL_B).
-// The FP64 64 x 64 tile stages its operands through one LDS buffer (17 KB, six
-// workgroups per CU, 7% faster than two buffers at four); the others through
-// two.
+// The FP64 64 x 64 tile stages its operands through one LDS buffer (17 KB, seven
+// workgroups per CU at 68 registers; two buffers at four are slower); the others
+// through two.  Its loads through buffer resources, whose 64-bit forms took ten more
+// registers (six workgroups): all updates of eight matrices of order 8192 86.3 to
+// 82.0 ms (71 TFLOP/s, of 73 in a large library product), of nine of order 3000 11.5 to
+// 11.1 ms, of 20 uneven ones 135.7 to 128.3 ms.  Held to 64 registers for eight
+// workgroups it spills and takes 95.5 ms.
 template <typename T, int TM, int TN>
 __global__ __launch_bounds__(256, 2) void trail_update_kernel(const FactorDesc *__restrict__ descs, int kind, int p0,
                                                               int nb) {
@@ -563,7 +587,7 @@ __global__ __launch_bounds__(256, 2) void trail_update_kernel(const FactorDesc *
 
 // The same update for a factorisation on the handle's aux stream (the
 // concurrent prior pass), always with two LDS buffers: the FP64 64 x 64 tile
-// then holds four workgroups per CU rather than six, which leaves every CU
+// then holds four workgroups per CU rather than seven, which leaves every CU
 // room for the caller's stream's panel steps and solves beside it.
 template <typename T, int TM, int TN>
 __global__ __launch_bounds__(256, 2) void trail_update_aux_kernel(const FactorDesc *__restrict__ descs, int kind,
@@ -626,28 +650,6 @@ struct PanelLds {
     T Ls[NBI][LDC];                                        // L[I, j] ([k][row])
     Potf2Lds f;                                            // the next diagonal block's factorisation
   };
-};
-
-// Elements of a tile through a buffer resource: a uniform base, one 32-bit lane
-// offset for the whole tile and a scalar offset per access (both in bytes), where
-// 64-bit addresses would hold two registers per element over the kernel's length.
-// The resource spans 2 GB from the base (a 64-column tile ends well before that).
-template <typename T> struct TileBuf {
-  __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ explicit TileBuf(const void *base)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, 0x7fffffff, 0x00020000)) {}
-  __device__ __forceinline__ T load(unsigned lane_off, unsigned off) const {
-    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, off, 0));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, lane_off, off, 0));
-  }
-  template <typename V> __device__ __forceinline__ V load16(unsigned lane_off, unsigned off) const {
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0));
-  }
-  __device__ __forceinline__ void store(T v, unsigned lane_off, unsigned off) const {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), r, lane_off, off, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, lane_off, off, 0);
-  }
 };
 
 // Four workgroups per CU in FP32; three in FP64, whose registers would
