@@ -366,12 +366,22 @@ __device__ __forceinline__ bool update_tile(const FactorDesc &d, int kind, int p
     c0 = min(pend + nb, d.nf); r0 = c0; cend = d.ncols;
   }
   if (r0 >= d.nrows || c0 >= cend) return false;
-  const int nr = (d.nrows - r0) / TM;
-  int I, J;
-  if (!trap_grouped(bx, nr, (cend - c0) / TN, I, J)) return false;
-  row0 = r0 + I * TM;
-  col0 = c0 + J * TN;
-  if ((sel == 1 && row0 >= d.nf) || (sel == 2 && row0 < d.nf)) return false;
+  // (the border rows' tiles are numbered by themselves: as the last of all tiles they
+  // were one XCD's work per theta, 178 us where 64 do for two of order 16384)
+  if (sel == 2) {
+    const int nb_rows = (d.nrows - d.nf) / TM, nc = (cend - c0) / TN;
+    if (bx >= nb_rows * nc) return false;
+    row0 = d.nf + bx % nb_rows * TM;
+    col0 = c0 + bx / nb_rows * TN;
+    if (col0 > row0) return false;
+  } else {
+    const int nr = (d.nrows - r0) / TM;
+    int I, J;
+    if (!trap_grouped(bx, nr, (cend - c0) / TN, I, J)) return false;
+    row0 = r0 + I * TM;
+    col0 = c0 + J * TN;
+    if (sel == 1 && row0 >= d.nf) return false;
+  }
   if (row0 >= d.id_row0 && row0 - d.id_row0 >= ke) return false;
   if (col0 >= d.id_row0 && col0 - d.id_row0 >= ke) return false;
   return true;
@@ -1019,9 +1029,12 @@ __global__ __launch_bounds__(256, 2) void trail_bf16_kernel(const FactorDesc *__
 // next chunk in registers, two workgroups per CU by registers: larger wave tiles
 // would leave LDS reads (three planes of both operands per chunk) further from
 // the bound but not fit the accumulators twice.  SEL as in update_tile.
-// Trailing updates of 25 theta at n = 8192 (two factorisations): 48.0 ms with 2.6 ms
-// of packing (74.1 ms on v_mfma_f32_16x16x4f32); that is 180 TF of FP32 products,
-// 1.08 PF on the BF16 units, the rate a large BF16 library product reaches (1.06).
+// The tile itself is read behind the last chunk's products in 16-byte pieces: four
+// dependent rounds of reads and writes after the loop were a quarter of a tile's time.
+// Trailing updates of 25 theta at n = 8192 (two factorisations): 45.8 ms with 2.6 ms
+// of packing (74.1 ms on v_mfma_f32_16x16x4f32, 48.0 with the tile read at the end);
+// that is 189 TF of FP32 products, 1.13 PF on the BF16 units (a large BF16 library
+// product: 1.06).
 // Error of log|S| at n = 1024: 6.6e-7 relative (2.1e-6 on the FP32 units).
 // --------------------------------------------------------------------------
 template <int SEL>
@@ -1029,7 +1042,6 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
                                                              int nb) {
   constexpr int TM = 128, KCH = 32, KG = KCH / 8, NP = 3, WT = 64, BM = 4, BN = 4;
   constexpr int E = NP * KG * TM / 256;   // entries per thread, operand and chunk
-  typedef __attribute__((address_space(1))) float gT;
   __shared__ bf8 As[NP * KG][TM];         // [plane KG + group][slot]
   __shared__ bf8 Bs[NP * KG][TM];
 
@@ -1040,9 +1052,8 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
   if (!update_tile(d, kind, p0, nb, TM, TM, SEL, bx, row0, col0, ks, ke)) return;
   const int ld = d.ld, prows = d.prows, K = ke - ks;
   gcbf8 *P = gptr((const bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot);
-  gT *Cg = gptr((float *)d.A) + (size_t)col0 * ld + row0;
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int g = lane >> 4, li = lane & 15;
 
@@ -1062,9 +1073,7 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
       rb[i] = src[col0];
     }
   };
-  gload(0);
-  for (int kc = 0; kc < K; kc += KCH) {
-    if (kc) __syncthreads();   // every wave is done reading the buffer
+  auto stage = [&] {
 #pragma unroll
     for (int i = 0; i < E; ++i) {
       const int e = i * 256 + tid, pg = e / TM, s = bf_slot(e % TM);
@@ -1072,7 +1081,8 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
       Bs[pg][s] = rb[i];
     }
     __syncthreads();
-    if (kc + KCH < K) gload(kc + KCH);
+  };
+  auto chunk = [&] {
     bf8 xb[NP][BN];
 #pragma unroll
     for (int q = 0; q < NP; ++q)
@@ -1090,10 +1100,44 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
         for (int b = 0; b < BN; ++b)
           acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ya[QA[s]], xb[QB[s]][b], acc[a][b], 0, 0, 0);
     }
+  };
+  gload(0);
+  for (int kc = KCH; kc < K; kc += KCH) {
+    stage();
+    gload(kc);
+    chunk();
+    __syncthreads();   // every wave is done reading the buffer
   }
-  auto rl = [&](int a, int v) { return wm * WT + a * 16 + 4 * g + v; };
-  auto cl = [&](int b, int v) { (void)v; return wn * WT + b * 16 + li; };
-  subtract_tile<float, BM, BN>(Cg, ld, acc, rl, cl, row0 < col0 + TM, row0, col0);
+  stage();
+  // the tile is read behind the last chunk's products: element v of block (a, b) at
+  // row 16 a + v, column 16 b from the lane's first, four rows in 16 bytes
+  const TileBuf<float> Cb((float *)d.A + (size_t)(col0 + wn * WT) * ld + row0 + wm * WT);
+  const unsigned lds = ld * 4u, cl = (unsigned)((li * ld + 4 * g) * 4);
+  f4 c[BM][BN];
+#pragma unroll
+  for (int a = 0; a < BM; ++a)
+#pragma unroll
+    for (int b = 0; b < BN; ++b) c[a][b] = Cb.load16<f4>(cl, 16 * b * lds + 16 * a * 4u);
+  chunk();
+  const int below = row0 + wm * WT + 4 * g - (col0 + wn * WT + li);   // row - column of the first
+  if (row0 >= col0 + TM) {
+    // (as global stores: behind a 16-byte buffer store with a register offset the
+    // compiler rewrites the data registers at once, which has stored wrong values)
+    typedef __attribute__((address_space(1))) f4 gf4;
+    auto *Cg = gptr((float *)d.A) + (size_t)(col0 + wn * WT + li) * ld + row0 + wm * WT + 4 * g;
+#pragma unroll
+    for (int b = 0; b < BN; ++b)
+#pragma unroll
+      for (int a = 0; a < BM; ++a) *(gf4 *)(Cg + (size_t)(16 * b) * ld + 16 * a) = c[a][b] - acc[a][b];
+  } else {   // its lower triangle only
+#pragma unroll
+    for (int a = 0; a < BM; ++a)
+#pragma unroll
+      for (int b = 0; b < BN; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (below + 16 * (a - b) + v >= 0) Cb.store(c[a][b][v] - acc[a][b][v], cl, 16 * b * lds + (16 * a + v) * 4u);
+  }
 }
 
 // --------------------------------------------------------------------------
@@ -1137,7 +1181,8 @@ static double lower_real(const HostFactor &h, int c0, int c1, bool only_factored
   return s;
 }
 
-static int tiles_for(const FactorDesc &d, int kind, int p0, int nb, int TM) {
+// Workgroups of a trailing update (border: of its border rows alone, SEL 2).
+static int tiles_for(const FactorDesc &d, int kind, int p0, int nb, int TM, bool border = false) {
   if (p0 >= d.nf) return 0;
   const int pend = std::min(p0 + nb, d.nf);
   int r0, c0, cend;
@@ -1147,6 +1192,7 @@ static int tiles_for(const FactorDesc &d, int kind, int p0, int nb, int TM) {
   if (r0 >= d.nrows || c0 >= cend) return 0;
   const int nr = (d.nrows - r0) / TM;
   const int nc = (cend - c0) / TM;
+  if (border) return (d.nrows - d.nf) / TM * nc;
   return nc * (nc + 1) / 2 + (nr - nc) * nc;
 }
 
@@ -1305,12 +1351,13 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
   auto trail = [&](int p0, int kind) {
     const int act = active(p0);
     const int TT = planes ? 128 : tm;   // the BF16 units' kernels have 128 x 128 tiles only
-    int gx = 0;
+    int gx = 0, gx_border = 0;
     double fl = 0, by = 0, fl_q = 0, by_q = 0;   // all tiles; tiles of the factored rows only
     bool rows_q = false;                          // some theta has factored rows in the region
     for (int i = 0; i < act; ++i) {
       const HostFactor &h = fs[order[i]];
       gx = std::max(gx, tiles_for(h.d, kind, p0, nb, TT));
+      gx_border = std::max(gx_border, tiles_for(h.d, kind, p0, nb, TT, true));
       const int pend = std::min(p0 + nb, h.d.nf), pnext = std::min(pend + nb, h.d.nf);
       int c0 = pend, c1 = h.d.ncols;
       if (kind == KIND_TRAIL_A) c1 = pnext;
@@ -1327,6 +1374,7 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
       by_q += elq > 0 ? 2.0 * esz * elq + esz * (nrq + ncq) * kr : 0.0;
     }
     if (gx == 0) return;
+    gx_border = round_up(gx_border, 8);
     gx = round_up(gx, 8);   // xcd_order needs a grid of a multiple of 8 workgroups
     if (bf16_trail && f32) {
       // BF16 operands for the factored rows only: the border rows carry the
@@ -1337,12 +1385,13 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
           hipLaunchKernelGGL((trail_bf16_kernel<128, 128>), dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind, p0,
                              nb);
         });
+      if (gx_border == 0) return;
       ctx.launch(INLA_K_BORDER, fl - fl_q, by - by_q, [&] {
         if (planes == 3)
-          hipLaunchKernelGGL(trail_split_kernel<2>, dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind, p0, nb);
+          hipLaunchKernelGGL(trail_split_kernel<2>, dim3(gx_border, act), dim3(256), 0, ctx.stream, dd, kind, p0, nb);
         else
-          hipLaunchKernelGGL((gemm_update_kernel<T, 128, 128, 2>), dim3(gx, act), dim3(256), 0, ctx.stream, dd, kind,
-                             p0, nb);
+          hipLaunchKernelGGL((gemm_update_kernel<T, 128, 128, 2>), dim3(gx_border, act), dim3(256), 0, ctx.stream, dd,
+                             kind, p0, nb);
       });
     } else if (planes == 3) {
       ctx.launch(INLA_K_TRAIL, fl, by, [&] {
