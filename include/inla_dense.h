@@ -79,8 +79,9 @@ enum {
 /* Precision of the Newton and final-pass factorisations (extension to the
  * paper's FP64 method).
  *  FP64: everything in FP64.
- *  FP32: FP32 storage and FP32 MFMA (FP32 accumulate) for the blocked Cholesky
- *        of Q*.  The prior pass, the log-det sums, the k x k kriging system and
+ *  FP32: FP32 storage and accumulation for the blocked Cholesky of Q*; its
+ *        trailing updates multiply exact three-way BF16 splits of the FP32
+ *        operands (error of a product below half an FP32 rounding).  The prior pass, the log-det sums, the k x k kriging system and
  *        the residuals stay FP64.  Newton is run inexactly while far from the
  *        mode; once the previous step is below 1e-3 of the iterate's scale (and
  *        always for a Gaussian likelihood) the constrained (KKT) solve is refined
@@ -516,7 +517,7 @@ enum {
   INLA_K_ASSEMBLE = 3,  /* prior build, Q* / border assembly, likelihood                  */
   INLA_K_SOLVE = 4,     /* triangular solves, kriging system, reductions                  */
   INLA_K_BORDER = 5,    /* trailing update of the border rows when it runs apart from the
-                           factored rows (FP32 operands beside a BF16 trailing update) */
+                           factored rows (FP32 values beside a BF16 trailing update) */
   INLA_K_COUNT = 6
 };
 typedef struct inla_kstats {
@@ -569,7 +570,9 @@ int inla_set_lookahead(inla_handle *h, int32_t enable);
  * (one more FP64 bordered matrix of order n + k + 1, padded to 128, per
  * theta).  Events order the two streams; every call still returns with its
  * work complete on the handle's stream.  Results are identical with and
- * without overlap.  Returns -1 for a null handle. */
+ * without overlap.  The built priors' own prior pass (space x time, and
+ * exponential covariance with few constraints) factors no matrix of order n and
+ * always runs on the handle's stream.  Returns -1 for a null handle. */
 int inla_set_overlap(inla_handle *h, int32_t enable);
 /* Graphs captured and replayed so far by this handle (host outputs; either may be NULL). */
 int inla_graph_stats(inla_handle *h, int64_t *captured, int64_t *replays);
