@@ -37,6 +37,8 @@ struct FactorDesc {
   int nrows;       // multiple of PADN
   int ncols;       // nf <= ncols <= nrows, multiple of PADN
   int id_row0;     // first row of an identity border block (INT_MAX if none)
+  int ne;          // end of the block columns with real columns; beyond it [ne, nf) is
+                   // identity padding (set by factor_batch)
   // packed BF16 copies of the current panel for the trailing updates with BF16
   // MFMA, one or two slots (by panel parity).  An entry holds the eight values of
   // one row at k = p0 + 8 g .. p0 + 8 g + 7 (16 bytes, an MFMA operand); plane q,

@@ -273,12 +273,22 @@ __device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, const FactorDes
   if (tid == 0 && S.fail != 0 && *d.info == 0) *d.info = j + S.fail;
 }
 
+// Block column j is padding: its diagonal block is the identity, and so is the inverse.
+template <typename T> __device__ __forceinline__ void identity_inverse(const FactorDesc &d, int j, int tid) {
+  auto *Li = gptr((T *)d.linv) + (size_t)(j / NBI) * NBI * NBI;
+  for (int e = tid; e < NBI * NBI; e += 256) Li[e] = (T)(e / NBI == e % NBI ? 1 : 0);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void potf2_inv_kernel(const FactorDesc *__restrict__ descs, int j) {
   const FactorDesc d = descs[blockIdx.x];
   if (j >= d.nf) return;
   __shared__ Potf2Lds S;
   const int tid = threadIdx.x;
+  if (j >= d.ne) {
+    identity_inverse<T>(d, j, tid);
+    return;
+  }
   __attribute__((address_space(1))) T *Ad = gptr((T *)d.A) + (size_t)j * d.ld + j;
   // all 16 loads in flight before the first LDS store
   T v[NBI * NBI / 256];
@@ -693,10 +703,19 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
     }
   }
   const FactorDesc d = descs[th];
-  if (j >= d.nf) return;
+  // Padding takes no steps: its columns keep their zeros, ones of an identity border and
+  // identity block (half of all orders end in a block column of it)
+  if (j >= d.ne) {
+    if (t == 0 && j + NBI < min(p0 + nb, d.nf)) identity_inverse<T>(d, j + NBI, threadIdx.x);
+    return;
+  }
   const int pend = min(p0 + nb, d.nf);
   const int r0 = t < 0 ? j + 2 * NBI : j + NBI * (t + 1), c0 = t < 0 ? j + NBI : j;   // tile rows and columns
   if (r0 >= (t < 0 ? pend : d.nrows)) return;
+  if (r0 >= d.ne && r0 < d.nf) {   // padding rows: zero
+    if (t == 0 && r0 < pend) identity_inverse<T>(d, r0, threadIdx.x);
+    return;
+  }
   // (the step before updated this step's tile 0 up to block column j - 64)
   int ks = t == 0 && j >= p0 + 2 * NBI && r0 < pend ? j - NBI : p0;
   if (r0 >= d.id_row0) {
@@ -1223,7 +1242,11 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
   for (int i = 0; i < B; ++i) order[i] = i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fs[a].d.nf > fs[b].d.nf; });
   std::vector<FactorDesc> hd(B);
-  for (int i = 0; i < B; ++i) hd[i] = fs[order[i]].d;
+  for (int i = 0; i < B; ++i) {
+    hd[i] = fs[order[i]].d;
+    const int real = fs[order[i]].n_real;
+    hd[i].ne = real > 0 ? std::min(hd[i].nf, round_up(real, NBI)) : hd[i].nf;
+  }
   // Packed panel copies (FP32 storage): three planes where every theta brings the
   // memory for them and the tile is the split kernel's (from a padded order of 640
   // on, the second half of an evaluation's working matrix is enough), else one for
@@ -1292,11 +1315,13 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
         // product over [p0, j), the TRSM, the SYRK of each in-panel diagonal
         // block below and the next diagonal block's factorisation
         int gx = 0;
+        bool any = false;   // some theta has real columns here or a padding block after them
         double fl = 0, by = 0;
         for (int i = 0; i < act; ++i) {
           const HostFactor &h = fs[order[i]];
           gx = std::max(gx, (h.d.nrows - j - NBI) / NBI);
           const int pend = std::min(p0 + nb, h.d.nf);
+          any = any || j < hd[i].ne || j + NBI < pend;
           const double kr = std::max(0, std::min(NBI, h.n_real - j));
           const double kl = std::max(0, std::min(j, h.n_real) - p0);
           const double m = count_rows_real(h, j + NBI);
@@ -1309,7 +1334,7 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
             if (r == j + NBI) fl += 2.0 * kd * kd * kd / 3.0;
           }
         }
-        if (gx == 0) continue;
+        if (gx == 0 || !any) continue;
         const int Q = (act * (gx - 1) + 7) / 8;
         const int pre = j > p0 && j + 2 * NBI < p0 + nb ? 1 : 0;
         ctx.launch(INLA_K_PANEL, fl, by, [&] {
