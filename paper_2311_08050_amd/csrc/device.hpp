@@ -42,9 +42,10 @@ struct FactorDesc {
   // packed BF16 copies of the current panel for the trailing updates with BF16
   // MFMA, one or two slots (by panel parity).  An entry holds the eight values of
   // one row at k = p0 + 8 g .. p0 + 8 g + 7 (16 bytes, an MFMA operand); plane q,
-  // group g, row r is entry pbf[slot + (q G + g) prows + r] (G = nb / 8 groups).
-  // One plane: the values rounded to BF16, rows [p0 + nb, nf).  Three planes: hi,
-  // mid and lo parts that add up to the FP32 value, rows [p0 + nb, nrows).
+  // group g, row r >= pend (the panel's end, packed_panel) is entry
+  // pbf[slot + (q G + g) prows + r - pend], G = min(nb, nf) / 8 groups.
+  // One plane: the values rounded to BF16, rows [pend, nf).  Three planes: hi,
+  // mid and lo parts that add up to the FP32 value, rows [pend, nrows).
   int prows;
   void *pbf;
   int64_t pbf_slot;  // entries from one slot to the other (0: one slot)

@@ -21,7 +21,8 @@ struct HostFactor {
   int kb_real;   // real border rows starting at row nf
   int ks_real;   // real Schur columns starting at column nf
   // device memory the factorisation may use for packed panel copies (FP32 and
-  // BF16; null: none beyond the handle's own for one BF16 plane)
+  // BF16; null: none beyond the handle's own for one BF16 plane), 4 nrows^2 bytes
+  // at least
   char *pack;
   size_t pack_bytes;
 };

@@ -925,6 +925,13 @@ typedef __attribute__((address_space(1))) const bf8 gcbf8;
 
 __device__ __forceinline__ int bf_slot(int r) { return r ^ ((r >> 4) & 3); }
 
+// Packed copy of the panel at p0: the address that row 0 of its first group would
+// have (the copy starts at the panel's end), and the groups of a plane.
+__device__ __forceinline__ bf8 *packed_panel(const FactorDesc &d, int p0, int nb) {
+  return (bf8 *)d.pbf + (int64_t)((p0 / nb) & 1) * d.pbf_slot - min(p0 + nb, d.nf);
+}
+__device__ __forceinline__ int packed_groups(const FactorDesc &d, int nb) { return min(nb, d.nf) / 8; }
+
 // Packed copy of the panel [p0, pend): one thread per (row, group of eight k),
 // one plane (rows [pend, nf)) or three (rows [pend, nrows)).
 template <int PLANES>
@@ -937,7 +944,7 @@ __global__ __launch_bounds__(256) void panel_pack_kernel(const FactorDesc *__res
   float v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = src[(size_t)i * d.ld];
-  bf8 *dst = (bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot + (size_t)gk * d.prows + r;
+  bf8 *dst = packed_panel(d, p0, nb) + (size_t)gk * d.prows + r;
 #pragma unroll
   for (int q = 0; q < PLANES; ++q) {
     bf8 e;
@@ -946,7 +953,7 @@ __global__ __launch_bounds__(256) void panel_pack_kernel(const FactorDesc *__res
       e[i] = (__bf16)v[i];       // round to nearest even
       v[i] -= (float)e[i];       // exact
     }
-    *gptr(dst + (size_t)q * (nb / 8) * d.prows) = e;
+    *gptr(dst + (size_t)q * packed_groups(d, nb) * d.prows) = e;
   }
 }
 
@@ -967,7 +974,7 @@ __global__ __launch_bounds__(256, 2) void trail_bf16_kernel(const FactorDesc *__
   if (!update_tile(d, kind, p0, nb, TM, TN, 1, bx, row0, col0, ks, ke)) return;
   const int ld = d.ld;
   // the packed panel: entry (group g, row r) at P[g * prows + r]; k = ks + 8 g
-  gcbf8 *P = gptr((const bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot);
+  gcbf8 *P = gptr((const bf8 *)packed_panel(d, p0, nb));
   gT *Cg = gptr((float *)d.A) + (size_t)col0 * ld + row0;
   const int K = ke - ks, prows = d.prows;
 
@@ -1070,7 +1077,8 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
   int row0, col0, ks, ke;
   if (!update_tile(d, kind, p0, nb, TM, TM, SEL, bx, row0, col0, ks, ke)) return;
   const int ld = d.ld, prows = d.prows, K = ke - ks;
-  gcbf8 *P = gptr((const bf8 *)d.pbf + (size_t)((p0 / nb) & 1) * d.pbf_slot);
+  const int G = packed_groups(d, nb);
+  gcbf8 *P = gptr((const bf8 *)packed_panel(d, p0, nb));
 
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 1, wn = w & 1;
@@ -1087,7 +1095,7 @@ __global__ __launch_bounds__(256, 2) void trail_split_kernel(const FactorDesc *_
 #pragma unroll
     for (int i = 0; i < E; ++i) {
       const int e = i * 256 + tid, pg = e / TM, er = e % TM;   // pg = plane KG + group
-      gcbf8 *src = P + (size_t)((pg / KG) * (nb / 8) + kc / 8 + pg % KG) * prows + er;
+      gcbf8 *src = P + (size_t)((pg / KG) * G + kc / 8 + pg % KG) * prows + er;
       ra[i] = src[row0];
       rb[i] = src[col0];
     }
@@ -1247,22 +1255,35 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
     const int real = fs[order[i]].n_real;
     hd[i].ne = real > 0 ? std::min(hd[i].nf, round_up(real, NBI)) : hd[i].nf;
   }
-  // Packed panel copies (FP32 storage): three planes where every theta brings the
-  // memory for them and the tile is the split kernel's (from a padded order of 640
-  // on, the second half of an evaluation's working matrix is enough), else one for
-  // BF16 updates.  A tuned 64 x 64 tile keeps the FP32 units.
+  // Lookahead: the next panel's columns are updated first (TRAIL_A, on the
+  // caller's stream), the rest (TRAIL_B) on the handle's side stream, and the
+  // next panel is factored on the caller's stream while TRAIL_B runs.  TRAIL_A
+  // of the following panel waits for TRAIL_B, which updated its columns too.
+  // (lookahead runs on the caller's lane only: the side stream and its events
+  // serve one factorisation at a time)
+  // (and not inside a pass graph, which is captured on one stream)
+  const bool look = look_cfg && ctx.lookahead && ctx.lane == 0 && ctx.pg_mode == Ctx::PG_OFF && hd[0].nf > nb &&
+                    ctx.side_ready() == INLA_OK;
+  // Packed panel copies (FP32 storage): three planes where the caller brings memory for
+  // them and the tile is the split kernel's, else one for BF16 updates.  A tuned 64 x 64
+  // tile keeps the FP32 units.  Which kernel multiplies is thus fixed by the caller and
+  // the configuration alone: not by an order, by the rest of the batch or by lookahead,
+  // so that the results don't depend on those.  Two slots of m = min(nb, nf) columns by
+  // nrows - m rows take 12 m (nrows - m) <= 3 nrows^2 bytes; the half of an evaluation's
+  // region that its FP32 matrix leaves free holds 4 nrows^2.
   const bool f32 = std::is_same<T, float>::value;
-  const int slots = look_cfg && ctx.lookahead && ctx.lane == 0 && ctx.pg_mode == Ctx::PG_OFF ? 2 : 1;
-  auto plane = [&](int i) { return (size_t)(nb / 8) * hd[i].nrows; };   // entries
   int planes = f32 && (bf16_trail || tm == 128) ? 3 : 0;
   for (int i = 0; i < B && planes == 3; ++i)
-    if (!fs[order[i]].pack || 16 * 3 * slots * plane(i) > fs[order[i]].pack_bytes) planes = 0;
+    if (!fs[i].pack) planes = 0;
   if (f32 && bf16_trail && planes == 0) planes = 1;
   if (planes == 3) {
     for (int i = 0; i < B; ++i) {
+      const int m = std::min(nb, hd[i].nf);
+      hd[i].prows = hd[i].nrows - m;
+      const size_t slot = (size_t)3 * (m / 8) * hd[i].prows;
       hd[i].pbf = fs[order[i]].pack;
-      hd[i].pbf_slot = slots == 2 ? (int64_t)(3 * plane(i)) : 0;
-      hd[i].prows = hd[i].nrows;
+      hd[i].pbf_slot = look && hd[i].nf > nb ? (int64_t)slot : 0;
+      if (16 * (slot + hd[i].pbf_slot) > fs[order[i]].pack_bytes) return INLA_ERR_NOMEM;
     }
   } else if (planes == 1) {
     // two slots of the packed BF16 panel copy per theta (16-byte entries)
@@ -1440,15 +1461,6 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
       });
     }
   };
-  // Lookahead: the next panel's columns are updated first (TRAIL_A, on the
-  // caller's stream), the rest (TRAIL_B) on the handle's side stream, and the
-  // next panel is factored on the caller's stream while TRAIL_B runs.  TRAIL_A
-  // of the following panel waits for TRAIL_B, which updated its columns too.
-  // (lookahead runs on the caller's lane only: the side stream and its events
-  // serve one factorisation at a time)
-  // (and not inside a pass graph, which is captured on one stream)
-  const bool look = look_cfg && ctx.lookahead && ctx.lane == 0 && ctx.pg_mode == Ctx::PG_OFF && nf_max > nb &&
-                    ctx.side_ready() == INLA_OK;
   int rc = 0;
   hipStream_t main_stream = ctx.stream;
   for (int p0 = 0; p0 < nf_max && !rc; p0 += nb) {
