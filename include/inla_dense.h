@@ -602,7 +602,8 @@ int inla_pass_graph_stats(inla_handle *h, int64_t *captured, int64_t *replays);
  * inla_set_lookahead).  inla_autotune times the factorisation of a synthetic
  * symmetric positive definite batch shaped like B matrices of orders n[b]
  * with kb[b] border rows (host arrays; kb = k + 1 for the Newton and final
- * passes of a model with k constraints): every (nb, tm) without lookahead in
+ * passes of a model with k constraints, timed with an evaluation's kernels; 0
+ * for inla_logdet): every (nb, tm) without lookahead in
  * the order (128,64), (128,128), (256,64), ..., (1024,128) (BF16: the four nb
  * with tm = 128), then the fastest of them with lookahead (unless lookahead is
  * turned off), one untimed and `reps` timed runs each.  It records the fastest

@@ -1553,8 +1553,7 @@ int autotune(Ctx &ctx, int B, const int *n, const int *kb, int prec, int reps, T
              int *n_cand) {
   const size_t esz = prec == INLA_PREC_FP64 ? 8 : 4;
   std::vector<HostFactor> fs(B);
-  std::vector<size_t> offs(B);
-  size_t total = 0;
+  std::vector<size_t> offs(B), offp(B);
   int nf_max = 0;
   for (int i = 0; i < B; ++i) {
     HostFactor &h = fs[i];
@@ -1564,15 +1563,31 @@ int autotune(Ctx &ctx, int B, const int *n, const int *kb, int prec, int reps, T
     h.d.id_row0 = std::numeric_limits<int>::max();
     h.n_real = n[i]; h.kb_real = kb[i] > 0 ? kb[i] : 0; h.ks_real = h.kb_real;
     nf_max = std::max(nf_max, nf);
-    offs[i] = total;
-    total += (esz * (size_t)h.d.ld * h.d.ncols + esz * (size_t)nf * NBI + sizeof(int) + 255) & ~size_t(255);
   }
-  if (!ctx.reserve(total)) return INLA_ERR_NOMEM;
+  // A bordered batch stands for an evaluation's, whose FP32 and BF16 updates have memory
+  // for packed panel copies and so multiply on split operands: timed without it, nine of
+  // order 3000 in FP32 chose 64 x 64 tiles on the FP32 units, which take the evaluation
+  // 20.4 ms and not 19.7.  (Without room for it, where the evaluation itself would go in
+  // pieces, the batch is timed without.)
+  auto layout = [&](bool pack) {
+    size_t total = 0;
+    for (int i = 0; i < B; ++i) {
+      HostFactor &h = fs[i];
+      offs[i] = total;
+      total += (esz * (size_t)h.d.ld * h.d.ncols + esz * (size_t)h.d.nf * NBI + sizeof(int) + 255) & ~size_t(255);
+      offp[i] = total;
+      total += h.pack_bytes = pack && kb[i] > 0 ? 4 * (size_t)h.d.nrows * h.d.nrows : 0;
+    }
+    return total;
+  };
+  const bool pack = prec != INLA_PREC_FP64;
+  if (!(pack && ctx.reserve(layout(true))) && !ctx.reserve(layout(false))) return INLA_ERR_NOMEM;
   for (int i = 0; i < B; ++i) {
     char *base = ctx.ws + offs[i];
     fs[i].d.A = base;
     fs[i].d.linv = base + esz * (size_t)fs[i].d.ld * fs[i].d.ncols;
     fs[i].d.info = (int *)((char *)fs[i].d.linv + esz * (size_t)fs[i].d.nf * NBI);
+    if (fs[i].pack_bytes) fs[i].pack = ctx.ws + offp[i];
   }
   std::vector<FactorDesc> hd(B);
   int cmax = 0;
