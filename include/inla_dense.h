@@ -572,7 +572,9 @@ int inla_set_lookahead(inla_handle *h, int32_t enable);
  * work complete on the handle's stream.  Results are identical with and
  * without overlap.  The built priors' own prior pass (space x time, and
  * exponential covariance with few constraints) factors no matrix of order n and
- * always runs on the handle's stream.  Returns -1 for a null handle. */
+ * always runs on the handle's stream; a prior that is singular to the rounding
+ * of Q_prior is left to Q_prior's own factorisation, which decides its status.
+ * Returns -1 for a null handle. */
 int inla_set_overlap(inla_handle *h, int32_t enable);
 /* Graphs captured and replayed so far by this handle (host outputs; either may be NULL). */
 int inla_graph_stats(inla_handle *h, int64_t *captured, int64_t *replays);

@@ -222,19 +222,34 @@ __global__ __launch_bounds__(256) void expcov_schur_kernel(const ThetaDesc *__re
   }
 }
 
-// log|Q_prior| from the factors' diagonals (all M_i, or Sigma).
+// log|Q_prior| from the factors' diagonals (all M_i, or Sigma); not a number where
+// Q_prior is singular to the rounding of its own factorisation, which then decides
+// (the caller takes the general pass).  Cholesky of Q_prior breaks down when its
+// smallest eigenvalue is within a few n eps of its largest element; the pass here
+// never forms that matrix and would accept any delta above zero, or points a rounding
+// apart.  In units of tau the eigenvalue is delta (KRON, by R_t's null vector) or at least
+// 1 / n (EXPCOV, Sigma's elements being at most 1), and the largest element
+// max R_t max (Sigma^{-1})_ii + delta.  The general pass refuses, a pivot or the rank of
+// the constraints, up to 3 n eps (orders 60 to 3000); the line is at 16.
 __global__ __launch_bounds__(256) void structured_logdet_kernel(const ThetaDesc *__restrict__ td) {
   const ThetaDesc t = td[blockIdx.x];
   __shared__ double sh[4];
   const bool kron = t.prior == PRIOR_KRON;
-  double s = 0.0;
+  double s = 0.0, big = 0.0;
   for (int i = threadIdx.x; i < t.n; i += 256) {
     const double *A = kron ? t.K + (size_t)(i / t.n_s) * t.kN * t.kN : t.P;
     const int c = kron ? i % t.n_s : i, ld = kron ? t.kN : t.ldp;
     s += log(A[(size_t)c * ld + c]);
+    // P's Schur block: -Sigma^{-1}
+    if (i < t.n_s) big = fmax(big, -t.P[(size_t)(t.ns_pad + i) * (t.ldp + 1)]);
   }
   s = block_sum256(s, sh);
-  if (threadIdx.x == 0) t.dres[DRES_LOGDET_L] = kron ? 2.0 * s : t.n * log(t.tau) - 2.0 * s;
+  big = block_max256(big, sh);
+  if (threadIdx.x != 0) return;
+  const double low = kron ? t.delta : 1.0 / t.n;
+  const double top = kron ? min(t.n_t - 1, 2) * big + t.delta : big;
+  if (!(low > 16.0 * t.n * 2.220446049250313e-16 * top)) s = __builtin_nan("");
+  t.dres[DRES_LOGDET_L] = kron ? 2.0 * s : t.n * log(t.tau) - 2.0 * s;
 }
 
 __device__ __forceinline__ void lik_point_at(const ThetaDesc &t, int i, double x, double &g, double &W, double &ll) {
