@@ -62,8 +62,7 @@ int Ctx::sync_all() {
 // caller's stream, the side stream and the aux stream.
 static bool ring_wrap(Ctx &c) {
   if (c.sync_all() != INLA_OK) return false;
-  c.ring_off = 0;
-  c.recent.clear();
+  c.places.start_over();
   return true;
 }
 
@@ -98,30 +97,26 @@ void *Ctx::upload(const void *src, size_t bytes) {
     pg.sig.push_back(-(int64_t)bytes);
     return pg.dbase + off;
   }
-  if (padded > ring_size) return nullptr;
-  for (const Recent &r : recent)
-    if (r.bytes == bytes && r.stream == stream && std::memcmp(ring_host + r.off, src, bytes) == 0) return ring + r.off;
-  if (ring_off + padded > ring_size && !ring_wrap(*this)) return nullptr;
-  if (recent.size() >= 8) recent.erase(recent.begin());
-  recent.push_back({ring_off, bytes, stream});
-  std::memcpy(ring_host + ring_off, src, bytes);
-  void *dst = ring + ring_off;
-  if (hipMemcpyAsync(dst, ring_host + ring_off, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) {
-    recent.pop_back();
+  if (padded > places.size) return nullptr;
+  size_t at;
+  if (places.find(ring_host, src, bytes, stream, at)) return ring + at;
+  if (!places.fits(padded) && !ring_wrap(*this)) return nullptr;
+  at = places.take(padded, bytes, stream, true);
+  std::memcpy(ring_host + at, src, bytes);
+  if (hipMemcpyAsync(ring + at, ring_host + at, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) {
+    places.recent.pop_back();
     return nullptr;
   }
-  ring_off += padded;
-  return dst;
+  return ring + at;
 }
 
 int Ctx::upload_to(void *dst, const void *src, size_t bytes) {
   const size_t padded = align256(bytes);
-  if (padded > ring_size) return INLA_ERR_NOMEM;
-  if (ring_off + padded > ring_size && !ring_wrap(*this)) return INLA_ERR_HIP;
-  std::memcpy(ring_host + ring_off, src, bytes);
-  if (hipMemcpyAsync(dst, ring_host + ring_off, bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return INLA_ERR_HIP;
-  ring_off += padded;
-  return INLA_OK;
+  if (padded > places.size) return INLA_ERR_NOMEM;
+  if (!places.fits(padded) && !ring_wrap(*this)) return INLA_ERR_HIP;
+  const size_t at = places.take(padded, bytes, stream, false);
+  std::memcpy(ring_host + at, src, bytes);
+  return hipMemcpyAsync(dst, ring_host + at, bytes, hipMemcpyHostToDevice, stream) == hipSuccess ? INLA_OK : INLA_ERR_HIP;
 }
 
 static constexpr size_t GRAPH_CACHE_MAX = 1024;
@@ -1592,9 +1587,9 @@ int inla_create(inla_handle **h, void *stream) {
   // the no-allocation entry point's scratch on this device (its failure is
   // reported by that entry point, not here)
   (void)noalloc_init_device(p->ctx.device);
-  p->ctx.ring_size = (size_t)16 << 20;
-  if (hipMalloc(&p->ctx.ring, p->ctx.ring_size) != hipSuccess ||
-      hipHostMalloc(&p->ctx.ring_host, p->ctx.ring_size) != hipSuccess) {
+  p->ctx.places.size = (size_t)16 << 20;
+  if (hipMalloc(&p->ctx.ring, p->ctx.places.size) != hipSuccess ||
+      hipHostMalloc(&p->ctx.ring_host, p->ctx.places.size) != hipSuccess) {
     delete p;
     return INLA_ERR_NOMEM;
   }

@@ -11,6 +11,7 @@
 
 #include "../../include/inla_dense.h"
 #include "device.hpp"
+#include "ring.hpp"
 
 namespace inla {
 
@@ -41,11 +42,7 @@ struct Ctx {
   // descriptor upload ring (device) and pinned staging (host)
   char *ring = nullptr;
   char *ring_host = nullptr;
-  size_t ring_size = 0, ring_off = 0;
-  // the latest uploads since the ring last wrapped: the same bytes on the same
-  // stream again take the earlier copy (ring contents stay until the wrap)
-  struct Recent { size_t off, bytes; hipStream_t stream; };
-  std::vector<Recent> recent;
+  UploadRing places;
   // pinned host staging of results, grow-only (slot 0: the main batch, 1: the
   // concurrent prior pass)
   void *pin[2] = {nullptr, nullptr};
@@ -141,7 +138,8 @@ struct Ctx {
   uint64_t tune_epoch = 0;   // counts changes of `tune` (pass graph keys carry it)
 
   // Copy a small host array to device memory through the ring; returns the device
-  // pointer (valid for work enqueued after this call on `stream`).
+  // pointer (valid for work enqueued on `stream` after this call and before another
+  // 3 / 4 of the ring, 12 MB, has been uploaded).
   void *upload(const void *src, size_t bytes);
   // Copy a small host array into device memory `dst` through the pinned ring
   // (stream-ordered on `stream`).
