@@ -1229,7 +1229,6 @@ static int eval_chunk(Ctx &ctx, int B, const inla_model *models, const double *t
       if ((rc = structured_prior(b, str))) return fail(rc);
       if ((rc = readback(b))) return fail(rc);
       bool refused = false;
-      std::vector<int> build;
       for (int i : str) {
         // any failure is left to the general pass, which names the failing minor
         // of Q_prior itself

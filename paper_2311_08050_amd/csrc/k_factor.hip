@@ -285,10 +285,6 @@ __global__ __launch_bounds__(256) void potf2_inv_kernel(const FactorDesc *__rest
   if (j >= d.nf) return;
   __shared__ Potf2Lds S;
   const int tid = threadIdx.x;
-  if (j >= d.ne) {
-    identity_inverse<T>(d, j, tid);
-    return;
-  }
   __attribute__((address_space(1))) T *Ad = gptr((T *)d.A) + (size_t)j * d.ld + j;
   // all 16 loads in flight before the first LDS store
   T v[NBI * NBI / 256];
@@ -705,10 +701,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 3) void panel_step_kernel
   const FactorDesc d = descs[th];
   // Padding takes no steps: its columns keep their zeros, ones of an identity border and
   // identity block (half of all orders end in a block column of it)
-  if (j >= d.ne) {
-    if (t == 0 && j + NBI < min(p0 + nb, d.nf)) identity_inverse<T>(d, j + NBI, threadIdx.x);
-    return;
-  }
+  if (j >= d.ne) return;
   const int pend = min(p0 + nb, d.nf);
   const int r0 = t < 0 ? j + 2 * NBI : j + NBI * (t + 1), c0 = t < 0 ? j + NBI : j;   // tile rows and columns
   if (r0 >= (t < 0 ? pend : d.nrows)) return;
@@ -1336,13 +1329,13 @@ static int factor_batch_t(Ctx &ctx, const std::vector<HostFactor> &fs, int nb, i
         // product over [p0, j), the TRSM, the SYRK of each in-panel diagonal
         // block below and the next diagonal block's factorisation
         int gx = 0;
-        bool any = false;   // some theta has real columns here or a padding block after them
+        bool any = false;   // some theta has real columns here
         double fl = 0, by = 0;
         for (int i = 0; i < act; ++i) {
           const HostFactor &h = fs[order[i]];
           gx = std::max(gx, (h.d.nrows - j - NBI) / NBI);
           const int pend = std::min(p0 + nb, h.d.nf);
-          any = any || j < hd[i].ne || j + NBI < pend;
+          any = any || j < hd[i].ne;
           const double kr = std::max(0, std::min(NBI, h.n_real - j));
           const double kl = std::max(0, std::min(j, h.n_real) - p0);
           const double m = count_rows_real(h, j + NBI);
