@@ -4,15 +4,13 @@ Workload: the n = 8192 Poisson space x time interaction model (128 regions x 64
 times, Q_prior = tau (R_t kron Sigma_s(rho)^{-1} + delta I), k = 191 independent
 sum-to-zero constraints), a batch of 64 theta ~ N(theta0, 0.5^2 I).  One step =
 one inla_laplace_eval over the batch (prior build, FP64 prior pass, Newton
-iterations with kriging, final pass at the mode, objective; the prior pass runs
-beside the Newton iterations on a second stream of the handle unless
---no-overlap).  Inputs are synthetic (seeded) and resident in HBM before the
-timed region.
+iterations with kriging, final pass at the mode, objective).  Inputs are
+synthetic (seeded) and resident in HBM before the timed region.
 
 Variants (each timed separately, same batch):
   fp64        FP64 everywhere, Newton from x = 0
-  fp32        FP32-storage FP32-MFMA factorisations of Q* with FP64 refinement,
-              Newton from x = 0
+  fp32        FP32 factorisations of Q* (trailing updates on split BF16 operands)
+              with FP64 refinement, Newton from x = 0
   bf16        as fp32, but the unrefined Newton steps factor with BF16 trailing
               operands (FP32 accumulation)
   fp32+mlp,   as fp32 / bf16, Newton started from the learned warm start (the
@@ -135,8 +133,6 @@ def run_variant(lib, binding, dms, thetas, xs, variant, steps, warmup, warm=None
     prec = variant.split("+")[0]
 
     def tname(p):   # the trailing kernel at the tile the handle uses for this batch
-        # (the space x time prior pass factors its n_t small systems on the caller's
-        # stream, overlap or not)
         return trail_kernel_name(p, lib.tune_get(p, dms[0].n, len(dms))[1], split=True)
 
     def peak_of(p):
@@ -694,14 +690,11 @@ def main():
     ap.add_argument("--no-autotune", action="store_true",
                     help="factor with the default panel width and tile instead of tuning them first")
     ap.add_argument("--no-graphs", action="store_true", help="launch every kernel directly (no hipGraph replays)")
-    ap.add_argument("--no-overlap", action="store_true",
-                    help="run each evaluation's FP64 prior pass in order instead of beside the Newton iteration "
-                         "(inla_set_overlap; on by default here: +3.7%% at the headline)")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the separately timed marginal-variance, VB-correction and Stage-1 figures")
     ap.add_argument("--timed-only", action="store_true",
-                    help="skip the headline's second timings (prior pass in order, unprofiled), so that the "
-                         "variants' timed regions are the last dispatches of a profiled run")
+                    help="skip the headline's second timing (unprofiled), so that the variants' timed regions are "
+                         "the last dispatches of a profiled run")
     ap.add_argument("--rocprof-window", metavar="CSV",
                     help="only summarise a rocprofv3 per-dispatch CSV over the timed region of --bench-json")
     ap.add_argument("--bench-json", metavar="FILE", help="the JSON line printed by the profiled bench run")
@@ -758,7 +751,7 @@ def main():
     variants = [v.strip() for v in args.variants.split(",") if v.strip()]
     if args.no_graphs:
         lib.set_graphs(False)
-    lib.set_overlap(not args.no_overlap)
+    lib.set_overlap(True)   # for the extras with dense priors; the headline's prior has nothing to overlap
     tuning = {}
     if not args.no_autotune:
         # one-time setup, not timed: the tuner factors synthetic batches of the
@@ -794,18 +787,6 @@ def main():
         results[v] = run_variant(lib, binding, dms, thetas, xs, v, args.steps, args.warmup, warm)
     head = variants[-1]
     hv = results[head]
-    in_order = None
-    if not args.no_overlap and not args.timed_only:
-        # the headline variant once more with the prior pass in order: the
-        # trailing kernel's own rate, which the concurrent prior pass stretches
-        lib.set_overlap(False)
-        w = max(3, args.steps // 4)
-        r = run_variant(lib, binding, dms, thetas, xs, head, w, 1, warm)
-        lib.set_overlap(True)
-        in_order = {"value": r["value"], "ms_per_step": r["ms_per_step"], "steps": w,
-                    "newton_iters": r["newton_iters"], "kernel_time_ms": r["kernel_time_ms"],
-                    "roofline": {k: r["roofline"][k] for k in ("achieved", "peak", "unit", "frac", "launches",
-                                                               "avg_launch_ms")}}
     unprofiled = None
     if not args.no_graphs and not args.timed_only:
         # the headline variant without per-launch events, with and without the
@@ -832,11 +813,6 @@ def main():
             roof["traffic_basis"] = (f"HBM bytes per launch = this run's algorithmic bytes per launch x the ratio of "
                                      f"FETCH_SIZE + WRITE_SIZE (copy-calibrated) to algorithmic bytes in "
                                      f"profiles/{os.path.basename(summary)}")
-    if in_order is not None:
-        # the same kernel's rate in the in-order repeat of the headline (the
-        # figure above is measured beside the concurrent prior pass, with which
-        # it shares the MFMA units)
-        hv["roofline"]["frac_prior_pass_in_order"] = in_order["roofline"]["frac"]
     out = {
         "metric": METRIC,
         "value": hv["value"],
@@ -857,12 +833,10 @@ def main():
             "n": n, "k": k, "batch": args.batch, "variant": head,
         },
         "roofline": hv["roofline"],
-        "headline_prior_pass_in_order": in_order,
         "headline_unprofiled": unprofiled,
         "variants": results,
         "autotune": tuning or None,
         "graphs": not args.no_graphs,
-        "overlap": not args.no_overlap,
     }
     if train_info is not None:
         out["warm_start_training"] = dict(train_info, **MLP_TRAIN)

@@ -473,7 +473,8 @@ __global__ __launch_bounds__(256) void kriging_build_kernel(const ThetaDesc *__r
 // A lane keeps one row of 16 columns, so both products come from the registers that
 // were loaded, and only their sums cross lanes, once per workgroup.  HBM-bound; four
 // tiles, since one workgroup per block column leaves the longest to run alone: at
-// order 16384, two, 724 to 279 us (7.7 TB/s); 25 of 1024 44 to 16 us.
+// order 16384, over a run's launches for two theta and for one, 724 to 279 us on average
+// (two 442 us, 4.9 TB/s; 25 of order 8192 1.36 ms, 4.9 TB/s); 25 of 1024 44 to 16 us.
 // src 0: v = xn (refinement residuals); 1: v = x (objective terms).
 constexpr int SYMV_TILES = 4;
 __device__ __forceinline__ int symv_splits(int np, int J) { return (np / 64 - J + SYMV_TILES - 1) / SYMV_TILES; }

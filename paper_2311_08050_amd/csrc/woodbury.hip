@@ -47,9 +47,9 @@ constexpr int JAC_MAX_N = 16384;
 // One inner sweep per block pair and round: the outer rounds carry the
 // convergence, and an inexact inner solve keeps each pair's rotation product
 // orthogonal, so the method stays exact while each round costs one inner sweep
-// instead of the 2-6 a converged inner solve takes.  Measured at n = 3000 and
-// on the order-1000 Kronecker block of the Type IV prior: 35 and 45 outer
-// sweeps, 1.8 and 3.8 times faster than converged inner solves.
+// instead of the 2-6 a converged inner solve takes: 1.8 times faster at n = 3000 and
+// 3.8 on the order-1000 Kronecker block of the Type IV prior, measured with the
+// earlier kernels (35 and 45 outer sweeps); they take 25 and 36 now.
 constexpr int JAC_MAX_SWEEPS = 120;
 constexpr int JAC_INNER_SWEEPS = 1;
 constexpr double JAC_RTOL_DEFAULT = 1e-9;
