@@ -69,7 +69,7 @@ constexpr int GKC = 32, GLD = 66;   // GLD: conflict-free reads of k = 8 gq + st
 // thread's elements (groups of W = 4 along the contiguous index in 16-byte loads, or
 // W = 1) fixed for the whole product.  Indices past the operand are clamped, so that
 // no load is conditional; values past nx belong to outputs that are not stored.
-constexpr int GPF = 4;   // chunks whose loads are in flight
+constexpr int GPF = 4;   // chunks whose loads are in flight (PF; 1 for a product of one chunk, see gemm())
 template <int W> struct TileLoad {
   static constexpr int NL = GKC * 64 / 256 / W;
   const float __attribute__((address_space(1))) *row[NL];
@@ -110,7 +110,7 @@ template <int W> struct TileLoad {
   }
 };
 
-template <int EPI, int W>
+template <int EPI, int W, int PF>
 __global__ __launch_bounds__(256) void mlp_gemm_kernel(GemmArgs g, float *part, int kper) {
   __shared__ float S[4][GKC][GLD];   // A and B, two buffers each; the product's tile
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -120,30 +120,30 @@ __global__ __launch_bounds__(256) void mlp_gemm_kernel(GemmArgs g, float *part, 
   TileLoad<W> A, B;
   A.init(g.A, g.sar, g.sac, i0, g.M, ke);
   B.init(g.B, g.sbc, g.sbr, j0, g.N, ke);
-  float ra[GPF][8], rb[GPF][8];
+  float ra[PF][8], rb[PF][8];
   f4m acc2[2][2][2];   // even and odd chunks: shorter chains of rounded sums
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc2[0][a][b] = acc2[1][a][b] = f4m{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int u = 0; u < GPF; ++u)
+  for (int u = 0; u < PF; ++u)
     if (kb + u * GKC < ke) {
       A.load(kb + u * GKC, ra[u]);
       B.load(kb + u * GKC, rb[u]);
     }
-  for (int k1 = kb; k1 < ke; k1 += GPF * GKC)
+  for (int k1 = kb; k1 < ke; k1 += PF * GKC)
 #pragma unroll
-    for (int u = 0; u < GPF; ++u) {
+    for (int u = 0; u < PF; ++u) {
       const int k0 = k1 + u * GKC;
       if (k0 >= ke) break;
       // a buffer is written again two chunks on: every wave has passed the barrier of
       // the chunk between, so it has read this one
       A.store(k0, ke, ra[u], &S[2 * (u & 1)][0][0]);
       B.store(k0, ke, rb[u], &S[2 * (u & 1) + 1][0][0]);
-      if (k0 + GPF * GKC < ke) {
-        A.load(k0 + GPF * GKC, ra[u]);
-        B.load(k0 + GPF * GKC, rb[u]);
+      if (k0 + PF * GKC < ke) {
+        A.load(k0 + PF * GKC, ra[u]);
+        B.load(k0 + PF * GKC, rb[u]);
       }
       __syncthreads();
 #pragma unroll
@@ -410,13 +410,20 @@ void gemm(inla_mlp *m, hipStream_t s, const GemmArgs &g) {
   auto launch = [&](auto epi) {
     constexpr int E = decltype(epi)::value;
     if (ks == 1) {
-      if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<E, 4>), grid, dim3(256), 0, s, g, nullptr, kper);
-      else hipLaunchKernelGGL((mlp_gemm_kernel<E, 1>), grid, dim3(256), 0, s, g, nullptr, kper);
+      // one chunk: the kernel without its pipeline, whose unrolled code a launch of one
+      // workgroup waits for (4-16-33 network, one row: 31.2 to 28.7 us for the three)
+      if (kper <= GKC) {
+        if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<E, 4, 1>), grid, dim3(256), 0, s, g, nullptr, kper);
+        else hipLaunchKernelGGL((mlp_gemm_kernel<E, 1, 1>), grid, dim3(256), 0, s, g, nullptr, kper);
+      } else {
+        if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<E, 4, GPF>), grid, dim3(256), 0, s, g, nullptr, kper);
+        else hipLaunchKernelGGL((mlp_gemm_kernel<E, 1, GPF>), grid, dim3(256), 0, s, g, nullptr, kper);
+      }
       return;
     }
     const int64_t cnt = (int64_t)g.M * g.N;
-    if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 4>), grid, dim3(256), 0, s, g, m->kpart, kper);
-    else hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 1>), grid, dim3(256), 0, s, g, m->kpart, kper);
+    if (vec) hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 4, GPF>), grid, dim3(256), 0, s, g, m->kpart, kper);
+    else hipLaunchKernelGGL((mlp_gemm_kernel<EPI_PART, 1, GPF>), grid, dim3(256), 0, s, g, m->kpart, kper);
     hipLaunchKernelGGL(gemm_epilogue_kernel<E>, dim3((unsigned)((cnt + 63) / 64)), dim3(64), 0, s, g,
                        (const float *)m->kpart, ks);
   };
