@@ -239,7 +239,9 @@ __device__ __forceinline__ void potf2_factor_invert(Potf2Lds &S, const FactorDes
       if (__any(!(dv > 0x1p-900 && dv < 0x1p900))) {
         load();
         potf2_eliminate<true>(d, b, dv);
-        const unsigned long long neg = __ballot(!(dv > 0.0));
+        // (an infinite pivot shows in the pivots after it, the block's last in none)
+        const bool inf_last = J == NJ - 1 && q == W - 1 && dv > 0x1.fffffffffffffp1023;
+        const unsigned long long neg = __ballot(!(dv > 0.0) || inf_last);
         if (neg && lane == 0 && S.fail == 0) S.fail = jb + __ffsll(neg);
       }
       double sq, rs;
